@@ -18,6 +18,10 @@ struct float2 {
   float x, y;
 };
 inline float2 make_float2(float a, float b) { return float2{a, b}; }
+struct float4 {
+  float x, y, z, w;
+};
+inline float4 make_float4(float a, float b, float c, float d) { return float4{a, b, c, d}; }
 
 namespace evx_emu {
 extern thread_local std::barrier<>* block_barrier;
@@ -40,6 +44,22 @@ inline float2 evx_buf_load2(evx_buf r, unsigned off) {
   if (off >= r.nbytes || r.nbytes - off < 8) return float2{0.f, 0.f};
   float2 v;
   __builtin_memcpy(&v, r.base + off, 8);
+  return v;
+}
+inline float4 evx_buf_load4(evx_buf r, unsigned off) {
+  if (off >= r.nbytes || r.nbytes - off < 16) return float4{0.f, 0.f, 0.f, 0.f};
+  float4 v;
+  __builtin_memcpy(&v, r.base + off, 16);
+  return v;
+}
+inline void evx_buf_store4(evx_buf r, unsigned off, float4 v) {
+  if (off >= r.nbytes || r.nbytes - off < 16) return;
+  __builtin_memcpy(r.base + off, &v, 16);
+}
+inline float evx_buf_load1(evx_buf r, unsigned off) {
+  if (off >= r.nbytes || r.nbytes - off < 4) return 0.f;
+  float v;
+  __builtin_memcpy(&v, r.base + off, 4);
   return v;
 }
 inline void evx_buf_store2(evx_buf r, unsigned off, float2 v) {
@@ -68,6 +88,7 @@ __device__ __forceinline__ float evx_rcp(float x) { return 1.0f / x; }
 // 32-bit vector offset; offsets at or past nbytes read zero and drop stores (hardware range check).
 typedef __amdgpu_buffer_rsrc_t evx_buf;
 typedef unsigned evx_u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned evx_u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ evx_buf evx_make_buf(const void* base, unsigned nbytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(nbytes), 0x00020000);
 }
@@ -81,10 +102,45 @@ __device__ __forceinline__ void evx_buf_store2(evx_buf r, unsigned off, float2 v
   u.y = __float_as_uint(v.y);
   __builtin_amdgcn_raw_buffer_store_b64(u, r, off, 0, 0);
 }
+__device__ __forceinline__ float4 evx_buf_load4(evx_buf r, unsigned off) {
+  const evx_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+  return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
+                     __uint_as_float(v.w));
+}
+__device__ __forceinline__ void evx_buf_store4(evx_buf r, unsigned off, float4 v) {
+  evx_u32x4 u;
+  u.x = __float_as_uint(v.x);
+  u.y = __float_as_uint(v.y);
+  u.z = __float_as_uint(v.z);
+  u.w = __float_as_uint(v.w);
+  __builtin_amdgcn_raw_buffer_store_b128(u, r, off, 0, 0);
+}
+__device__ __forceinline__ float evx_buf_load1(evx_buf r, unsigned off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
 __device__ __forceinline__ void evx_buf_store1(evx_buf r, unsigned off, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, 0, 0);
 }
 #endif
+
+// The same at a constant byte offset IMM from the lane's (the lane offset plus IMM must not wrap).
+template <int IMM>
+EVX_DEV float2 evx_buf_load2i(evx_buf r, unsigned off) {
+  return evx_buf_load2(r, off + unsigned(IMM));
+}
+template <int IMM>
+EVX_DEV void evx_buf_store2i(evx_buf r, unsigned off, float2 v) {
+  evx_buf_store2(r, off + unsigned(IMM), v);
+}
+
+template <int IMM>
+EVX_DEV float4 evx_buf_load4i(evx_buf r, unsigned off) {
+  return evx_buf_load4(r, off + unsigned(IMM));
+}
+template <int IMM>
+EVX_DEV void evx_buf_store4i(evx_buf r, unsigned off, float4 v) {
+  evx_buf_store4(r, off + unsigned(IMM), v);
+}
 
 namespace evx {
 

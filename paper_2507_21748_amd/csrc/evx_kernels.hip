@@ -83,7 +83,7 @@ static hipError_t row_go(const RowArgs& a, hipStream_t s) {
   using C = RowCfg<NH, BC>;
   const long long nblk = (a.nrows + C::ROWS - 1) / C::ROWS;
   if (nblk <= 0) return hipSuccess;
-  if (nblk > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  if (nblk > 0x7fffffffLL || !row_fits32<NH, BC>(a)) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((row_kernel<NH, BC, MODE>), dim3(unsigned(nblk)), dim3(C::THREADS), 0, s, a);
   return hipGetLastError();
 }
@@ -111,7 +111,7 @@ static hipError_t row_go_batch(const RowArgs& a, const PassBatch& p, hipStream_t
   const long long nblk = (a.nrows + C::ROWS - 1) / C::ROWS;
   if (nblk <= 0) return hipSuccess;
   if (p.n < 1 || p.n > kMaxBatch) return hipErrorInvalidValue;
-  if (nblk > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  if (nblk > 0x7fffffffLL || !row_fits32<NH, BC>(a)) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((row_kernel_batch<NH, BC, MODE>), dim3(unsigned(nblk), unsigned(p.n)),
                      dim3(C::THREADS), 0, s, a, p);
   return hipGetLastError();

@@ -189,23 +189,6 @@ EVX_DEV int remap_block(int bid, int nblk, int on) {
   return (bid % 8) * per + bid / 8;
 }
 
-EVX_DEV float fprime(float c) { return c * c * c - c; }
-
-// The fused x pass's pointwise nonlinearity: f'(c) = c^3 - c, or a cubic polynomial (Horner form
-// with explicit fused multiply-adds) for the reaction-diffusion step.
-template <int MODE>
-EVX_DEV float2 row_nonlin(const RowArgs& a, float2 v) {
-  if constexpr (MODE == ROW_FUSED_POLY) {
-    auto p = [&](float c) {
-      return __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(a.poly[3], c, a.poly[2]), c, a.poly[1]),
-                            c, a.poly[0]);
-    };
-    return make_float2(p(v.x), p(v.y));
-  } else {
-    return make_float2(fprime(v.x), fprime(v.y));
-  }
-}
-
 // Index of the cell-centred input point that becomes point n of Makhoul's reordered sequence
 // (v_n = x_{2n} for 2n < N, else x_{2N-2n-1}).
 template <int N>
@@ -580,247 +563,70 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
 }
 
 // ------------------------------------------------------------------ row pass
-// Cooperative copies between the block's contiguous slice of global memory and LDS.  Every load
-// of a thread is issued before its first LDS write, so a wave waits on memory once per copy
-// rather than once per element.  `valid` is the number of in-range float2 (ragged last block).
-template <int COUNT, int T>
-EVX_DEV void copy_in(const float2* EVX_RESTRICT src, long long valid, float2* lds, int tid) {
-  constexpr int IT = (COUNT + T - 1) / T;
-  float2 r[IT];
-  static_for<IT>([&](auto I) {
-    const int i = tid + T * decltype(I)::value;
-    r[I] = load_or_zero(src, i, i < COUNT && i < valid);
-  });
-  static_for<IT>([&](auto I) {
-    const int i = tid + T * decltype(I)::value;
-    if (i < COUNT) lds[i] = r[I];
-  });
-}
+// Spectral rows (grouped layout) <-> registers.  Lane (t, b) of a block whose first row is r0
+// holds columns k = t + TPS e of row r0 + ROWMUL b (+ 1 for the second row of a packed pair).
+// Eight consecutive t of the eight b of a wave are one contiguous 512-byte piece of a group (eight
+// rows x 64 bytes), so the rows need no staging in LDS.  Column k lies in group k / 8; over
+// P = 8 / gcd(TPS, 8) consecutive e the lanes' (group, column) offsets repeat, STEP groups
+// further on, so a lane keeps P byte offsets and every P points advance a wave-uniform base.
+//
+// A lane without a row gets an offset past the resources' range, which stays past it when a
+// point's constant offset is added (kDeadLane would wrap); live offsets span at most 8 groups and
+// the planes of one block's rows (under 0.6 GB at 1024^3; row_fits32 checks it on the host).
+constexpr unsigned kDeadRow = 0x80000000u, kRowRange = 0x7fffffffu;
 
-template <int COUNT, int T, bool ADD = false>
-EVX_DEV void copy_out(float2* EVX_RESTRICT dst, long long valid, const float2* lds, int tid) {
-  constexpr int IT = (COUNT + T - 1) / T;
-  static_for<IT>([&](auto I) {
-    const int i = tid + T * decltype(I)::value;
-    if (i < COUNT && i < valid) {
-      if constexpr (ADD) {
-        const float2 o = dst[i], v = lds[i];
-        dst[i] = make_float2(o.x + v.x, o.y + v.y);
-      } else {
-        dst[i] = lds[i];
-      }
-    }
-  });
-}
+constexpr int ct_gcd(int a, int b) { return b == 0 ? a : ct_gcd(b, a % b); }
 
-// Vertex-centred x: ROWS real rows of NR = NH + 1 floats, contiguous in the field (the block's
-// slice starts at src), copied into LDS as floats; `valid` floats are in range.
-template <int COUNT, int T>
-EVX_DEV void copy_in_floats(const float* EVX_RESTRICT src, long long valid, float* lds, int tid) {
-  constexpr int IT = (COUNT + T - 1) / T;
-  float r[IT];
-  static_for<IT>([&](auto I) {
-    const int i = tid + T * decltype(I)::value;
-    r[I] = load_or_zero(src, i, i < COUNT && i < valid);
-  });
-  static_for<IT>([&](auto I) {
-    const int i = tid + T * decltype(I)::value;
-    if (i < COUNT) lds[i] = r[I];
-  });
-}
-
-// ... and back: row b of the block holds the 2 NH points of the extension at lds[b 2 NH + j]; the
-// first NR = NH + 1 of them are the field's row (stored, or added with ADD).
-template <int ROWS, int NH, int T, bool ADD>
-EVX_DEV void copy_out_vertex(float* EVX_RESTRICT dst, long long valid_rows, const float* lds,
-                             int tid) {
-  constexpr int NR = NH + 1, COUNT = ROWS * NR, IT = (COUNT + T - 1) / T;
-  static_for<IT>([&](auto I) {
-    const int i = tid + T * decltype(I)::value;
-    const int row = i / NR, j = i - row * NR;
-    if (i < COUNT && row < valid_rows) {
-      const float v = lds[row * 2 * NH + j];
-      if constexpr (ADD) {
-        dst[i] = dst[i] + v;
-      } else {
-        dst[i] = v;
-      }
-    }
-  });
-}
-
-// Periodic complex rows: ROWS rows of NLIVE values at global pitch P are staged at LDS row
-// stride S.  T / ROWS consecutive lanes copy one row, so every global access is a contiguous run
-// within a row; the row padding is skipped on the way in and written as zeros on the way out.
-template <int ROWS, int P, int S, int NLIVE, int T>
-EVX_DEV void rows_in(const float2* EVX_RESTRICT src, long long valid_rows, float2* lds, int tid) {
-  static_assert(T % ROWS == 0, "rows must split the block evenly");
-  constexpr int TR = T / ROWS, IT = (NLIVE + TR - 1) / TR;
-  const int row = tid / TR, c0 = tid - row * TR;
-  const bool ok = row < valid_rows;
-  float2 r[IT];
-  static_for<IT>([&](auto I) {
-    const int c = c0 + TR * decltype(I)::value;
-    r[I] = load_or_zero(src, (long long)row * P + c, ok && c < NLIVE);
-  });
-  static_for<IT>([&](auto I) {
-    const int c = c0 + TR * decltype(I)::value;
-    if (c < NLIVE) lds[row * S + c] = r[I];
-  });
-}
-
-template <int ROWS, int P, int S, int NLIVE, int T, bool ADD = false>
-EVX_DEV void rows_out(float2* EVX_RESTRICT dst, long long valid_rows, const float2* lds, int tid) {
-  static_assert(T % ROWS == 0, "rows must split the block evenly");
-  constexpr int TR = T / ROWS, IT = (P + TR - 1) / TR;
-  const int row = tid / TR, c0 = tid - row * TR;
-  if (row >= valid_rows) return;
-  static_for<IT>([&](auto I) {
-    const int c = c0 + TR * decltype(I)::value;
-    if constexpr (ADD) {  // real rows only: NLIVE == P, no padding
-      static_assert(NLIVE == P, "adding rows have no padding");
-      if (c < P) {
-        const float2 o = dst[row * P + c], v = lds[row * S + c];
-        dst[row * P + c] = make_float2(o.x + v.x, o.y + v.y);
-      }
-    } else {
-      if (c < P) dst[row * P + c] = (c < NLIVE) ? lds[row * S + c] : make_float2(0.f, 0.f);
-    }
-  });
-}
-
-// Spectral rows (grouped layout) <-> LDS: rows r0 .. r0 + ROWS - 1 (those below valid_rows) of
-// NL live float2 each, staged at LDS row stride S.  Eight consecutive lanes move one row's 64-byte
-// piece of one x group and 8 ROWS consecutive lanes that group for all the block's rows, so rows
-// that share a z plane move one contiguous ROWS x 64-byte run per group.  Every load is issued
-// before the first LDS write.  Dead columns of the last group are written as zeros.
-template <int ROWS, int NL>
-struct SpecRowsCfg {
-  static constexpr int NG = (NL + 7) / 8;  // x groups
-  static constexpr int PER = 8 * ROWS;     // float2 of one group for all rows
-  static constexpr int TOT = NG * PER;
-};
-
-// With T a multiple of 8 ROWS (>= 64) a lane keeps its row and column across iterations and the
-// x group is the same for a whole wave: each group's slab is then a buffer resource with a
-// wave-uniform base and the lane adds one 32-bit offset (no per-element 64-bit addresses).
-// Within a wave the 64 lanes move rows 8 w .. 8 w + 7 (w = wave index mod ROWS / 8) of one group,
-// lane l taking column l % 8 of row 2 ((l / 8) % 4) + l / 32: the same 512 contiguous bytes per
-// wave as the plain order, but the two halves of the wave write (and read) the LDS rows
-// {0, 2, 4, 6} and {1, 3, 5, 7}, whose 64-byte segments fall in disjoint banks at the staging
-// strides used here.
-template <int ROWS, int NL, int T>
-struct SpecRowsLane {
-  using RC = SpecRowsCfg<ROWS, NL>;
-  static constexpr bool FIXED = (T % RC::PER) == 0 && RC::PER % 64 == 0;
-  int c, row;
-  long long zbase;  // float2 offset of the z plane of the block's first row (uniform)
-  unsigned off;     // byte offset of the lane's element from zbase + group, or kDeadLane
-  unsigned range;   // bytes addressable from zbase + group: the planes the block's rows reach
-  EVX_DEV SpecRowsLane(const SpecGeom& sg, long long r0, long long valid_rows, int tid) {
-    const int l = tid & 63;
-    c = l & 7;
-    row = 8 * ((tid >> 6) % (ROWS / 8)) + 2 * ((l >> 3) & 3) + (l >> 5);
+template <int TPS>
+struct SpecLane {
+  static constexpr int P = 8 / ct_gcd(TPS, 8);
+  static constexpr int STEP = TPS * P / 8;
+  long long base;   // float2 offset of the z plane of the block's first row (uniform)
+  long long gstep;  // float2 stride of STEP groups (uniform)
+  unsigned off[P];  // lane byte offset of point e from base + (e / P) gstep, or kDeadRow
+  unsigned row;     // lane byte offset of the row's column 0 from base, or kDeadRow
+  EVX_DEV SpecLane(const SpecGeom& sg, long long r0, int j, bool live, int t) {
     const long long z0 = r0 / sg.ny;
     const int y0 = int(r0 - z0 * sg.ny);
-    zbase = z0 * sg.zstride;
-    range = unsigned((ROWS / sg.ny + 2) * sg.zstride * 8);
-    off = row < valid_rows ? unsigned((spec_row_offset_from(sg, 0, y0, row) + c) * 8)
-                           : kDeadLane;
-  }
-  // x group of iteration I (wave-uniform)
-  template <int I>
-  EVX_DEV int group(int tid) const {
-    return evx_wave_uniform(tid / RC::PER) + (T / RC::PER) * I;
+    base = z0 * sg.zstride;
+    gstep = STEP * sg.xstride;
+    const unsigned gbytes = unsigned(sg.xstride * 8);
+    row = live ? unsigned(spec_row_offset_from(sg, 0, y0, j) * 8) : kDeadRow;
+    static_for<P>([&](auto R) {
+      const unsigned k = unsigned(t + TPS * decltype(R)::value);
+      off[R] = live ? row + (k >> 3) * gbytes + (k & 7u) * 8u : kDeadRow;
+    });
   }
 };
 
-// RE: the columns are complex values whose real part is the data (a cosine x transform under a
-// periodic y or z): only the real parts are staged, as floats at row stride S.
-template <int ROWS, int S, int NL, int T, bool RE = false>
-EVX_DEV void spec_rows_in(const float2* EVX_RESTRICT src, const SpecGeom& sg, long long r0,
-                          long long valid_rows, float2* lds, int tid) {
-  auto put = [&](int row, int x, float2 v) {
-    if constexpr (RE) {
-      reinterpret_cast<float*>(lds)[row * S + x] = v.x;
-    } else {
-      lds[row * S + x] = v;
-    }
-  };
-  using RC = SpecRowsCfg<ROWS, NL>;
-  using LN = SpecRowsLane<ROWS, NL, T>;
-  static_assert(T % 8 == 0, "lanes move whole 8-column pieces");
-  constexpr int IT = (RC::TOT + T - 1) / T;
-  float2 r[IT];
-  if constexpr (LN::FIXED) {
-    const LN ln(sg, r0, valid_rows, tid);
-    static_for<IT>([&](auto I) {
-      const int g = ln.template group<decltype(I)::value>(tid);
-      const bool ok = g < RC::NG && g * 8 + ln.c < NL;
-      r[I] = evx_buf_load2(evx_make_buf(src + ln.zbase + g * sg.xstride, ln.range),
-                           ok ? ln.off : kDeadLane);
+// Applies f(e, buffer resource, lane byte offset) to points e = 0 .. COUNT - 1.
+template <int COUNT, int TPS, class F>
+EVX_DEV void spec_points(const float2* p, const SpecLane<TPS>& ln, F&& f) {
+  constexpr int P = SpecLane<TPS>::P;
+  const float2* q = p + ln.base;
+  static_for<(COUNT + P - 1) / P>([&](auto M) {
+    const evx_buf r = evx_make_buf(q, kRowRange);
+    static_for<P>([&](auto R) {
+      constexpr int e = decltype(M)::value * P + decltype(R)::value;
+      if constexpr (e < COUNT) f(std::integral_constant<int, e>{}, r, ln.off[R]);
     });
-    static_for<IT>([&](auto I) {
-      const int g = ln.template group<decltype(I)::value>(tid);
-      if (g < RC::NG && g * 8 + ln.c < NL) put(ln.row, g * 8 + ln.c, r[I]);
-    });
-    return;
-  }
-  const int c = tid & 7;
-  const long long z0 = r0 / sg.ny;
-  const int y0 = int(r0 - z0 * sg.ny);
-  static_for<IT>([&](auto I) {
-    const int f = tid + T * decltype(I)::value;
-    const int g = f / RC::PER;
-    const int row = (f >> 3) % ROWS;
-    const bool ok = f < RC::TOT && row < valid_rows && g * 8 + c < NL;
-    r[I] = load_or_zero(src, g * sg.xstride + spec_row_offset_from(sg, z0, y0, row) + c, ok);
-  });
-  static_for<IT>([&](auto I) {
-    const int f = tid + T * decltype(I)::value;
-    const int g = f / RC::PER;
-    const int row = (f >> 3) % ROWS;
-    if (f < RC::TOT && g * 8 + c < NL) put(row, g * 8 + c, r[I]);
+    q += ln.gstep;
   });
 }
 
-template <int ROWS, int S, int NL, int T, bool RE = false>
-EVX_DEV void spec_rows_out(float2* EVX_RESTRICT dst, const SpecGeom& sg, long long r0,
-                           long long valid_rows, const float2* lds, int tid) {
-  auto get = [&](int row, int x) {
-    if constexpr (RE) {
-      return make_float2(reinterpret_cast<const float*>(lds)[row * S + x], 0.f);
-    } else {
-      return lds[row * S + x];
-    }
-  };
-  using RC = SpecRowsCfg<ROWS, NL>;
-  using LN = SpecRowsLane<ROWS, NL, T>;
-  static_assert(T % 8 == 0, "lanes move whole 8-column pieces");
-  constexpr int IT = (RC::TOT + T - 1) / T;
-  if constexpr (LN::FIXED) {
-    const LN ln(sg, r0, valid_rows, tid);
-    static_for<IT>([&](auto I) {
-      const int g = ln.template group<decltype(I)::value>(tid);
-      const int x = g * 8 + ln.c;
-      const float2 v = x < NL ? get(ln.row, x) : make_float2(0.f, 0.f);
-      evx_buf_store2(evx_make_buf(dst + ln.zbase + g * sg.xstride, ln.range),
-                     g < RC::NG ? ln.off : kDeadLane, v);
-    });
-    return;
-  }
-  const int c = tid & 7;
-  const long long z0 = r0 / sg.ny;
-  const int y0 = int(r0 - z0 * sg.ny);
-  static_for<IT>([&](auto I) {
-    const int f = tid + T * decltype(I)::value;
-    const int g = f / RC::PER;
-    const int row = (f >> 3) % ROWS;
-    if (f < RC::TOT && row < valid_rows) {
-      const int x = g * 8 + c;
-      dst[g * sg.xstride + spec_row_offset_from(sg, z0, y0, row) + c] =
-          x < NL ? get(row, x) : make_float2(0.f, 0.f);
-    }
+// The columns from LAST on, after the lanes' points: the value of column LAST (if its lane, t = 0,
+// has one to store) and zeros in the dead columns of its group, so that a buffer is always written
+// in whole 64-byte pieces.  LAST is periodic: the Nyquist column NH; cosine: the first dead column.
+template <int LAST, bool VALUE, int TPS>
+EVX_DEV void spec_tail_out(float2* p, const SpecGeom& sg, const SpecLane<TPS>& ln, int t,
+                           float2 v) {
+  constexpr int C0 = LAST % 8, ND = (VALUE || C0 != 0) ? 8 - C0 : 0;
+  const evx_buf r = evx_make_buf(p + ln.base + (LAST / 8) * sg.xstride, kRowRange);
+  static_for<(ND + TPS - 1) / TPS>([&](auto J) {
+    const int d = t + TPS * decltype(J)::value;
+    const bool ok = ln.row != kDeadRow && d < ND;
+    evx_buf_store2(r, ok ? ln.row + unsigned((C0 + d) * 8) : kDeadRow,
+                   VALUE && d == 0 ? v : make_float2(0.f, 0.f));
   });
 }
 
@@ -834,247 +640,469 @@ constexpr int row_lds_stride(int need, int b) {
   return s;
 }
 
+// Periodic real rows <-> registers: the block's rows are one contiguous run of the field, moved in
+// 8 V byte pieces by consecutive lanes (a row pitch that is a power of two would put lanes of
+// different rows on one memory channel: 1.87 against 1.76 ms for a pass over 1024^3) and staged in
+// LDS at a row stride of S.
+template <int B, int NH, int S, int V, int T>
+struct RealRows {
+  static constexpr int NP = NH / V, COUNT = B * NP, IT = (COUNT + T - 1) / T;
+  evx_buf buf;  // the rows that exist: pieces past them read zero and are not stored
+  float4 r[IT];
+  EVX_DEV RealRows(const float* rows, long long r0, long long nrows) {
+    const long long left = nrows - r0;
+    buf = evx_make_buf(rows + r0 * (2 * NH), unsigned(left < B ? left : B) * unsigned(NH * 8));
+  }
+  template <class F>
+  EVX_DEV void pieces(int tid, F&& f) {
+    static_for<IT>([&](auto I) {
+      const int i = tid + T * decltype(I)::value;
+      const int row = i / NP;
+      if (COUNT % T == 0 || i < COUNT) f(I, unsigned(i * 8 * V), row * S + (i - row * NP) * V);
+    });
+  }
+  EVX_DEV void load(int tid) {
+    static_for<IT>([&](auto I) {  // no branch around the loads: pieces past COUNT are out of range
+      const unsigned off = unsigned(tid + T * decltype(I)::value) * unsigned(8 * V);
+      if constexpr (V == 2) {
+        r[I] = evx_buf_load4(buf, off);
+      } else {
+        const float2 v = evx_buf_load2(buf, off);
+        r[I] = make_float4(v.x, v.y, 0.f, 0.f);
+      }
+    });
+  }
+  EVX_DEV void stage(int tid, float2* lds) {
+    pieces(tid, [&](auto I, unsigned, int at) {
+      lds[at] = make_float2(r[I].x, r[I].y);
+      if constexpr (V == 2) lds[at + 1] = make_float2(r[I].z, r[I].w);
+    });
+  }
+  // stores the staged rows, or adds them to the rows loaded before
+  template <bool ADD>
+  EVX_DEV void store(int tid, const float2* lds) {
+    pieces(tid, [&](auto I, unsigned off, int at) {
+      float2 u = lds[at], v = V == 2 ? lds[at + V - 1] : u;
+      if constexpr (ADD) {
+        u = make_float2(r[I].x + u.x, r[I].y + u.y);
+        v = make_float2(r[I].z + v.x, r[I].w + v.y);
+      }
+      if constexpr (V == 2)
+        evx_buf_store4(buf, off, make_float4(u.x, u.y, v.x, v.y));
+      else
+        evx_buf_store2(buf, off, u);
+    });
+  }
+};
+
+// Rows take the fewest sequences per workgroup that fill a wave, and at least 8 (64-byte pieces
+// of the real rows, 512-byte ones of the spectral rows per wave).
+template <int N>
+constexpr int row_seqs_per_block() {
+  int b = 8;
+  while (b * FftPlan<N>::TPS < 64) b *= 2;
+  return b;
+}
+
+// Zero flux: LDS area in which whole rows meet packed pairs of rows.  A lane moves bins of row r
+// (r = b, then B + b: a wave's accesses are then whole 128-byte lines of the grouped layout, which
+// two half-line accesses of rows 2b and 2b + 1 are not: 45 against 34 us a pass at 256^3), while
+// sequence b carries rows 2b and 2b + 1 as a + i b.  Bin n of row r is float 2B n + r plus a pad,
+// which spreads bins 2t (t of one wave) over distinct banks.
+template <int N, int B>
+struct RowXch {
+  static constexpr int SH = B == 8 ? 2 : 1;
+  static constexpr int SLOTS = B * N + B / 2 * (((N - 1) >> SH) + 1);
+  EVX_DEV static int at(int n) { return n * (2 * B) + (n >> SH) * B; }
+  // at(n0 + C), given at0 = at(n0): a constant away where C keeps the pad's phase
+  template <int C>
+  EVX_DEV static int at(int n0, int at0) {
+    if constexpr (C % (1 << SH) == 0) return at0 + C * (2 * B) + (C >> SH) * B;
+    return at(n0 + C);
+  }
+};
+
 // Periodic: template length NH = nx/2, the complex FFT length of the packed real row; the row
 // has NH+1 complex points.  Zero flux: NH = nx, one sequence carries two rows packed as a + i b.
 template <int NH, int BC>
 struct RowCfg {
   static constexpr int E = FftPlan<NH>::E;
   static constexpr int TPS = FftPlan<NH>::TPS;
-  static constexpr int B = seqs_per_block<NH>();       // sequences per block
+  static constexpr int B = row_seqs_per_block<NH>();   // sequences per block
   static constexpr int THREADS = B * TPS;
   static constexpr int ROWS = (BC == BC_PERIODIC) ? B : 2 * B;  // rows per block
-  static constexpr int SROW = row_lds_stride(NH + 1, B);  // periodic LDS row stride
-  // zero flux: 2B rows of NH floats staged at a float stride ZS with ZS/2 odd (rows 2b of the
-  // lanes b then fall in distinct banks), when the rows split the block's lanes evenly
-  static constexpr bool ZPAD = (THREADS % (2 * B)) == 0;
-  static constexpr int ZS = (!ZPAD || NH % 4 == 2) ? NH : NH + 2;
-  static constexpr int STAGE = (BC == BC_PERIODIC) ? B * SROW : B * ZS;  // float2 slots
-  static constexpr int TW = STAGE > B * NH ? STAGE : B * NH;  // twiddle table offset
-  static constexpr int PO = TW + NH;                            // post table offset
-  // post table entries: periodic keeps k <= NH/2 (the rest follows from
-  // exp(-2 pi i (NH - k) / nx) = -conj(exp(-2 pi i k / nx))); zero flux keeps all NH
-  static constexpr int NPOST = (BC == BC_PERIODIC) ? NH / 2 + 1 : NH;
-  static constexpr int LDS = PO + NPOST;
+  // real rows move in 16-byte pieces (V = 2 pairs of reals) where the row length, its LDS stride
+  // (periodic) and the lane's points (zero flux) allow it
+  static constexpr int SROW = row_lds_stride(NH, B);    // periodic: LDS stride of real rows
+  static constexpr int V =
+      (BC == BC_PERIODIC ? (NH % 2 == 0 && SROW % 2 == 0) : E % 4 == 0) ? 2 : 1;
+  // the staging area of whole rows is a little larger than the transform's exchange area
+  static constexpr int TW = (BC == BC_PERIODIC) ? B * SROW : RowXch<NH, B>::SLOTS;  // twiddles
+  static constexpr int LDS = TW + (FftPlan<NH>::S > 1 ? NH : 0);
 };
 
-// Periodic post-processing twiddle exp(-2 pi i k / nx), nx = 2 NH, 0 <= k < NH, from the half
-// table held in LDS.
-template <int NH>
-EVX_DEV float2 post_tw(const float2* po, int k) {
-  if (k <= NH / 2) return po[k];
-  const float2 w = po[NH - k];
-  return make_float2(-w.x, w.y);
+// Whether every live lane offset of a row block (SpecLane: at most 8 groups, the planes its rows
+// reach, one 64-byte piece) is below kDeadRow with room for a constant offset.
+template <int NH, int BC>
+inline bool row_fits32(const RowArgs& a) {
+  const long long planes = RowCfg<NH, BC>::ROWS / a.sg.ny + 2;
+  return (8 * a.sg.xstride + planes * a.sg.zstride + 8) * 8 < (long long)kDeadRow;
 }
 
+// C2R pre-processing, Z[k] = (X[k] + conj X[NH-k]) + i (X[k] - conj X[NH-k]) e^{+2 pi i k / nx}:
+// X = X[k], Xr = conj X[NH-k], w = e^{-2 pi i k / nx}.
+EVX_DEV float2 c2r_pre(float2 X, float2 Xr, float2 w) {
+  const float2 Ev = cadd(X, Xr);
+  const float2 Od = cmulc(csub(X, Xr), w);
+  return make_float2(Ev.x - Od.y, Ev.y + Od.x);
+}
+// R2C post-processing of the transform of half the real row (the factor 1/2 of the even and odd
+// parts travels with the input, where it is free): P = Z[k], Q = conj Z[NH-k].
+EVX_DEV float2 r2c_post(float2 P, float2 Q, float2 w) {
+  const float2 d = csub(P, Q);
+  return cadd(cadd(P, Q), cmul(w, make_float2(d.y, -d.x)));
+}
+
+// The pointwise part of the fused x pass on an inverse transform's output v (real values scale v):
+// h f'(c) or h poly(c) with c = scale v, h = 1/2 under a periodic x (r2c_post), 1 under a cosine
+// one.  Scaling by 1/2 is exact, so h changes no rounding.
+template <int MODE, bool HALF>
+EVX_DEV float row_nonlin1(float scale, const float* poly, float v) {
+  const float c = scale * v;
+  if constexpr (MODE == ROW_FUSED_POLY) {
+    constexpr float h = HALF ? 0.5f : 1.0f;
+    return __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(h * poly[3], c, h * poly[2]), c,
+                                         h * poly[1]), c, h * poly[0]);
+  } else {
+    const float hc = HALF ? (0.5f * scale) * v : c;
+    return c * c * hc - hc;
+  }
+}
+template <int MODE, bool HALF>
+EVX_DEV float2 row_nonlin(float scale, const float* poly, float2 v) {
+  return make_float2(row_nonlin1<MODE, HALF>(scale, poly, v.x),
+                     row_nonlin1<MODE, HALF>(scale, poly, v.y));
+}
+
+// What bounds this pass: with spectral rows staged through LDS it was VALU issue (87% of the SIMD
+// cycles at 1024^3 periodic, 96% at 400^3 zero flux, rocprofv3 SQ counters), a third to a half of it
+// the staging's addresses.  Spectral rows now move between memory and registers directly (994 ->
+// 777 VALU instructions a wave at length 512, about 4000 -> 2300 at 400 zero flux) and their
+// mirrored points through the transform's own exchange area.  Measured a pass, before -> after: 400^3
+// zero flux 184 -> 151 us, 256^3 zero flux 39.5 -> 34.7, 128^3 10.5 -> 9.0, 48 x 100 x 96 mixed 7.6 ->
+// 5.9; forward from real rows at 256^3 37 -> 26 us (1.3 -> 2.6 TB/s each way out of cache); at 1024^3
+// it is bound by its access pattern (65 pieces of 512 bytes a block) and stays at 2.14 ms.
 template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* lds) {
   using C = RowCfg<NH, BC>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
+  constexpr bool real_in = MODE == ROW_FWD || MODE == ROW_FWD_FP;
+  constexpr bool real_out =
+      MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC;
+  constexpr bool add = MODE == ROW_INV_ADD;
   const int b = tid % B;
   const int t = tid / B;
   // consecutive row blocks (their 8-row pieces of each x group are neighbours) on one XCD
   const long long r0 = (long long)remap_block(bid, nblk, a.remap) * C::ROWS;
-  float2 x[E];
+  float2 x[E], w[E];
   float2* const twl = lds + C::TW;
-  float2* const pol = lds + C::PO;
   TwStage<NH, T> tws;
   tws.load(a.tw, tid);
-  TableStage<C::NPOST, T, float2> pos;
-  pos.load(a.post, tid);
+  // post-processing twiddles of the lane's points, held for both directions
+  static_for<E>([&](auto e) { w[e] = a.post[t + TPS * decltype(e)::value]; });
+  // a lane's points in LDS, and its mirrored ones: slot NH - k, k = t + TPS e > 0
+  auto put = [&](int n, float2 v) { lds[lidx<B>(n, b)] = v; };
+  auto get = [&](int n) { return lds[lidx<B>(n, b)]; };
 
   if constexpr (BC == BC_PERIODIC) {
-    constexpr int NX = 2 * NH, W = C::SROW;
-    // ---------------------------------------------------------------- input
-    if constexpr (MODE == ROW_FWD || MODE == ROW_FWD_FP) {
+    const long long row = r0 + b;
+    const bool live = row < a.nrows;
+    const SpecLane<TPS> ln(a.sg, r0, b, live, t);
+    using RR = RealRows<B, NH, C::SROW, C::V, T>;
+    float2* const rowl = lds + b * C::SROW + t;  // the lane's points of its staged real row
+    // vertex-centred x: rows of NH + 1 points, 4 (b (NH + 1) + j) bytes from the block's first
+    auto voff = [&](int j) { return live ? unsigned((b * (NH + 1) + j) * 4) : kDeadRow; };
+    if constexpr (real_in) {
       if (a.vx) {
-        // vertex-centred x: rows of NH + 1 points, extended evenly about both end points to the
-        // 2 NH points the real transform takes: point j > NH is point 2 NH - j
-        float* st = reinterpret_cast<float*>(lds);
-        copy_in_floats<B * (NH + 1), T>(a.in_r + r0 * (NH + 1), (a.nrows - r0) * (NH + 1), st,
-                                        tid);
-        tws.store(twl, tid);
-        pos.store(pol, tid);
-        evx_sync();
-        const float* row = st + b * (NH + 1);
+        // extended evenly about both end points to the 2 NH points the real transform takes:
+        // point j > NH is point 2 NH - j
+        const evx_buf src = evx_make_buf(a.in_r + r0 * (NH + 1), kRowRange);
         static_for<E>([&](auto e) {
           const int j = 2 * (t + TPS * decltype(e)::value);
-          x[e] = make_float2(row[j <= NH ? j : 2 * NH - j], row[j + 1 <= NH ? j + 1 : 2 * NH - j - 1]);
+          x[e] = make_float2(evx_buf_load1(src, voff(j <= NH ? j : 2 * NH - j)),
+                             evx_buf_load1(src, voff(j + 1 <= NH ? j + 1 : 2 * NH - j - 1)));
         });
       } else {
-        // real rows, read as pairs (c[2n], c[2n+1]) into stage[b*NH + n]
-        copy_in<B * NH, T>(reinterpret_cast<const float2*>(a.in_r) + r0 * NH,
-                           (a.nrows - r0) * NH, lds, tid);
-        tws.store(twl, tid);
-        pos.store(pol, tid);
+        RR rr(a.in_r, r0, a.nrows);
+        rr.load(tid);
+        rr.stage(tid, lds);
         evx_sync();
-        static_for<E>([&](auto e) { x[e] = lds[b * NH + t + TPS * decltype(e)::value]; });
+        static_for<E>([&](auto e) { x[e] = rowl[TPS * decltype(e)::value]; });
+        evx_sync();
       }
+      tws.store(twl, tid);
       if (a.flip) {  // Dirichlet y / z: one sign per row
-        const float sg = dirichlet_sign(r0 + b, 0, a.ny, a.flip);
+        const float sg = dirichlet_sign(row, 0, a.ny, a.flip);
         static_for<E>([&](auto e) { x[e] = cscale(x[e], sg); });
       }
-      if constexpr (MODE == ROW_FWD_FP)
-        static_for<E>([&](auto e) { x[e] = make_float2(fprime(x[e].x), fprime(x[e].y)); });
-      evx_sync();
+      static_for<E>([&](auto e) {  // with the halves r2c_post leaves out
+        if constexpr (MODE == ROW_FWD_FP) {
+          x[e] = row_nonlin<MODE, true>(1.0f, nullptr, x[e]);
+        } else {
+          x[e] = cscale(x[e], 0.5f);
+        }
+      });
     } else {
-      spec_rows_in<B, W, NH + 1, T>(a.in_c, a.sg, r0, a.nrows - r0, lds, tid);
+      spec_points<E>(a.in_c, ln, [&](auto e, evx_buf r, unsigned off) {
+        x[e] = evx_buf_load2(r, off);
+      });
+      // the Nyquist column, for the lane that mirrors it (k = 0)
+      const float2 nyq =
+          evx_buf_load2(evx_make_buf(a.in_c + ln.base + (NH / 8) * a.sg.xstride, kRowRange),
+                        live && t == 0 ? ln.row + unsigned(NH % 8 * 8) : kDeadRow);
       tws.store(twl, tid);
-      pos.store(pol, tid);
+      static_for<E>([&](auto e) { put(t + TPS * decltype(e)::value, x[e]); });
       evx_sync();
-      // C2R pre-processing: Z[k] = (X[k] + conj X[NH-k]) + i (X[k] - conj X[NH-k]) e^{+2pi i k/NX}
       static_for<E>([&](auto e) {
         const int k = t + TPS * decltype(e)::value;
-        const float2 X = lds[b * W + k];
-        const float2 Xr = cconj(lds[b * W + NH - k]);
-        const float2 Ev = cadd(X, Xr);
-        const float2 Od = cmulc(csub(X, Xr), post_tw<NH>(pol, k));
-        x[e] = make_float2(Ev.x - Od.y, Ev.y + Od.x);
+        float2 m = get(decltype(e)::value == 0 && t == 0 ? 0 : NH - k);
+        if constexpr (decltype(e)::value == 0) m = t == 0 ? nyq : m;
+        x[e] = c2r_pre(x[e], cconj(m), w[e]);
       });
       evx_sync();
-      fft_regs<NH, +1, B>(x, lds, b, t, twl);
-      static_for<E>([&](auto e) { x[e] = cscale(x[e], a.scale); });
-      if constexpr (MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC) {
-        const float sg = a.flip ? dirichlet_sign(r0 + b, 0, a.ny, a.flip) : 1.0f;
-        static_for<E>([&](auto e) {
-          lds[b * NH + t + TPS * decltype(e)::value] = a.flip ? cscale(x[e], sg) : x[e];
-        });
-        evx_sync();
-        if (a.vx)
-          copy_out_vertex<B, NH, T, MODE == ROW_INV_ADD>(a.out_r + r0 * (NH + 1), a.nrows - r0,
-                                                         reinterpret_cast<const float*>(lds), tid);
-        else
-          copy_out<B * NH, T, MODE == ROW_INV_ADD>(reinterpret_cast<float2*>(a.out_r) + r0 * NH,
-                                                   (a.nrows - r0) * NH, lds, tid);
-        if constexpr (MODE == ROW_INV || MODE == ROW_INV_ADD) return;
-        evx_sync();  // the forward transform reuses the staging area
+      // real rows to add to: in flight during the transform
+      RR rr(a.out_r, r0, a.nrows);
+      if constexpr (add) {
+        if (!a.vx) rr.load(tid);
       }
-      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE>(a, x[e]); });
+      fft_regs<NH, +1, B>(x, lds, b, t, twl);
+      if constexpr (real_out) {
+        const float sg =
+            a.scale * (a.flip ? dirichlet_sign(row, 0, a.ny, a.flip) : 1.0f);
+        if (a.vx) {  // the first NH + 1 of the extension's points are the field's
+          const evx_buf dst = evx_make_buf(a.out_r + r0 * (NH + 1), kRowRange);
+          static_for<E>([&](auto e) {
+            const int j = 2 * (t + TPS * decltype(e)::value);
+            const unsigned o0 = j <= NH ? voff(j) : kDeadRow;
+            const unsigned o1 = j + 1 <= NH ? voff(j + 1) : kDeadRow;
+            float2 v = cscale(x[e], sg);
+            if constexpr (add) v = cadd(make_float2(evx_buf_load1(dst, o0), evx_buf_load1(dst, o1)), v);
+            evx_buf_store1(dst, o0, v.x);
+            evx_buf_store1(dst, o1, v.y);
+          });
+        } else {
+          static_for<E>([&](auto e) { rowl[TPS * decltype(e)::value] = cscale(x[e], sg); });
+          evx_sync();
+          rr.template store<add>(tid, lds);
+        }
+        if constexpr (MODE == ROW_FUSED_REC) evx_sync();  // the forward transform reuses the area
+        if constexpr (MODE != ROW_FUSED_REC) return;
+      }
+      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, true>(a.scale, a.poly, x[e]); });
     }
     // ---------------------------------------------------------------- forward x (R2C)
     fft_regs<NH, -1, B>(x, lds, b, t, twl);
-    static_for<E>([&](auto e) { lds[lidx<B>(t + TPS * decltype(e)::value, b)] = x[e]; });
+    static_for<E>([&](auto e) { put(t + TPS * decltype(e)::value, x[e]); });
     evx_sync();
-    float2 y[E];
-    float2 ynyq = make_float2(0.f, 0.f);
+    float2 nyq = make_float2(0.f, 0.f);
     static_for<E>([&](auto e) {
       const int k = t + TPS * decltype(e)::value;
-      const float2 P = x[e];
-      const float2 Q = cconj(lds[lidx<B>(k == 0 ? 0 : NH - k, b)]);
-      const float2 Ev = cscale(cadd(P, Q), 0.5f);
-      const float2 dq = cscale(csub(P, Q), 0.5f);
-      const float2 Od = make_float2(dq.y, -dq.x);  // -i (P - Q) / 2
-      y[e] = cadd(Ev, cmul(post_tw<NH>(pol, k), Od));
-      if (k == 0) ynyq = make_float2(Ev.x - Od.x, 0.f);
+      const float2 Q = cconj(get(decltype(e)::value == 0 && t == 0 ? 0 : NH - k));
+      // k = NH: w = -1 on the pair of k = 0
+      if constexpr (decltype(e)::value == 0) nyq = make_float2(2.0f * (x[e].x - x[e].y), 0.f);
+      x[e] = r2c_post(x[e], Q, w[e]);
     });
-    evx_sync();
-    static_for<E>([&](auto e) { lds[b * W + t + TPS * decltype(e)::value] = y[e]; });
-    if (t == 0) lds[b * W + NH] = ynyq;
-    evx_sync();
-    spec_rows_out<B, W, NH + 1, T>(a.out_c, a.sg, r0, a.nrows - r0, lds, tid);
-    (void)NX;
+    spec_points<E>(a.out_c, ln, [&](auto e, evx_buf r, unsigned off) {
+      evx_buf_store2(r, off, x[e]);
+    });
+    spec_tail_out<NH, true>(a.out_c, a.sg, ln, t, nyq);
   } else {
-    // zero flux: rows ra = r0 + 2b, rb = ra + 1, staged as floats [2B][ZS]
-    constexpr int NX = NH, ZS = C::ZS;
-    float* st = reinterpret_cast<float*>(lds);
-    constexpr bool real_in = MODE == ROW_FWD || MODE == ROW_FWD_FP;
-    constexpr int SS = C::ZPAD ? ZS / 2 : NX / 2;  // LDS row stride in float2
-    // rows are NX floats (NX even) = NX/2 float2; r0 is even
-    if constexpr (!real_in) {
-      if (a.xcplx)  // complex columns, one per bin (a periodic y or z follows)
-        spec_rows_in<2 * B, ZS, NX, T, true>(a.in_c, a.sg, r0, a.nrows - r0, lds, tid);
-      else
-        spec_rows_in<2 * B, SS, NX / 2, T>(a.in_c, a.sg, r0, a.nrows - r0, lds, tid);
-    } else if constexpr (C::ZPAD) {
-      rows_in<2 * B, NX / 2, ZS / 2, NX / 2, T>(
-          reinterpret_cast<const float2*>(a.in_r) + r0 * (NX / 2), a.nrows - r0, lds, tid);
-    } else {
-      copy_in<B * NX, T>(reinterpret_cast<const float2*>(a.in_r) + r0 * (NX / 2),
-                         (a.nrows - r0) * (NX / 2), lds, tid);
-    }
-    tws.store(twl, tid);
-    pos.store(pol, tid);
-    evx_sync();
-    if constexpr (real_in) {
-      static_for<E>([&](auto e) {
-        const int n = t + TPS * decltype(e)::value;
-        const int s = makhoul_src<NX>(n);
-        x[e] = make_float2(st[(2 * b) * ZS + s], st[(2 * b + 1) * ZS + s]);
-        if (a.flip) {
-          const long long ra = r0 + 2 * b;
-          x[e] = make_float2(x[e].x * dirichlet_sign(ra, s, a.ny, a.flip),
-                             x[e].y * dirichlet_sign(ra + 1, s, a.ny, a.flip));
+    // zero flux: sequence b packs rows r0 + 2b and r0 + 2b + 1 as a + i b; lane (t, b) moves bins of
+    // rows r0 + b and r0 + B + b (RowXch).  A spectral column is a pair of real bins (2c, 2c + 1), or
+    // with xcplx one complex column per bin.
+    static_assert(E % 2 == 0, "a lane's bins come in pairs");
+    using X = RowXch<NH, B>;
+    constexpr int NX = NH, H = E / 2, V = C::V, HV = H / V;
+    float* const st = reinterpret_cast<float*>(lds);
+    // float offsets of the lane's bin t, its mirror, and the row it moves; bins come as base + C
+    const int atp = X::at(t), atm = X::at(-t);
+    const int ate = X::at(2 * t), ato = X::at(2 * t + 1), ats = X::at(V * t), atn = X::at(-V * t);
+    float2* const prs = lds + b;   // pair b of bin n: prs[at(n) / 2]
+    float* const rwa = st + b;     // row r0 + b of bin n: rwa[at(n)]
+    float* const rwb = st + B + b;
+    const long long ra = r0 + b, rb = ra + B;
+    const bool va = ra < a.nrows, vb = rb < a.nrows;
+    const SpecLane<TPS> la(a.sg, r0, b, va, t);
+    const SpecLane<TPS> lb(a.sg, r0, B + b, vb, t);
+    // real rows: lane offsets of its first pairs from the block's first row
+    const unsigned oa = va ? unsigned((b * NX + 2 * V * t) * 4) : kDeadRow;
+    const unsigned ob = vb ? unsigned(((B + b) * NX + 2 * V * t) * 4) : kDeadRow;
+    // pairs c = V (t + TPS i) .. + V - 1 of a real row
+    auto row_in = [&](evx_buf r, unsigned off, float2 (&p)[H]) {
+      static_for<HV>([&](auto i) {
+        constexpr int iv = decltype(i)::value;
+        if constexpr (V == 2) {
+          const float4 q = evx_buf_load4i<TPS * iv * 16>(r, off);
+          p[2 * iv] = make_float2(q.x, q.y);
+          p[2 * iv + 1] = make_float2(q.z, q.w);
+        } else {
+          p[iv] = evx_buf_load2i<TPS * iv * 8>(r, off);
         }
       });
-      if constexpr (MODE == ROW_FWD_FP)
-        static_for<E>([&](auto e) { x[e] = make_float2(fprime(x[e].x), fprime(x[e].y)); });
-      evx_sync();
-    } else {
-      static_for<E>([&](auto e) {
-        const int k = t + TPS * decltype(e)::value;
-        const float Da = st[(2 * b) * ZS + k], Db = st[(2 * b + 1) * ZS + k];
-        const float Dar = (k == 0) ? 0.f : st[(2 * b) * ZS + NX - k];
-        const float Dbr = (k == 0) ? 0.f : st[(2 * b + 1) * ZS + NX - k];
-        const float2 w = cconj(pol[k]);
-        const float2 va = cmul(w, make_float2(Da, -Dar));
-        const float2 vb = cmul(w, make_float2(Db, -Dbr));
-        x[e] = make_float2(va.x - vb.y, va.y + vb.x);
+    };
+    auto row_out = [&](evx_buf r, unsigned off, const float2 (&p)[H]) {
+      static_for<HV>([&](auto i) {
+        constexpr int iv = decltype(i)::value;
+        if constexpr (V == 2)
+          evx_buf_store4i<TPS * iv * 16>(
+              r, off, make_float4(p[2 * iv].x, p[2 * iv].y, p[2 * iv + 1].x, p[2 * iv + 1].y));
+        else
+          evx_buf_store2i<TPS * iv * 8>(r, off, p[iv]);
+      });
+    };
+    // pair c holds points 2c = src(c) and 2c + 1 = src(N - 1 - c) of Makhoul's order
+    auto flip = [&](long long row, int c, float2 v) {
+      return make_float2(v.x * dirichlet_sign(row, 2 * c, a.ny, a.flip),
+                         v.y * dirichlet_sign(row, 2 * c + 1, a.ny, a.flip));
+    };
+    float2 pa[H], pb[H];
+    if constexpr (real_in) {
+      const evx_buf src = evx_make_buf(a.in_r + r0 * NX, kRowRange);
+      row_in(src, oa, pa);
+      row_in(src, ob, pb);
+      tws.store(twl, tid);
+      static_for<H>([&](auto m) {
+        constexpr int c0 = V * TPS * (decltype(m)::value / V) + decltype(m)::value % V;
+        if (a.flip) {
+          pa[m] = flip(ra, V * t + c0, pa[m]);
+          pb[m] = flip(rb, V * t + c0, pb[m]);
+        }
+        const int lo = X::template at<c0>(V * t, ats), hi = X::template at<NX - 1 - c0>(-V * t, atn);
+        rwa[lo] = pa[m].x;
+        rwa[hi] = pa[m].y;
+        rwb[lo] = pb[m].x;
+        rwb[hi] = pb[m].y;
       });
       evx_sync();
-      fft_regs<NX, +1, B>(x, lds, b, t, twl);
-      static_for<E>([&](auto e) { x[e] = cscale(x[e], a.scale); });
-      if constexpr (MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC) {
+      static_for<E>([&](auto e) { x[e] = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2]; });
+      if constexpr (MODE == ROW_FWD_FP)
+        static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, false>(1.0f, nullptr, x[e]); });
+      evx_sync();
+    } else {
+      if (a.xcplx) {  // complex columns, one per bin (a periodic y or z follows): real parts
+        float qa[E], qb[E];
+        spec_points<E>(a.in_c, la, [&](auto e, evx_buf r, unsigned off) {
+          qa[e] = evx_buf_load1(r, off);
+        });
+        spec_points<E>(a.in_c, lb, [&](auto e, evx_buf r, unsigned off) {
+          qb[e] = evx_buf_load1(r, off);
+        });
+        tws.store(twl, tid);
         static_for<E>([&](auto e) {
-          const int n = t + TPS * decltype(e)::value;
-          const int s = makhoul_src<NX>(n);
-          float va = x[e].x, vb = x[e].y;
-          if (a.flip) {
-            const long long ra = r0 + 2 * b;
-            va *= dirichlet_sign(ra, s, a.ny, a.flip);
-            vb *= dirichlet_sign(ra + 1, s, a.ny, a.flip);
-          }
-          st[(2 * b) * ZS + s] = va;
-          st[(2 * b + 1) * ZS + s] = vb;
+          const int k = X::template at<TPS * decltype(e)::value>(t, atp);
+          rwa[k] = qa[e];
+          rwb[k] = qb[e];
+        });
+      } else {
+        spec_points<H>(a.in_c, la, [&](auto i, evx_buf r, unsigned off) {
+          pa[i] = evx_buf_load2(r, off);
+        });
+        spec_points<H>(a.in_c, lb, [&](auto i, evx_buf r, unsigned off) {
+          pb[i] = evx_buf_load2(r, off);
+        });
+        tws.store(twl, tid);
+        static_for<H>([&](auto i) {
+          const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
+          const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
+          rwa[ev] = pa[i].x;
+          rwa[od] = pa[i].y;
+          rwb[ev] = pb[i].x;
+          rwb[od] = pb[i].y;
+        });
+      }
+      evx_sync();
+      static_for<E>([&](auto e) {
+        const float2 D = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2];
+        const int m = X::template at<NX - TPS * decltype(e)::value>(-t, atm);
+        float2 Dr = prs[decltype(e)::value == 0 && t == 0 ? 0 : m / 2];
+        if constexpr (decltype(e)::value == 0) Dr = t == 0 ? make_float2(0.f, 0.f) : Dr;
+        const float2 wc = cconj(w[e]);
+        const float2 za = cmul(wc, make_float2(D.x, -Dr.x));
+        const float2 zb = cmul(wc, make_float2(D.y, -Dr.y));
+        x[e] = make_float2(za.x - zb.y, za.y + zb.x);
+      });
+      evx_sync();
+      if constexpr (add) {  // real rows to add to: in flight during the transform
+        const evx_buf dst = evx_make_buf(a.out_r + r0 * NX, kRowRange);
+        row_in(dst, oa, pa);
+        row_in(dst, ob, pb);
+      }
+      fft_regs<NX, +1, B>(x, lds, b, t, twl);
+      if constexpr (real_out) {
+        static_for<E>([&](auto e) {
+          prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2] = cscale(x[e], a.scale);
         });
         evx_sync();
-        if constexpr (C::ZPAD) {
-          rows_out<2 * B, NX / 2, ZS / 2, NX / 2, T, MODE == ROW_INV_ADD>(
-              reinterpret_cast<float2*>(a.out_r) +
-                                                         r0 * (NX / 2),
-                                                     a.nrows - r0, lds, tid);
-        } else {
-          copy_out<B * NX, T, MODE == ROW_INV_ADD>(reinterpret_cast<float2*>(a.out_r) +
-                                                       r0 * (NX / 2),
-                                                   (a.nrows - r0) * (NX / 2), lds, tid);
-        }
-        if constexpr (MODE == ROW_INV || MODE == ROW_INV_ADD) return;
-        evx_sync();  // the forward transform reuses the staging area
+        static_for<H>([&](auto m) {
+          constexpr int c0 = V * TPS * (decltype(m)::value / V) + decltype(m)::value % V;
+          const int lo = X::template at<c0>(V * t, ats);
+          const int hi = X::template at<NX - 1 - c0>(-V * t, atn);
+          float2 u = make_float2(rwa[lo], rwa[hi]), v = make_float2(rwb[lo], rwb[hi]);
+          if (a.flip) {
+            u = flip(ra, V * t + c0, u);
+            v = flip(rb, V * t + c0, v);
+          }
+          pa[m] = add ? cadd(pa[m], u) : u;
+          pb[m] = add ? cadd(pb[m], v) : v;
+        });
+        const evx_buf dst = evx_make_buf(a.out_r + r0 * NX, kRowRange);
+        row_out(dst, oa, pa);
+        row_out(dst, ob, pb);
+        if constexpr (MODE != ROW_FUSED_REC) return;
+        evx_sync();  // the forward transform reuses the exchange area
       }
-      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE>(a, x[e]); });
+      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, false>(a.scale, a.poly, x[e]); });
     }
     fft_regs<NX, -1, B>(x, lds, b, t, twl);
-    static_for<E>([&](auto e) { lds[lidx<B>(t + TPS * decltype(e)::value, b)] = x[e]; });
-    evx_sync();
-    float2 y[E];
-    static_for<E>([&](auto e) {
-      const int k = t + TPS * decltype(e)::value;
-      const float2 P = x[e];
-      const float2 Q = cconj(lds[lidx<B>(k == 0 ? 0 : NX - k, b)]);
-      const float2 w = pol[k];
-      const float2 sp = cmul(w, cadd(P, Q));
-      const float2 sm = cmul(w, csub(P, Q));
-      y[e] = make_float2(sp.x, sm.y);
-    });
+    static_for<E>([&](auto e) { put(t + TPS * decltype(e)::value, x[e]); });
     evx_sync();
     static_for<E>([&](auto e) {
       const int k = t + TPS * decltype(e)::value;
-      st[(2 * b) * ZS + k] = y[e].x;
-      st[(2 * b + 1) * ZS + k] = y[e].y;
+      const float2 Q = cconj(get(decltype(e)::value == 0 && t == 0 ? 0 : NX - k));
+      const float2 sp = cmul(w[e], cadd(x[e], Q));
+      const float2 sm = cmul(w[e], csub(x[e], Q));
+      x[e] = make_float2(sp.x, sm.y);
     });
     evx_sync();
-    if (a.xcplx)
-      spec_rows_out<2 * B, ZS, NX, T, true>(a.out_c, a.sg, r0, a.nrows - r0, lds, tid);
-    else
-      spec_rows_out<2 * B, SS, NX / 2, T>(a.out_c, a.sg, r0, a.nrows - r0, lds, tid);
+    static_for<E>([&](auto e) {
+      prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2] = x[e];
+    });
+    evx_sync();
+    if (a.xcplx) {
+      spec_points<E>(a.out_c, la, [&](auto e, evx_buf r, unsigned off) {
+        evx_buf_store2(r, off, make_float2(rwa[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
+      });
+      spec_points<E>(a.out_c, lb, [&](auto e, evx_buf r, unsigned off) {
+        evx_buf_store2(r, off, make_float2(rwb[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
+      });
+      spec_tail_out<NX, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
+      spec_tail_out<NX, false>(a.out_c, a.sg, lb, t, make_float2(0.f, 0.f));
+      return;
+    }
+    static_for<H>([&](auto i) {
+      const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
+      const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
+      pa[i] = make_float2(rwa[ev], rwa[od]);
+      pb[i] = make_float2(rwb[ev], rwb[od]);
+    });
+    spec_points<H>(a.out_c, la, [&](auto i, evx_buf r, unsigned off) {
+      evx_buf_store2(r, off, pa[i]);
+    });
+    spec_points<H>(a.out_c, lb, [&](auto i, evx_buf r, unsigned off) {
+      evx_buf_store2(r, off, pb[i]);
+    });
+    spec_tail_out<NX / 2, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
+    spec_tail_out<NX / 2, false>(a.out_c, a.sg, lb, t, make_float2(0.f, 0.f));
   }
 }
 
@@ -1093,7 +1121,7 @@ struct PlaneArgs {
   int nz, ngx;
   const float2* tw_y;   // exp(-2 pi i j / NY)
   const float2* tw_x;   // exp(-2 pi i j / NH)
-  const float2* post;   // exp(-2 pi i k / (2 NH)), k <= NH / 2
+  const float2* post;   // exp(-2 pi i k / (2 NH)), k < NH
   float scale;          // 1 / (nx ny nz), applied after the inverse x transform
 };
 
@@ -1135,7 +1163,7 @@ struct PlaneCfg {
   static constexpr int PLANE = NY * PW;
   static constexpr int XCH = BY * NY > BX * NH ? BY * NY : BX * NH;  // FFT exchange area
   static constexpr int TWY = PLANE + XCH, TWX = TWY + NY, PO = TWX + NH;
-  static constexpr int NPOST = NH / 2 + 1;
+  static constexpr int NPOST = NH;
   static constexpr int LDS = PO + NPOST;  // float2 slots
   static constexpr int LOADS = (((NC + 7) / 8) * NY * 8 + THREADS - 1) / THREADS;
 };
@@ -1211,16 +1239,13 @@ EVX_DEV void planepass_body(const PlaneArgs& a, int tid, int bid, float2* lds) {
         if (act) {
           const float2 X = row[k];
           const float2 Xr = cconj(row[NH - k]);
-          const float2 Ev = cadd(X, Xr);
-          const float2 Od = cmulc(csub(X, Xr), post_tw<NH>(pol, k));
-          x[e] = make_float2(Ev.x - Od.y, Ev.y + Od.x);
+          x[e] = c2r_pre(X, Xr, pol[k]);
         } else {
           x[e] = make_float2(0.f, 0.f);
         }
       });
       fft_regs<NH, +1, B, typename C::PX>(x, xch, b, t, twx);
-      static_for<E>([&](auto e) { x[e] = cscale(x[e], a.scale); });
-      static_for<E>([&](auto e) { x[e] = make_float2(fprime(x[e].x), fprime(x[e].y)); });
+      static_for<E>([&](auto e) { x[e] = row_nonlin<ROW_FUSED, true>(a.scale, nullptr, x[e]); });
       fft_regs<NH, -1, B, typename C::PX>(x, xch, b, t, twx);
       static_for<E>([&](auto e) { xch[lidx<B>(t + TPS * decltype(e)::value, b)] = x[e]; });
       evx_sync();
@@ -1230,11 +1255,8 @@ EVX_DEV void planepass_body(const PlaneArgs& a, int tid, int bid, float2* lds) {
         const int k = t + TPS * decltype(e)::value;
         const float2 Pk = x[e];
         const float2 Q = cconj(xch[lidx<B>(k == 0 ? 0 : NH - k, b)]);
-        const float2 Ev = cscale(cadd(Pk, Q), 0.5f);
-        const float2 dq = cscale(csub(Pk, Q), 0.5f);
-        const float2 Od = make_float2(dq.y, -dq.x);  // -i (P - Q) / 2
-        yv[e] = cadd(Ev, cmul(post_tw<NH>(pol, k), Od));
-        if (k == 0) ynyq = make_float2(Ev.x - Od.x, 0.f);
+        yv[e] = r2c_post(Pk, Q, pol[k]);
+        if (k == 0) ynyq = make_float2(2.0f * (Pk.x - Pk.y), 0.f);
       });
       evx_sync();  // the exchange area is read; the next batch (or y pass) may write it
       if (act) {

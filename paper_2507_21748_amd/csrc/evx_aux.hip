@@ -32,14 +32,6 @@ hipError_t evx_launch_finite(const FiniteArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(AUX_THREADS) void gs_react_kernel(GsReactArgs a) {
-  gs_react_body(a, threadIdx.x, blockIdx.x, gridDim.x);
-}
-
-__global__ __launch_bounds__(AUX_THREADS) void gs_update_kernel(GsUpdateArgs a) {
-  gs_update_body(a, threadIdx.x, blockIdx.x, gridDim.x);
-}
-
 __global__ __launch_bounds__(VF_THREADS) void vm_fused_kernel(VmStencilArgs a, int lz) {
   __shared__ float lds[VF_LDS];
   vm_fused_body(a, lz, threadIdx.x, blockIdx.x, lds);
@@ -58,16 +50,6 @@ hipError_t evx_launch_vm_fused(const VmStencilArgs& a, hipStream_t s) {
   const long long grid = ncols * ((a.nz + lz - 1) / lz);
   if (grid >= (1LL << 31)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(vm_fused_kernel, dim3(unsigned(grid)), dim3(VF_THREADS), 0, s, a, lz);
-  return hipGetLastError();
-}
-
-hipError_t evx_launch_gs_react(const GsReactArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(gs_react_kernel, dim3(AUX_BLOCKS), dim3(AUX_THREADS), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t evx_launch_gs_update(const GsUpdateArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(gs_update_kernel, dim3(AUX_BLOCKS), dim3(AUX_THREADS), 0, s, a);
   return hipGetLastError();
 }
 

@@ -214,6 +214,8 @@ EVX_DEV void finite_body(const FiniteArgs& a, int tid, int bid, int nblk, int* r
   if (tid == 0) a.flag[bid] = red[0];
 }
 
+// The two bodies below are the Gray-Scott step's pieces taken one at a time (its kernels fuse them
+// into the x and z passes); the host emulator's launcher still offers them.
 // Gray-Scott reaction terms in real space (feed F, kill k): ru = -u v^2 + F (1 - u),
 // rv = u v^2 - k v.
 struct GsReactArgs {

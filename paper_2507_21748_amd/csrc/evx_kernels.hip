@@ -42,6 +42,15 @@ __global__ __launch_bounds__((row_threads<NH, BC>())) void row_kernel_batch(RowA
   rowpass_body<NH, BC, MODE>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
 }
 
+// the two-species fused x pass (RowArgs::gs)
+template <int NH, int BC, int MODE>
+__global__ __launch_bounds__((row_threads<NH, BC>())) void row_gs_kernel(RowArgs a) {
+  __shared__ float2 lds[RowCfg<NH, BC>::LDS];
+  rowpass_gs_body<NH, BC, MODE>(
+      a, threadIdx.x, (long long)remap_block(blockIdx.x, gridDim.x, a.remap) * RowCfg<NH, BC>::B,
+      lds);
+}
+
 // One workgroup per z plane (small periodic grids; see planepass_body).
 template <int NY, int NH>
 constexpr int plane_threads() {
@@ -84,6 +93,15 @@ static hipError_t row_go(const RowArgs& a, hipStream_t s) {
   const long long nblk = (a.nrows + C::ROWS - 1) / C::ROWS;
   if (nblk <= 0) return hipSuccess;
   if (nblk > 0x7fffffffLL || !row_fits32<NH, BC>(a)) return hipErrorInvalidConfiguration;
+  if constexpr (MODE == ROW_FUSED_POLY || MODE == ROW_FWD) {
+    if (a.gs) {
+      const long long ngs = (a.nrows + C::B - 1) / C::B;
+      if (ngs > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+      hipLaunchKernelGGL((row_gs_kernel<NH, BC, MODE>), dim3(unsigned(ngs)), dim3(C::THREADS), 0,
+                         s, a);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((row_kernel<NH, BC, MODE>), dim3(unsigned(nblk)), dim3(C::THREADS), 0, s, a);
   return hipGetLastError();
 }
@@ -152,6 +170,7 @@ static hipError_t col_mode_batch(int mode, const ColArgs& a, const PassBatch& p,
   switch (mode) {
     case COL_FWD: return col_go_batch<N, BC, COL_FWD>(a, p, s);
     case COL_INV: return col_go_batch<N, BC, COL_INV>(a, p, s);
+    case COL_Z_VM: return col_go_batch<N, BC, COL_Z_VM>(a, p, s);
     default: return hipErrorInvalidValue;
   }
 }

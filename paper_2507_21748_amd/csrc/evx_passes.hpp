@@ -86,7 +86,7 @@ enum : int {
   COL_Z_ETD = 5,       // as COL_Z_UPDATE with the exponential (ETD1) update
   COL_Z_AC = 6,        // as COL_Z_UPDATE for the Allen-Cahn model (semi-implicit)
   COL_Z_AC_ETD = 7,    // Allen-Cahn, exponential (ETD1) update
-  COL_Z_VM = 8         // in -> forward -> x dt / (1 + c4 K2^2) -> inverse -> out (no state)
+  COL_Z_VM = 8         // in -> forward -> x dt / (1 + c2 K2 + c4 K2^2) -> inverse -> out (no state)
 };
 
 // row (x) pass modes
@@ -146,6 +146,13 @@ struct RowArgs {
   int xcplx;           // cosine x: spectral columns are complex, one per bin (real data)
   int vx;              // vertex-centred x: real rows of vx = NH + 1 points, extended evenly
   float poly[4];       // ROW_FUSED_POLY: poly(c) = poly[0] + poly[1] c + poly[2] c^2 + poly[3] c^3
+  // Two-species pass (ROW_FUSED_POLY or ROW_FWD with gs set): in_c / in_r and out_c belong to u,
+  // these to v; the pointwise part is one explicit reaction step of Gray-Scott (gs_react).
+  int gs;
+  const float2* in_c2;
+  const float* in_r2;
+  float2* out_c2;
+  float gs_dt, gs_F, gs_k;
 };
 
 // (-1)^(i [x Dirichlet] + j [y Dirichlet] + l [z Dirichlet]) of point i of row r = j + ny l
@@ -164,10 +171,12 @@ struct PassBatch {
   const void* in[kMaxBatch];
   void* out[kMaxBatch];
   int n;
+  float a_dt[kMaxBatch];  // ColArgs::a_dt of each pair (the two-species z pass)
 };
 EVX_HD void bind_batch(ColArgs& a, const PassBatch& b, int k) {
   a.in = static_cast<const float2*>(b.in[k]);
   a.out = static_cast<float2*>(b.out[k]);
+  a.a_dt = b.a_dt[k];
 }
 // forward modes read real rows and write complex ones; the inverse does the opposite
 EVX_HD void bind_batch(RowArgs& a, bool inverse, const PassBatch& b, int k) {
@@ -485,16 +494,24 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
   }
 
   if constexpr (vm) {
-    // Increment multiplier of the variable-mobility step, x <- dt x / (1 + c4 K2^2): dt travels
-    // in dt_m and c4 = 2 dt gamma0 eps M0 in dt_m_kappa.  No state.
+    // Implicit multiplier without a state, x <- dt x / (1 + c2 K2 + c4 K2^2) (c2 in a_dt, c4 in
+    // dt_m_kappa, dt in dt_m): the variable-mobility increment (c4 = 2 dt gamma0 eps M0) and
+    // Gray-Scott's diffusion (c2 = dt D, dt_m = 1).  One reciprocal a bin: an FP32 division costs
+    // about ten VALU instructions, and two of them a point were a fifth of this pass's.
     evx_sync();  // K2 table visible
-    static_for<E>([&](auto e) {
-      const int k = t + TPS * decltype(e)::value;
-      const float kr = k2l[k];
-      const float K2a = kca + kr, K2b = kcb + kr;
-      x[e] = make_float2(a.dt_m * x[e].x / (1.0f + a.dt_m_kappa * K2a * K2a),
-                         a.dt_m * x[e].y / (1.0f + a.dt_m_kappa * K2b * K2b));
-    });
+    auto mult = [&](float K2) {
+      return a.dt_m * evx_rcp_fast(1.0f + a.a_dt * K2 + a.dt_m_kappa * K2 * K2);
+    };
+    if (a.xcomplex) {
+      static_for<E>([&](auto e) {
+        x[e] = cscale(x[e], mult(kca + k2l[t + TPS * decltype(e)::value]));
+      });
+    } else {
+      static_for<E>([&](auto e) {
+        const float kr = k2l[t + TPS * decltype(e)::value];
+        x[e] = make_float2(x[e].x * mult(kca + kr), x[e].y * mult(kcb + kr));
+      });
+    }
   }
 
   if constexpr (upd) {
@@ -784,6 +801,329 @@ EVX_DEV float2 row_nonlin(float scale, const float* poly, float2 v) {
                      row_nonlin1<MODE, HALF>(scale, poly, v.y));
 }
 
+// A periodic row's half spectrum x (Nyquist column nyq, held by lane t = 0) to the input of the
+// inverse transform, and back; w: post-processing twiddles of the lane's points.  The exchange
+// area must be free on entry; row_c2r leaves it free, row_r2c does not.
+template <int NH, int B>
+EVX_DEV void row_c2r(float2 (&x)[FftPlan<NH>::E], float2 nyq, const float2 (&w)[FftPlan<NH>::E],
+                     float2* lds, int b, int t) {
+  constexpr int E = FftPlan<NH>::E, TPS = FftPlan<NH>::TPS;
+  static_for<E>([&](auto e) { lds[lidx<B>(t + TPS * decltype(e)::value, b)] = x[e]; });
+  evx_sync();
+  static_for<E>([&](auto e) {
+    const int k = t + TPS * decltype(e)::value;
+    float2 m = lds[lidx<B>(decltype(e)::value == 0 && t == 0 ? 0 : NH - k, b)];
+    if constexpr (decltype(e)::value == 0) m = t == 0 ? nyq : m;
+    x[e] = c2r_pre(x[e], cconj(m), w[e]);
+  });
+  evx_sync();
+}
+template <int NH, int B>
+EVX_DEV float2 row_r2c(float2 (&x)[FftPlan<NH>::E], const float2 (&w)[FftPlan<NH>::E],
+                       float2* lds, int b, int t) {
+  constexpr int E = FftPlan<NH>::E, TPS = FftPlan<NH>::TPS;
+  float2 nyq = make_float2(0.f, 0.f);
+  static_for<E>([&](auto e) { lds[lidx<B>(t + TPS * decltype(e)::value, b)] = x[e]; });
+  evx_sync();
+  static_for<E>([&](auto e) {
+    const int k = t + TPS * decltype(e)::value;
+    const float2 Q = cconj(lds[lidx<B>(decltype(e)::value == 0 && t == 0 ? 0 : NH - k, b)]);
+    // k = NH: w = -1 on the pair of k = 0
+    if constexpr (decltype(e)::value == 0) nyq = make_float2(2.0f * (x[e].x - x[e].y), 0.f);
+    x[e] = r2c_post(x[e], Q, w[e]);
+  });
+  return nyq;
+}
+
+// A periodic block's spectral rows: the lane's points and, for lane t = 0, the Nyquist column.
+template <int NH>
+EVX_DEV float2 spec_row_in(const float2* p, const SpecGeom& sg, const SpecLane<FftPlan<NH>::TPS>& ln,
+                           int t, float2 (&x)[FftPlan<NH>::E]) {
+  spec_points<FftPlan<NH>::E>(p, ln, [&](auto e, evx_buf r, unsigned off) {
+    x[e] = evx_buf_load2(r, off);
+  });
+  return evx_buf_load2(evx_make_buf(p + ln.base + (NH / 8) * sg.xstride, kRowRange),
+                       ln.row != kDeadRow && t == 0 ? ln.row + unsigned(NH % 8 * 8) : kDeadRow);
+}
+template <int NH>
+EVX_DEV void spec_row_out(float2* p, const SpecGeom& sg, const SpecLane<FftPlan<NH>::TPS>& ln,
+                          int t, const float2 (&x)[FftPlan<NH>::E], float2 nyq) {
+  spec_points<FftPlan<NH>::E>(p, ln, [&](auto e, evx_buf r, unsigned off) {
+    evx_buf_store2(r, off, x[e]);
+  });
+  spec_tail_out<NH, true>(p, sg, ln, t, nyq);
+}
+
+// One explicit Gray-Scott reaction step of a point, scaled by h (r2c_post's half): u, v are scale
+// times the given values; sg is the point's Dirichlet sign (the fields then carry it, and of the
+// reaction's terms only the constant feed does not).
+EVX_DEV void gs_react(const RowArgs& a, float scale, float h, float sg, float& u, float& v) {
+  const float cu = scale * u, cv = scale * v;
+  const float uv2 = cu * cv * cv;
+  u = h * __builtin_fmaf(a.gs_dt, a.gs_F * (sg - cu) - uv2, cu);
+  v = h * __builtin_fmaf(a.gs_dt, uv2 - a.gs_k * cv, cv);
+}
+
+// Real rows of a periodic-family block to the lane's points x (pairs of reals), with the Dirichlet
+// sign of y / z; `tables` runs once the loads are issued.  Leaves the exchange area free.
+template <int NH, int B, class F>
+EVX_DEV void real_row_in(const RowArgs& a, const float* in, long long r0, int tid, F&& tables,
+                         float2* lds, float2 (&x)[FftPlan<NH>::E]) {
+  using C = RowCfg<NH, BC_PERIODIC>;
+  constexpr int E = C::E, TPS = C::TPS;
+  const int b = tid % B, t = tid / B;
+  const long long row = r0 + b;
+  if (a.vx) {
+    // vertex-centred x: rows of NH + 1 points, extended evenly about both end points to the 2 NH
+    // points the real transform takes: point j > NH is point 2 NH - j
+    const evx_buf src = evx_make_buf(in + r0 * (NH + 1), kRowRange);
+    auto at = [&](int j) {
+      return row < a.nrows ? unsigned((b * (NH + 1) + (j <= NH ? j : 2 * NH - j)) * 4) : kDeadRow;
+    };
+    static_for<E>([&](auto e) {
+      const int j = 2 * (t + TPS * decltype(e)::value);
+      x[e] = make_float2(evx_buf_load1(src, at(j)), evx_buf_load1(src, at(j + 1)));
+    });
+    tables();
+  } else {
+    RealRows<B, NH, C::SROW, C::V, C::THREADS> rr(in, r0, a.nrows);
+    rr.load(tid);
+    tables();
+    rr.stage(tid, lds);
+    evx_sync();
+    static_for<E>([&](auto e) { x[e] = lds[b * C::SROW + t + TPS * decltype(e)::value]; });
+    evx_sync();
+  }
+  if (a.flip) {  // Dirichlet y / z: one sign per row
+    const float sg = dirichlet_sign(row, 0, a.ny, a.flip);
+    static_for<E>([&](auto e) { x[e] = cscale(x[e], sg); });
+  }
+}
+
+// Cosine rows.  GS = false: sequence b packs rows r0 + 2b and r0 + 2b + 1 as a + i b, and lane (t, b)
+// moves bins of rows r0 + b and r0 + B + b (RowXch).  GS = true: sequence b packs row r0 + b of the
+// two species as u + i v.  A spectral column is a pair of real bins (2c, 2c + 1), or with xcplx one
+// complex column per bin.
+template <int NH, int MODE, bool GS>
+EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
+  using C = RowCfg<NH, BC_ZERO_FLUX>;
+  constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
+  constexpr bool real_in = MODE == ROW_FWD || MODE == ROW_FWD_FP;
+  constexpr bool real_out =
+      MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC;
+  constexpr bool add = MODE == ROW_INV_ADD;
+  const int b = tid % B;
+  const int t = tid / B;
+  float2 x[E], w[E];
+  float2* const twl = lds + C::TW;
+  TwStage<NH, T> tws;
+  tws.load(a.tw, tid);
+  static_for<E>([&](auto e) { w[e] = a.post[t + TPS * decltype(e)::value]; });
+  auto put = [&](int n, float2 v) { lds[lidx<B>(n, b)] = v; };
+  auto get = [&](int n) { return lds[lidx<B>(n, b)]; };
+  static_assert(E % 2 == 0, "a lane's bins come in pairs");
+  using X = RowXch<NH, B>;
+  constexpr int NX = NH, H = E / 2, V = C::V, HV = H / V;
+  float* const st = reinterpret_cast<float*>(lds);
+  // float offsets of the lane's bin t, its mirror, and the row it moves; bins come as base + C
+  const int atp = X::at(t), atm = X::at(-t);
+  const int ate = X::at(2 * t), ato = X::at(2 * t + 1), ats = X::at(V * t), atn = X::at(-V * t);
+  float2* const prs = lds + b;   // pair b of bin n: prs[at(n) / 2]
+  float* const rwa = st + (GS ? 2 * b : b);           // the lane's first row of bin n: rwa[at(n)]
+  float* const rwb = st + (GS ? 2 * b + 1 : B + b);   // and its second
+  const float2* const in_b = GS ? a.in_c2 : a.in_c;
+  float2* const out_b = GS ? a.out_c2 : a.out_c;
+  const long long ra = r0 + b, rb = GS ? ra : ra + B;  // rows whose bins the lane moves
+  const bool va = ra < a.nrows, vb = rb < a.nrows;
+  const SpecLane<TPS> la(a.sg, r0, b, va, t);
+  const SpecLane<TPS> lb(a.sg, r0, int(rb - r0), vb, t);
+  // real rows: lane offsets of its first pairs from the block's first row
+  const unsigned oa = va ? unsigned((b * NX + 2 * V * t) * 4) : kDeadRow;
+  const unsigned ob = vb ? unsigned((int(rb - r0) * NX + 2 * V * t) * 4) : kDeadRow;
+  // pairs c = V (t + TPS i) .. + V - 1 of a real row
+  auto row_in = [&](evx_buf r, unsigned off, float2 (&p)[H]) {
+    static_for<HV>([&](auto i) {
+      constexpr int iv = decltype(i)::value;
+      if constexpr (V == 2) {
+        const float4 q = evx_buf_load4i<TPS * iv * 16>(r, off);
+        p[2 * iv] = make_float2(q.x, q.y);
+        p[2 * iv + 1] = make_float2(q.z, q.w);
+      } else {
+        p[iv] = evx_buf_load2i<TPS * iv * 8>(r, off);
+      }
+    });
+  };
+  auto row_out = [&](evx_buf r, unsigned off, const float2 (&p)[H]) {
+    static_for<HV>([&](auto i) {
+      constexpr int iv = decltype(i)::value;
+      if constexpr (V == 2)
+        evx_buf_store4i<TPS * iv * 16>(
+            r, off, make_float4(p[2 * iv].x, p[2 * iv].y, p[2 * iv + 1].x, p[2 * iv + 1].y));
+      else
+        evx_buf_store2i<TPS * iv * 8>(r, off, p[iv]);
+    });
+  };
+  // pair c holds points 2c = src(c) and 2c + 1 = src(N - 1 - c) of Makhoul's order
+  // Dirichlet signs: of the lane's rows at even points, and of odd points against even ones
+  float sa = 1.0f, sb = 1.0f;
+  if (a.flip) {
+    sa = dirichlet_sign(ra, 0, a.ny, a.flip);
+    sb = dirichlet_sign(rb, 0, a.ny, a.flip);
+  }
+  const float sodd = (a.flip & 1) ? -1.0f : 1.0f;
+  auto flip = [&](float sg, float2 v) { return make_float2(v.x * sg, v.y * (sg * sodd)); };
+  // the two-species reaction
+  auto react = [&](float scale) {
+    static_for<E>([&](auto e) {
+      // (the first half of the order are the row's even points, the second its odd ones)
+      gs_react(a, scale, 1.0f, decltype(e)::value < H ? sa : sa * sodd, x[e].x, x[e].y);
+    });
+  };
+  float2 pa[H], pb[H];
+  if constexpr (real_in) {
+    const evx_buf src = evx_make_buf(a.in_r + r0 * NX, kRowRange);
+    row_in(src, oa, pa);
+    row_in(GS ? evx_make_buf(a.in_r2 + r0 * NX, kRowRange) : src, ob, pb);
+    tws.store(twl, tid);
+    static_for<H>([&](auto m) {
+      constexpr int c0 = V * TPS * (decltype(m)::value / V) + decltype(m)::value % V;
+      if (a.flip) {
+        pa[m] = flip(sa, pa[m]);
+        pb[m] = flip(sb, pb[m]);
+      }
+      const int lo = X::template at<c0>(V * t, ats), hi = X::template at<NX - 1 - c0>(-V * t, atn);
+      rwa[lo] = pa[m].x;
+      rwa[hi] = pa[m].y;
+      rwb[lo] = pb[m].x;
+      rwb[hi] = pb[m].y;
+    });
+    evx_sync();
+    static_for<E>([&](auto e) { x[e] = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2]; });
+    if constexpr (MODE == ROW_FWD_FP)
+      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, false>(1.0f, nullptr, x[e]); });
+    evx_sync();
+    if constexpr (GS) react(1.0f);
+  } else {
+    if (a.xcplx) {  // complex columns, one per bin (a periodic y or z follows): real parts
+      float qa[E], qb[E];
+      spec_points<E>(a.in_c, la, [&](auto e, evx_buf r, unsigned off) {
+        qa[e] = evx_buf_load1(r, off);
+      });
+      spec_points<E>(in_b, lb, [&](auto e, evx_buf r, unsigned off) {
+        qb[e] = evx_buf_load1(r, off);
+      });
+      tws.store(twl, tid);
+      static_for<E>([&](auto e) {
+        const int k = X::template at<TPS * decltype(e)::value>(t, atp);
+        rwa[k] = qa[e];
+        rwb[k] = qb[e];
+      });
+    } else {
+      spec_points<H>(a.in_c, la, [&](auto i, evx_buf r, unsigned off) {
+        pa[i] = evx_buf_load2(r, off);
+      });
+      spec_points<H>(in_b, lb, [&](auto i, evx_buf r, unsigned off) {
+        pb[i] = evx_buf_load2(r, off);
+      });
+      tws.store(twl, tid);
+      static_for<H>([&](auto i) {
+        const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
+        const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
+        rwa[ev] = pa[i].x;
+        rwa[od] = pa[i].y;
+        rwb[ev] = pb[i].x;
+        rwb[od] = pb[i].y;
+      });
+    }
+    evx_sync();
+    static_for<E>([&](auto e) {
+      const float2 D = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2];
+      const int m = X::template at<NX - TPS * decltype(e)::value>(-t, atm);
+      float2 Dr = prs[decltype(e)::value == 0 && t == 0 ? 0 : m / 2];
+      if constexpr (decltype(e)::value == 0) Dr = t == 0 ? make_float2(0.f, 0.f) : Dr;
+      const float2 wc = cconj(w[e]);
+      const float2 za = cmul(wc, make_float2(D.x, -Dr.x));
+      const float2 zb = cmul(wc, make_float2(D.y, -Dr.y));
+      x[e] = make_float2(za.x - zb.y, za.y + zb.x);
+    });
+    evx_sync();
+    if constexpr (add) {  // real rows to add to: in flight during the transform
+      const evx_buf dst = evx_make_buf(a.out_r + r0 * NX, kRowRange);
+      row_in(dst, oa, pa);
+      row_in(dst, ob, pb);
+    }
+    fft_regs<NX, +1, B>(x, lds, b, t, twl);
+    if constexpr (real_out) {
+      static_for<E>([&](auto e) {
+        prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2] = cscale(x[e], a.scale);
+      });
+      evx_sync();
+      static_for<H>([&](auto m) {
+        constexpr int c0 = V * TPS * (decltype(m)::value / V) + decltype(m)::value % V;
+        const int lo = X::template at<c0>(V * t, ats);
+        const int hi = X::template at<NX - 1 - c0>(-V * t, atn);
+        float2 u = make_float2(rwa[lo], rwa[hi]), v = make_float2(rwb[lo], rwb[hi]);
+        if (a.flip) {
+          u = flip(sa, u);
+          v = flip(sb, v);
+        }
+        pa[m] = add ? cadd(pa[m], u) : u;
+        pb[m] = add ? cadd(pb[m], v) : v;
+      });
+      const evx_buf dst = evx_make_buf(a.out_r + r0 * NX, kRowRange);
+      row_out(dst, oa, pa);
+      row_out(dst, ob, pb);
+      if constexpr (MODE != ROW_FUSED_REC) return;
+      evx_sync();  // the forward transform reuses the exchange area
+    }
+    if constexpr (GS) {
+      react(a.scale);
+    } else {
+      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, false>(a.scale, a.poly, x[e]); });
+    }
+  }
+  fft_regs<NX, -1, B>(x, lds, b, t, twl);
+  static_for<E>([&](auto e) { put(t + TPS * decltype(e)::value, x[e]); });
+  evx_sync();
+  static_for<E>([&](auto e) {
+    const int k = t + TPS * decltype(e)::value;
+    const float2 Q = cconj(get(decltype(e)::value == 0 && t == 0 ? 0 : NX - k));
+    const float2 sp = cmul(w[e], cadd(x[e], Q));
+    const float2 sm = cmul(w[e], csub(x[e], Q));
+    x[e] = make_float2(sp.x, sm.y);
+  });
+  evx_sync();
+  static_for<E>([&](auto e) {
+    prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2] = x[e];
+  });
+  evx_sync();
+  if (a.xcplx) {
+    spec_points<E>(a.out_c, la, [&](auto e, evx_buf r, unsigned off) {
+      evx_buf_store2(r, off, make_float2(rwa[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
+    });
+    spec_points<E>(out_b, lb, [&](auto e, evx_buf r, unsigned off) {
+      evx_buf_store2(r, off, make_float2(rwb[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
+    });
+    spec_tail_out<NX, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
+    spec_tail_out<NX, false>(out_b, a.sg, lb, t, make_float2(0.f, 0.f));
+    return;
+  }
+  static_for<H>([&](auto i) {
+    const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
+    const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
+    pa[i] = make_float2(rwa[ev], rwa[od]);
+    pb[i] = make_float2(rwb[ev], rwb[od]);
+  });
+  spec_points<H>(a.out_c, la, [&](auto i, evx_buf r, unsigned off) {
+    evx_buf_store2(r, off, pa[i]);
+  });
+  spec_points<H>(out_b, lb, [&](auto i, evx_buf r, unsigned off) {
+    evx_buf_store2(r, off, pb[i]);
+  });
+  spec_tail_out<NX / 2, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
+  spec_tail_out<NX / 2, false>(out_b, a.sg, lb, t, make_float2(0.f, 0.f));
+}
+
 // What bounds this pass: with spectral rows staged through LDS it was VALU issue (87% of the SIMD
 // cycles at 1024^3 periodic, 96% at 400^3 zero flux, rocprofv3 SQ counters), a third to a half of it
 // the staging's addresses.  Spectral rows now move between memory and registers directly (994 ->
@@ -793,6 +1133,9 @@ EVX_DEV float2 row_nonlin(float scale, const float* poly, float2 v) {
 // 5.9; forward from real rows at 256^3 37 -> 26 us (1.3 -> 2.6 TB/s each way out of cache); at 1024^3
 // it is bound by its access pattern (65 pieces of 512 bytes a block) and stays at 2.14 ms.
 template <int NH, int BC, int MODE>
+EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* lds);
+
+template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* lds) {
   using C = RowCfg<NH, BC>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
@@ -800,21 +1143,27 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
   constexpr bool real_out =
       MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC;
   constexpr bool add = MODE == ROW_INV_ADD;
-  const int b = tid % B;
-  const int t = tid / B;
+  if constexpr (kEmulated && (MODE == ROW_FUSED_POLY || MODE == ROW_FWD)) {
+    if (a.gs) {  // on the GPU a kernel of its own
+      const long long r0 = (long long)bid * C::ROWS;
+      for (long long r = r0; r < r0 + C::ROWS && r < a.nrows; r += B) {
+        rowpass_gs_body<NH, BC, MODE>(a, tid, r, lds);
+        evx_sync();
+      }
+      return;
+    }
+  }
   // consecutive row blocks (their 8-row pieces of each x group are neighbours) on one XCD
   const long long r0 = (long long)remap_block(bid, nblk, a.remap) * C::ROWS;
-  float2 x[E], w[E];
-  float2* const twl = lds + C::TW;
-  TwStage<NH, T> tws;
-  tws.load(a.tw, tid);
-  // post-processing twiddles of the lane's points, held for both directions
-  static_for<E>([&](auto e) { w[e] = a.post[t + TPS * decltype(e)::value]; });
-  // a lane's points in LDS, and its mirrored ones: slot NH - k, k = t + TPS e > 0
-  auto put = [&](int n, float2 v) { lds[lidx<B>(n, b)] = v; };
-  auto get = [&](int n) { return lds[lidx<B>(n, b)]; };
-
   if constexpr (BC == BC_PERIODIC) {
+    const int b = tid % B;
+    const int t = tid / B;
+    float2 x[E], w[E];
+    float2* const twl = lds + C::TW;
+    TwStage<NH, T> tws;
+    tws.load(a.tw, tid);
+    // post-processing twiddles of the lane's points, held for both directions
+    static_for<E>([&](auto e) { w[e] = a.post[t + TPS * decltype(e)::value]; });
     const long long row = r0 + b;
     const bool live = row < a.nrows;
     const SpecLane<TPS> ln(a.sg, r0, b, live, t);
@@ -823,28 +1172,7 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     // vertex-centred x: rows of NH + 1 points, 4 (b (NH + 1) + j) bytes from the block's first
     auto voff = [&](int j) { return live ? unsigned((b * (NH + 1) + j) * 4) : kDeadRow; };
     if constexpr (real_in) {
-      if (a.vx) {
-        // extended evenly about both end points to the 2 NH points the real transform takes:
-        // point j > NH is point 2 NH - j
-        const evx_buf src = evx_make_buf(a.in_r + r0 * (NH + 1), kRowRange);
-        static_for<E>([&](auto e) {
-          const int j = 2 * (t + TPS * decltype(e)::value);
-          x[e] = make_float2(evx_buf_load1(src, voff(j <= NH ? j : 2 * NH - j)),
-                             evx_buf_load1(src, voff(j + 1 <= NH ? j + 1 : 2 * NH - j - 1)));
-        });
-      } else {
-        RR rr(a.in_r, r0, a.nrows);
-        rr.load(tid);
-        rr.stage(tid, lds);
-        evx_sync();
-        static_for<E>([&](auto e) { x[e] = rowl[TPS * decltype(e)::value]; });
-        evx_sync();
-      }
-      tws.store(twl, tid);
-      if (a.flip) {  // Dirichlet y / z: one sign per row
-        const float sg = dirichlet_sign(row, 0, a.ny, a.flip);
-        static_for<E>([&](auto e) { x[e] = cscale(x[e], sg); });
-      }
+      real_row_in<NH, B>(a, a.in_r, r0, tid, [&] { tws.store(twl, tid); }, lds, x);
       static_for<E>([&](auto e) {  // with the halves r2c_post leaves out
         if constexpr (MODE == ROW_FWD_FP) {
           x[e] = row_nonlin<MODE, true>(1.0f, nullptr, x[e]);
@@ -853,23 +1181,9 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
         }
       });
     } else {
-      spec_points<E>(a.in_c, ln, [&](auto e, evx_buf r, unsigned off) {
-        x[e] = evx_buf_load2(r, off);
-      });
-      // the Nyquist column, for the lane that mirrors it (k = 0)
-      const float2 nyq =
-          evx_buf_load2(evx_make_buf(a.in_c + ln.base + (NH / 8) * a.sg.xstride, kRowRange),
-                        live && t == 0 ? ln.row + unsigned(NH % 8 * 8) : kDeadRow);
+      const float2 nyq = spec_row_in<NH>(a.in_c, a.sg, ln, t, x);
       tws.store(twl, tid);
-      static_for<E>([&](auto e) { put(t + TPS * decltype(e)::value, x[e]); });
-      evx_sync();
-      static_for<E>([&](auto e) {
-        const int k = t + TPS * decltype(e)::value;
-        float2 m = get(decltype(e)::value == 0 && t == 0 ? 0 : NH - k);
-        if constexpr (decltype(e)::value == 0) m = t == 0 ? nyq : m;
-        x[e] = c2r_pre(x[e], cconj(m), w[e]);
-      });
-      evx_sync();
+      row_c2r<NH, B>(x, nyq, w, lds, b, t);
       // real rows to add to: in flight during the transform
       RR rr(a.out_r, r0, a.nrows);
       if constexpr (add) {
@@ -902,207 +1216,60 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     }
     // ---------------------------------------------------------------- forward x (R2C)
     fft_regs<NH, -1, B>(x, lds, b, t, twl);
-    static_for<E>([&](auto e) { put(t + TPS * decltype(e)::value, x[e]); });
-    evx_sync();
-    float2 nyq = make_float2(0.f, 0.f);
-    static_for<E>([&](auto e) {
-      const int k = t + TPS * decltype(e)::value;
-      const float2 Q = cconj(get(decltype(e)::value == 0 && t == 0 ? 0 : NH - k));
-      // k = NH: w = -1 on the pair of k = 0
-      if constexpr (decltype(e)::value == 0) nyq = make_float2(2.0f * (x[e].x - x[e].y), 0.f);
-      x[e] = r2c_post(x[e], Q, w[e]);
-    });
-    spec_points<E>(a.out_c, ln, [&](auto e, evx_buf r, unsigned off) {
-      evx_buf_store2(r, off, x[e]);
-    });
-    spec_tail_out<NH, true>(a.out_c, a.sg, ln, t, nyq);
+    const float2 nyq = row_r2c<NH, B>(x, w, lds, b, t);
+    spec_row_out<NH>(a.out_c, a.sg, ln, t, x, nyq);
   } else {
-    // zero flux: sequence b packs rows r0 + 2b and r0 + 2b + 1 as a + i b; lane (t, b) moves bins of
-    // rows r0 + b and r0 + B + b (RowXch).  A spectral column is a pair of real bins (2c, 2c + 1), or
-    // with xcplx one complex column per bin.
-    static_assert(E % 2 == 0, "a lane's bins come in pairs");
-    using X = RowXch<NH, B>;
-    constexpr int NX = NH, H = E / 2, V = C::V, HV = H / V;
-    float* const st = reinterpret_cast<float*>(lds);
-    // float offsets of the lane's bin t, its mirror, and the row it moves; bins come as base + C
-    const int atp = X::at(t), atm = X::at(-t);
-    const int ate = X::at(2 * t), ato = X::at(2 * t + 1), ats = X::at(V * t), atn = X::at(-V * t);
-    float2* const prs = lds + b;   // pair b of bin n: prs[at(n) / 2]
-    float* const rwa = st + b;     // row r0 + b of bin n: rwa[at(n)]
-    float* const rwb = st + B + b;
-    const long long ra = r0 + b, rb = ra + B;
-    const bool va = ra < a.nrows, vb = rb < a.nrows;
-    const SpecLane<TPS> la(a.sg, r0, b, va, t);
-    const SpecLane<TPS> lb(a.sg, r0, B + b, vb, t);
-    // real rows: lane offsets of its first pairs from the block's first row
-    const unsigned oa = va ? unsigned((b * NX + 2 * V * t) * 4) : kDeadRow;
-    const unsigned ob = vb ? unsigned(((B + b) * NX + 2 * V * t) * 4) : kDeadRow;
-    // pairs c = V (t + TPS i) .. + V - 1 of a real row
-    auto row_in = [&](evx_buf r, unsigned off, float2 (&p)[H]) {
-      static_for<HV>([&](auto i) {
-        constexpr int iv = decltype(i)::value;
-        if constexpr (V == 2) {
-          const float4 q = evx_buf_load4i<TPS * iv * 16>(r, off);
-          p[2 * iv] = make_float2(q.x, q.y);
-          p[2 * iv + 1] = make_float2(q.z, q.w);
-        } else {
-          p[iv] = evx_buf_load2i<TPS * iv * 8>(r, off);
-        }
-      });
-    };
-    auto row_out = [&](evx_buf r, unsigned off, const float2 (&p)[H]) {
-      static_for<HV>([&](auto i) {
-        constexpr int iv = decltype(i)::value;
-        if constexpr (V == 2)
-          evx_buf_store4i<TPS * iv * 16>(
-              r, off, make_float4(p[2 * iv].x, p[2 * iv].y, p[2 * iv + 1].x, p[2 * iv + 1].y));
-        else
-          evx_buf_store2i<TPS * iv * 8>(r, off, p[iv]);
-      });
-    };
-    // pair c holds points 2c = src(c) and 2c + 1 = src(N - 1 - c) of Makhoul's order
-    auto flip = [&](long long row, int c, float2 v) {
-      return make_float2(v.x * dirichlet_sign(row, 2 * c, a.ny, a.flip),
-                         v.y * dirichlet_sign(row, 2 * c + 1, a.ny, a.flip));
-    };
-    float2 pa[H], pb[H];
-    if constexpr (real_in) {
-      const evx_buf src = evx_make_buf(a.in_r + r0 * NX, kRowRange);
-      row_in(src, oa, pa);
-      row_in(src, ob, pb);
-      tws.store(twl, tid);
-      static_for<H>([&](auto m) {
-        constexpr int c0 = V * TPS * (decltype(m)::value / V) + decltype(m)::value % V;
-        if (a.flip) {
-          pa[m] = flip(ra, V * t + c0, pa[m]);
-          pb[m] = flip(rb, V * t + c0, pb[m]);
-        }
-        const int lo = X::template at<c0>(V * t, ats), hi = X::template at<NX - 1 - c0>(-V * t, atn);
-        rwa[lo] = pa[m].x;
-        rwa[hi] = pa[m].y;
-        rwb[lo] = pb[m].x;
-        rwb[hi] = pb[m].y;
-      });
-      evx_sync();
-      static_for<E>([&](auto e) { x[e] = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2]; });
-      if constexpr (MODE == ROW_FWD_FP)
-        static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, false>(1.0f, nullptr, x[e]); });
-      evx_sync();
+    cos_rows<NH, MODE, false>(a, tid, r0, lds);
+  }
+}
+
+// The two-species fused x pass: u and v to real rows, one explicit reaction step, and back (MODE
+// ROW_FUSED_POLY; ROW_FWD starts from real rows) for the B rows from r0.  Periodic rows: a lane
+// holds its points of both species.  Cosine rows: one sequence holds a row of both.
+// Bound by memory traffic and occupancy (96 to 190 VGPRs for both species' points): 61 us at 256^3
+// periodic, 4.4 TB/s.  With a reaction kernel, four fields' forward transforms and an update kernel
+// of its own a step took 0.61 ms at 256^3; with this pass and the multiplier in the z pass 0.19 ms.
+template <int NH, int BC, int MODE>
+EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* lds) {
+  using C = RowCfg<NH, BC>;
+  if constexpr (BC != BC_PERIODIC) {
+    cos_rows<NH, MODE, true>(a, tid, r0, lds);
+  } else {
+    constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
+    const int b = tid % B;
+    const int t = tid / B;
+    const long long row = r0 + b;
+    float2 u[E], v[E], w[E];
+    float2* const twl = lds + C::TW;
+    TwStage<NH, T> tws;
+    tws.load(a.tw, tid);
+    static_for<E>([&](auto e) { w[e] = a.post[t + TPS * decltype(e)::value]; });
+    const SpecLane<TPS> ln(a.sg, r0, b, row < a.nrows, t);
+    if constexpr (MODE == ROW_FWD) {
+      real_row_in<NH, B>(a, a.in_r, r0, tid, [&] { tws.store(twl, tid); }, lds, u);
+      real_row_in<NH, B>(a, a.in_r2, r0, tid, [] {}, lds, v);
     } else {
-      if (a.xcplx) {  // complex columns, one per bin (a periodic y or z follows): real parts
-        float qa[E], qb[E];
-        spec_points<E>(a.in_c, la, [&](auto e, evx_buf r, unsigned off) {
-          qa[e] = evx_buf_load1(r, off);
-        });
-        spec_points<E>(a.in_c, lb, [&](auto e, evx_buf r, unsigned off) {
-          qb[e] = evx_buf_load1(r, off);
-        });
-        tws.store(twl, tid);
-        static_for<E>([&](auto e) {
-          const int k = X::template at<TPS * decltype(e)::value>(t, atp);
-          rwa[k] = qa[e];
-          rwb[k] = qb[e];
-        });
-      } else {
-        spec_points<H>(a.in_c, la, [&](auto i, evx_buf r, unsigned off) {
-          pa[i] = evx_buf_load2(r, off);
-        });
-        spec_points<H>(a.in_c, lb, [&](auto i, evx_buf r, unsigned off) {
-          pb[i] = evx_buf_load2(r, off);
-        });
-        tws.store(twl, tid);
-        static_for<H>([&](auto i) {
-          const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
-          const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
-          rwa[ev] = pa[i].x;
-          rwa[od] = pa[i].y;
-          rwb[ev] = pb[i].x;
-          rwb[od] = pb[i].y;
-        });
-      }
-      evx_sync();
-      static_for<E>([&](auto e) {
-        const float2 D = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2];
-        const int m = X::template at<NX - TPS * decltype(e)::value>(-t, atm);
-        float2 Dr = prs[decltype(e)::value == 0 && t == 0 ? 0 : m / 2];
-        if constexpr (decltype(e)::value == 0) Dr = t == 0 ? make_float2(0.f, 0.f) : Dr;
-        const float2 wc = cconj(w[e]);
-        const float2 za = cmul(wc, make_float2(D.x, -Dr.x));
-        const float2 zb = cmul(wc, make_float2(D.y, -Dr.y));
-        x[e] = make_float2(za.x - zb.y, za.y + zb.x);
-      });
-      evx_sync();
-      if constexpr (add) {  // real rows to add to: in flight during the transform
-        const evx_buf dst = evx_make_buf(a.out_r + r0 * NX, kRowRange);
-        row_in(dst, oa, pa);
-        row_in(dst, ob, pb);
-      }
-      fft_regs<NX, +1, B>(x, lds, b, t, twl);
-      if constexpr (real_out) {
-        static_for<E>([&](auto e) {
-          prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2] = cscale(x[e], a.scale);
-        });
-        evx_sync();
-        static_for<H>([&](auto m) {
-          constexpr int c0 = V * TPS * (decltype(m)::value / V) + decltype(m)::value % V;
-          const int lo = X::template at<c0>(V * t, ats);
-          const int hi = X::template at<NX - 1 - c0>(-V * t, atn);
-          float2 u = make_float2(rwa[lo], rwa[hi]), v = make_float2(rwb[lo], rwb[hi]);
-          if (a.flip) {
-            u = flip(ra, V * t + c0, u);
-            v = flip(rb, V * t + c0, v);
-          }
-          pa[m] = add ? cadd(pa[m], u) : u;
-          pb[m] = add ? cadd(pb[m], v) : v;
-        });
-        const evx_buf dst = evx_make_buf(a.out_r + r0 * NX, kRowRange);
-        row_out(dst, oa, pa);
-        row_out(dst, ob, pb);
-        if constexpr (MODE != ROW_FUSED_REC) return;
-        evx_sync();  // the forward transform reuses the exchange area
-      }
-      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, false>(a.scale, a.poly, x[e]); });
+      const float2 nu = spec_row_in<NH>(a.in_c, a.sg, ln, t, u);
+      const float2 nv = spec_row_in<NH>(a.in_c2, a.sg, ln, t, v);
+      tws.store(twl, tid);
+      row_c2r<NH, B>(u, nu, w, lds, b, t);
+      fft_regs<NH, +1, B>(u, lds, b, t, twl);
+      row_c2r<NH, B>(v, nv, w, lds, b, t);
+      fft_regs<NH, +1, B>(v, lds, b, t, twl);
     }
-    fft_regs<NX, -1, B>(x, lds, b, t, twl);
-    static_for<E>([&](auto e) { put(t + TPS * decltype(e)::value, x[e]); });
-    evx_sync();
+    const float sg = a.flip ? dirichlet_sign(row, 0, a.ny, a.flip) : 1.0f;
+    const float scale = MODE == ROW_FWD ? 1.0f : a.scale;
     static_for<E>([&](auto e) {
-      const int k = t + TPS * decltype(e)::value;
-      const float2 Q = cconj(get(decltype(e)::value == 0 && t == 0 ? 0 : NX - k));
-      const float2 sp = cmul(w[e], cadd(x[e], Q));
-      const float2 sm = cmul(w[e], csub(x[e], Q));
-      x[e] = make_float2(sp.x, sm.y);
+      gs_react(a, scale, 0.5f, sg, u[e].x, v[e].x);
+      gs_react(a, scale, 0.5f, sg, u[e].y, v[e].y);
     });
-    evx_sync();
-    static_for<E>([&](auto e) {
-      prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2] = x[e];
-    });
-    evx_sync();
-    if (a.xcplx) {
-      spec_points<E>(a.out_c, la, [&](auto e, evx_buf r, unsigned off) {
-        evx_buf_store2(r, off, make_float2(rwa[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
-      });
-      spec_points<E>(a.out_c, lb, [&](auto e, evx_buf r, unsigned off) {
-        evx_buf_store2(r, off, make_float2(rwb[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
-      });
-      spec_tail_out<NX, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
-      spec_tail_out<NX, false>(a.out_c, a.sg, lb, t, make_float2(0.f, 0.f));
-      return;
-    }
-    static_for<H>([&](auto i) {
-      const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
-      const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
-      pa[i] = make_float2(rwa[ev], rwa[od]);
-      pb[i] = make_float2(rwb[ev], rwb[od]);
-    });
-    spec_points<H>(a.out_c, la, [&](auto i, evx_buf r, unsigned off) {
-      evx_buf_store2(r, off, pa[i]);
-    });
-    spec_points<H>(a.out_c, lb, [&](auto i, evx_buf r, unsigned off) {
-      evx_buf_store2(r, off, pb[i]);
-    });
-    spec_tail_out<NX / 2, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
-    spec_tail_out<NX / 2, false>(a.out_c, a.sg, lb, t, make_float2(0.f, 0.f));
+    fft_regs<NH, -1, B>(u, lds, b, t, twl);
+    const float2 nu = row_r2c<NH, B>(u, w, lds, b, t);
+    spec_row_out<NH>(a.out_c, a.sg, ln, t, u, nu);
+    evx_sync();  // the mirrored points are read
+    fft_regs<NH, -1, B>(v, lds, b, t, twl);
+    const float2 nv = row_r2c<NH, B>(v, w, lds, b, t);
+    spec_row_out<NH>(a.out_c2, a.sg, ln, t, v, nv);
   }
 }
 

@@ -128,7 +128,10 @@ void sched_distance(L& l, const Geom& g, const float* a, const float* b, const A
 // reaction explicit, U' = T[u + dt R_u] / (1 + dt Du K2): the transform is linear, so each species
 // transforms its field and reaction together, and the multiplier needs no spectral state.  Between
 // steps both species stay spectral (A and B hold F_z^{-1} of them): a step is the two y passes, the
-// two-species x pass with the reaction, and one z pass with the multiplier, 64 bytes a voxel.
+// two-species x pass with the reaction, and one z pass with the multiplier, 64 bytes a voxel.  The
+// species' means travel beside the buffers (spec_mean): adding the reaction to the whole field
+// instead rounded relative to the mean at every step (relative error of 20 steps at 64^3 and 128^3
+// 4.0e-7 against 2.7e-7 with separately transformed reactions).  A Dirichlet axis has no mean mode.
 struct GsCoef {
   float dt, dt_du, dt_dv, F, k;
 };
@@ -150,9 +153,14 @@ void sched_gray_scott(L& l, const Geom& g, const TablePtrs& t, float* u, float* 
   const StepCoef zc{0.0f, 0.0f, 1.0f};  // a_dt comes with the batch
   for (int n = 0; n < nsteps; ++n) {
     if (n > 0) l.col_batch(g.fy, g.bcy, COL_INV, y_args(g, t, b.A, b.A, remap), two);
+    ColArgs za = z_args(g, t, b.A, b.A, nullptr, zc, remap);
+    if (!g.flip) {
+      xa.mean = n > 0 ? MEAN_IN : 0;
+      za.mean = xa.mean | (n + 1 < nsteps ? MEAN_OUT : 0);
+    }
     l.row(g.row_len, g.bc, n > 0 ? ROW_FUSED_POLY : ROW_FWD, xa);
     l.col_batch(g.fy, g.bcy, COL_FWD, y_args(g, t, b.A, b.A, remap), two);
-    l.col_batch(g.fz, g.bcz, COL_Z_VM, z_args(g, t, b.A, b.A, nullptr, zc, remap), two);
+    l.col_batch(g.fz, g.bcz, COL_Z_VM, za, two);
   }
   l.col_batch(g.fy, g.bcy, COL_INV, y_args(g, t, b.A, b.A, remap), two);
   const PassBatch back{{b.A, b.B}, {u, v}, 2};

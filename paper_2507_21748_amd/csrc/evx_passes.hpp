@@ -127,6 +127,7 @@ struct ColArgs {
   float dt_m;              // dt M
   int remap;               // XCD-aware block order
   int xcomplex;            // z pass: a column is one complex x bin (else two real x bins)
+  int mean;                // COL_Z_VM: MEAN_* (the buffer's mean travels beside it, see spec_mean)
   unsigned lane_bytes;     // bytes addressable from a point's block base (col_lane_bytes)
 };
 
@@ -153,7 +154,16 @@ struct RowArgs {
   const float* in_r2;
   float2* out_c2;
   float gs_dt, gs_F, gs_k;
+  int mean;            // MEAN_IN: in_c and in_c2 lack their means (spec_mean)
 };
+
+// A spectral buffer may lack its mean: its bin 0 is then zero and the bin's value, an FP64 number,
+// lies in the first pad row of (group 0, plane 0), which no pass addresses otherwise.  A nearly
+// uniform field then rounds relative to its fluctuations instead of its mean.
+enum : int { MEAN_IN = 1, MEAN_OUT = 2 };
+EVX_HD double* spec_mean(const float2* p, int ny) {
+  return reinterpret_cast<double*>(const_cast<float2*>(p) + 8 * (long long)ny);
+}
 
 // (-1)^(i [x Dirichlet] + j [y Dirichlet] + l [z Dirichlet]) of point i of row r = j + ny l
 EVX_HD float dirichlet_sign(long long r, int i, int ny, int mask) {
@@ -502,6 +512,12 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     auto mult = [&](float K2) {
       return a.dt_m * evx_rcp_fast(1.0f + a.a_dt * K2 + a.dt_m_kappa * K2 * K2);
     };
+    if (a.mean && ct.tile == 0 && b == 0 && t == 0) {  // bin 0, whose multiplier is dt
+      double* const m = spec_mean(a.out, a.n_lo);
+      const double v = double(x[0].x) + ((a.mean & MEAN_IN) ? *m : 0.0);
+      x[0].x = (a.mean & MEAN_OUT) ? 0.0f : float(v);
+      if (a.mean & MEAN_OUT) *m = v;
+    }
     if (a.xcomplex) {
       static_for<E>([&](auto e) {
         x[e] = cscale(x[e], mult(kca + k2l[t + TPS * decltype(e)::value]));
@@ -855,13 +871,22 @@ EVX_DEV void spec_row_out(float2* p, const SpecGeom& sg, const SpecLane<FftPlan<
 }
 
 // One explicit Gray-Scott reaction step of a point, scaled by h (r2c_post's half): u, v are scale
-// times the given values; sg is the point's Dirichlet sign (the fields then carry it, and of the
-// reaction's terms only the constant feed does not).
-EVX_DEV void gs_react(const RowArgs& a, float scale, float h, float sg, float& u, float& v) {
-  const float cu = scale * u, cv = scale * v;
+// times the given values plus their means mu, mv, which the results lack too; sg is the point's
+// Dirichlet sign (the fields then carry it, and of the reaction's terms only the constant feed does
+// not).
+EVX_DEV void gs_react(const RowArgs& a, float scale, float h, float sg, float mu, float mv, float& u,
+                      float& v) {
+  const float du = scale * u, dv = scale * v;
+  const float cu = du + mu, cv = dv + mv;
   const float uv2 = cu * cv * cv;
-  u = h * __builtin_fmaf(a.gs_dt, a.gs_F * (sg - cu) - uv2, cu);
-  v = h * __builtin_fmaf(a.gs_dt, uv2 - a.gs_k * cv, cv);
+  u = h * __builtin_fmaf(a.gs_dt, a.gs_F * (sg - cu) - uv2, du);
+  v = h * __builtin_fmaf(a.gs_dt, uv2 - a.gs_k * cv, dv);
+}
+// The means of the two species of a block's input.
+EVX_DEV float2 gs_means(const RowArgs& a) {
+  if (!(a.mean & MEAN_IN)) return make_float2(0.f, 0.f);
+  return make_float2(float(*spec_mean(a.in_c, a.sg.ny) * a.scale),
+                     float(*spec_mean(a.in_c2, a.sg.ny) * a.scale));
 }
 
 // Real rows of a periodic-family block to the lane's points x (pairs of reals), with the Dirichlet
@@ -973,10 +998,12 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   const float sodd = (a.flip & 1) ? -1.0f : 1.0f;
   auto flip = [&](float sg, float2 v) { return make_float2(v.x * sg, v.y * (sg * sodd)); };
   // the two-species reaction
+  const float2 mean = GS && !real_in ? gs_means(a) : make_float2(0.f, 0.f);
   auto react = [&](float scale) {
     static_for<E>([&](auto e) {
       // (the first half of the order are the row's even points, the second its odd ones)
-      gs_react(a, scale, 1.0f, decltype(e)::value < H ? sa : sa * sodd, x[e].x, x[e].y);
+      gs_react(a, scale, 1.0f, decltype(e)::value < H ? sa : sa * sodd, mean.x, mean.y, x[e].x,
+               x[e].y);
     });
   };
   float2 pa[H], pb[H];
@@ -1259,9 +1286,10 @@ EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* ld
     }
     const float sg = a.flip ? dirichlet_sign(row, 0, a.ny, a.flip) : 1.0f;
     const float scale = MODE == ROW_FWD ? 1.0f : a.scale;
+    const float2 mean = MODE == ROW_FWD ? make_float2(0.f, 0.f) : gs_means(a);
     static_for<E>([&](auto e) {
-      gs_react(a, scale, 0.5f, sg, u[e].x, v[e].x);
-      gs_react(a, scale, 0.5f, sg, u[e].y, v[e].y);
+      gs_react(a, scale, 0.5f, sg, mean.x, mean.y, u[e].x, v[e].x);
+      gs_react(a, scale, 0.5f, sg, mean.x, mean.y, u[e].y, v[e].y);
     });
     fft_regs<NH, -1, B>(u, lds, b, t, twl);
     const float2 nu = row_r2c<NH, B>(u, w, lds, b, t);

@@ -291,19 +291,23 @@ struct VmStencilArgs {
 };
 
 // mu and div(M grad mu) in one pass: a block owns a VF_X x VF_Y column and marches up lz of its
-// z planes, with phi (2-point xy halo) and mu (1-point halo) held
-// in LDS rings of 4 and 3 planes.  Per plane z it loads phi of plane z + 2, evaluates mu on plane
-// z + 1 and the fluxes on plane z:
+// z planes:
 //   mu = c_g p (1 - p)(1 - 2 p) - c_lap (sum of the 6 neighbours' phi - 6 p),
 //   div(M grad mu) = c_flux sum_faces (p (1 - p) + q (1 - q)) (mu_q - mu_p),
-// the neighbours taken in the order +x, -x, +y, -y, +z, -z; mu never leaves LDS (8 bytes per
-// voxel).  On a zero-flux axis phi is loaded clamped (the ghost is the edge cell) and mu at a
-// point past the grid is evaluated at the clamped point, i.e. it is the edge cell's mu, so the
+// the neighbours and faces taken in the order +x, -x, +y, -y, +z, -z; mu never leaves the block (8
+// bytes per voxel).  On a zero-flux axis phi is loaded clamped (the ghost is the edge cell) and a
 // boundary face carries no flux.
-constexpr int VF_X = 32, VF_Y = 16, VF_THREADS = VF_X * VF_Y;
-constexpr int VF_PX = VF_X + 4, VF_PY = VF_Y + 4, VF_PP = VF_PX * VF_PY;  // phi plane: 36 x 20
-constexpr int VF_MX = VF_X + 2, VF_MY = VF_Y + 2, VF_MP = VF_MX * VF_MY;  // mu plane: 34 x 18
-constexpr int VF_LDS = 4 * VF_PP + 3 * VF_MP;                              // floats
+//
+// What bounds it: with one point a lane and all six neighbours read from LDS rings it was
+// instruction issue (119 VALU and 104 scalar instructions a voxel, 75 us at 256^3, 1.8 TB/s).  A
+// lane owns VF_R consecutive rows of one x: its z neighbours are registers, its y neighbours mostly
+// too, a y or z face is evaluated once for the two voxels it joins, and the planes' LDS images
+// (phi with a 2-point halo, mu with a 1-point halo, two of each) are addressed by constants: 52 us,
+// 2.6 TB/s.  What remains is two barriers a plane and the 128-byte rows of a 32-wide column.
+constexpr int VF_X = 32, VF_Y = 32, VF_R = 4, VF_THREADS = VF_X * VF_Y / VF_R;
+constexpr int VF_P = 40;  // row pitch of both images: rows VF_R apart fall in opposite bank halves
+constexpr int VF_PP = VF_P * (VF_Y + 4), VF_MP = VF_P * (VF_Y + 2);
+constexpr int VF_LDS = 2 * (VF_PP + VF_MP);  // floats
 
 EVX_DEV int vf_mod(int v, int n) {
   const int r = v % n;
@@ -324,86 +328,143 @@ inline int vm_fused_lz(const VmStencilArgs& a, int cus) {
   return int(lz);
 }
 
+// Point q of the square ring of half-open box [-h, VF_X + h) x [-h, VF_Y + h): its top and bottom
+// rows, then its left and right columns between them.
+EVX_DEV void vf_ring(int q, int h, int& x, int& y) {
+  const int w = VF_X + 2 * h, c = VF_Y + 2 * h - 2;
+  if (q < 2 * w) {
+    y = q < w ? -h : VF_Y + h - 1;
+    x = (q < w ? q : q - w) - h;
+  } else {
+    q -= 2 * w;
+    x = q < c ? -h : VF_X + h - 1;
+    y = (q < c ? q : q - c) - h + 1;
+  }
+}
+
 // Launch: ceil(nx / VF_X) ceil(ny / VF_Y) columns times ceil(nz / lz) z ranges, VF_THREADS each.
 EVX_DEV void vm_fused_body(const VmStencilArgs& a, int lz, int tid, int bid, float* lds) {
+  constexpr int R = VF_R, P = VF_P;
+  constexpr int RING1 = 2 * (VF_X + 2) + 2 * VF_Y, RING2 = 2 * (VF_X + 4) + 2 * (VF_Y + 2);
+  static_assert(RING1 <= VF_THREADS && RING2 <= VF_THREADS, "one halo point of each ring a lane");
   const int ntx = (a.nx + VF_X - 1) / VF_X, nty = (a.ny + VF_Y - 1) / VF_Y;
   const int ncols = ntx * nty;
   const int col = bid % ncols, chunk = bid / ncols;
   const int x0 = (col % ntx) * VF_X, y0 = (col / ntx) * VF_Y;
   const int z0 = chunk * lz, z1 = z0 + lz < a.nz ? z0 + lz : a.nz;
-  float* const P = lds;               // [4][VF_PP]
-  float* const M = lds + 4 * VF_PP;   // [3][VF_MP]
-  auto pl = [&](int z) { return P + vf_mod(z, 4) * VF_PP; };
-  auto ml = [&](int z) { return M + vf_mod(z, 3) * VF_MP; };
-  // a phi plane travels through registers: its loads are issued a plane ahead of the LDS
-  // writes, every lane always loads (clamped index), and the flux stores below are buffer
-  // stores issued by every lane, so the compiler waits for the loads alone
-  constexpr int PIT = (VF_PP + VF_THREADS - 1) / VF_THREADS;
-  int src_xy[PIT];
   const bool px = a.per & 1, py = a.per & 2, pz = a.per & 4;
-  for (int k = 0; k < PIT; ++k) {
-    const int i0 = tid + k * VF_THREADS, i = i0 < VF_PP ? i0 : 0;
-    src_xy[k] = vf_map(y0 + i / VF_PX - 2, a.ny, py) * a.nx + vf_map(x0 + i % VF_PX - 2, a.nx, px);
-  }
-  const int plane = a.nx * a.ny;
-  float nxt[PIT];
-  auto fetch_phi = [&](int z) {
-    const float* src = a.phi + vf_map(z, a.nz, pz) * plane;
-    for (int k = 0; k < PIT; ++k) nxt[k] = src[src_xy[k]];
+  const int tx = tid % VF_X, ty = R * (tid / VF_X);
+  // the lane's points: R own rows, one of the 1-point ring (mu there too), one of the 2-point ring;
+  // lanes past a ring repeat its first point
+  auto src = [&](int x, int y) {
+    return unsigned(vf_map(y0 + y, a.ny, py) * a.nx + vf_map(x0 + x, a.nx, px)) * 4u;
   };
-  auto put_phi = [&](int z) {
-    float* dst = pl(z);
-    for (int k = 0; k < PIT; ++k)
-      if (tid + k * VF_THREADS < VF_PP) dst[tid + k * VF_THREADS] = nxt[k];
+  unsigned own[R];
+  static_for<R>([&](auto r) { own[r] = src(tx, ty + decltype(r)::value); });
+  int x1, y1, x2, y2;
+  vf_ring(tid < RING1 ? tid : 0, 1, x1, y1);
+  vf_ring(tid < RING2 ? tid : 0, 2, x2, y2);
+  const unsigned src1 = src(x1, y1), src2 = src(x2, y2);
+  const int p0 = (ty + 2) * P + tx + 2, m0 = (ty + 1) * P + tx + 1;  // own first point: phi, mu
+  const int p1 = (y1 + 2) * P + x1 + 2, m1 = (y1 + 1) * P + x1 + 1;
+  const int p2 = (y2 + 2) * P + x2 + 2;
+  // boundary faces of zero-flux axes, by whether the lane's face carries flux
+  const bool fxp = px || x0 + tx + 1 < a.nx, fxm = px || x0 + tx > 0;
+  const int ylast = py ? 0x7fffffff : a.ny - 1 - (y0 + ty);  // own row with no +y face
+  const bool fym = py || y0 + ty > 0;
+  const unsigned plane = unsigned(a.nx) * unsigned(a.ny) * 4u;
+  const long long pstep = (long long)a.nx * a.ny;
+  struct Plane {
+    float o[R], e, c;  // own rows, 1-point ring, 2-point ring
   };
-  auto calc_mu = [&](int z) {
-    const int zc = pz ? z : vf_map(z, a.nz, false);
-    const float *pc = pl(zc), *pu = pl(zc + 1), *pd = pl(zc - 1);
-    float* dst = ml(z);
-    for (int i = tid; i < VF_MP; i += VF_THREADS) {
-      // the point in the phi plane (clamped into the grid along zero-flux axes)
-      const int gx = x0 + i % VF_MX - 1, gy = y0 + i / VF_MX - 1;
-      const int mx = i % VF_MX + (px ? 0 : vf_map(gx, a.nx, false) - gx);
-      const int my = i / VF_MX + (py ? 0 : vf_map(gy, a.ny, false) - gy);
-      const int c = (my + 1) * VF_PX + mx + 1;
-      const float p = pc[c];
-      float s = 0.0f;
-      s += pc[c + 1];
-      s += pc[c - 1];
-      s += pc[c + VF_PX];
-      s += pc[c - VF_PX];
-      s += pu[c];
-      s += pd[c];
-      dst[i] = a.c_g * p * (1.0f - p) * (1.0f - 2.0f * p) - a.c_lap * (s - 6.0f * p);
+  auto fetch = [&](int z, Plane& q) {
+    const evx_buf b = evx_make_buf(a.phi + vf_map(z, a.nz, pz) * pstep, plane);
+    static_for<R>([&](auto r) { q.o[r] = evx_buf_load1(b, own[r]); });
+    q.e = evx_buf_load1(b, src1);
+    q.c = evx_buf_load1(b, src2);
+  };
+  auto mu_of = [&](float p, float xp, float xm, float yp, float ym, float zp, float zm) {
+    float s = 0.0f;
+    s += xp;
+    s += xm;
+    s += yp;
+    s += ym;
+    s += zp;
+    s += zm;
+    return a.c_g * p * (1.0f - p) * (1.0f - 2.0f * p) - a.c_lap * (s - 6.0f * p);
+  };
+  Plane dn, cur, up, nxt;  // phi of planes k - 1, k, k + 1, k + 2
+  fetch(z0 - 2, dn);
+  fetch(z0 - 1, cur);
+  fetch(z0, up);
+  float md[R], mud[R], fz[R], acc[R];  // plane k - 1: p (1 - p), mu, its lower face's flux, sum
+  static_for<R>([&](auto r) { md[r] = mud[r] = fz[r] = acc[r] = 0.0f; });
+  for (int k = z0 - 1; k <= z1; ++k) {
+    float* const ph = lds + (k & 1) * VF_PP;
+    float* const mu = lds + 2 * VF_PP + (k & 1) * VF_MP;
+    static_for<R>([&](auto r) { ph[p0 + P * decltype(r)::value] = cur.o[r]; });
+    if (tid < RING1) ph[p1] = cur.e;
+    if (tid < RING2) ph[p2] = cur.c;
+    fetch(k + 2, nxt);  // past the range on the last planes: a mapped plane, loaded and unused
+    evx_sync();
+    float xp[R], xm[R], u[R], m[R];
+    const float yl = ph[p0 - P], yh = ph[p0 + P * R];
+    static_for<R>([&](auto r) {
+      constexpr int j = decltype(r)::value;
+      xp[j] = ph[p0 + P * j + 1];
+      xm[j] = ph[p0 + P * j - 1];
+    });
+    static_for<R>([&](auto r) {
+      constexpr int j = decltype(r)::value;
+      const float p = cur.o[j];
+      u[j] = mu_of(p, xp[j], xm[j], j + 1 < R ? cur.o[j + 1 < R ? j + 1 : j] : yh,
+                   j > 0 ? cur.o[j > 0 ? j - 1 : j] : yl, up.o[j], dn.o[j]);
+      m[j] = p * (1.0f - p);
+      mu[m0 + P * j] = u[j];
+    });
+    if (tid < RING1)
+      mu[m1] = mu_of(cur.e, ph[p1 + 1], ph[p1 - 1], ph[p1 + P], ph[p1 - P], up.e, dn.e);
+    evx_sync();
+    // the +z faces of plane k - 1 (the -z faces of plane k), which complete plane k - 1
+    const bool face = pz || (k > 0 && k < a.nz);
+    static_for<R>([&](auto r) {
+      constexpr int j = decltype(r)::value;
+      const float f = face ? (md[j] + m[j]) * (u[j] - mud[j]) : 0.0f;
+      const float sum = (acc[j] + f) - fz[j];
+      fz[j] = f;
+      acc[j] = sum;
+    });
+    if (k > z0) {
+      const evx_buf b = evx_make_buf(a.out + (long long)(k - 1) * pstep, plane);
+      const bool in = x0 + tx < a.nx;
+      static_for<R>([&](auto r) {
+        constexpr int j = decltype(r)::value;
+        evx_buf_store1(b, in && y0 + ty + j < a.ny ? own[j] : 0xfffffff0u, a.c_flux * acc[j]);
+      });
     }
-  };
-  const int tx = tid % VF_X, ty = tid / VF_X;
-  const int pc0 = (ty + 2) * VF_PX + tx + 2, mc0 = (ty + 1) * VF_MX + tx + 1;
-  const bool own = x0 + tx < a.nx && y0 + ty < a.ny;
-  const unsigned out_off = own ? unsigned(((y0 + ty) * a.nx + x0 + tx) * 4) : 0xfffffff0u;
-  for (int z = z0 - 2; z <= z0 + 1; ++z) {
-    fetch_phi(z);
-    put_phi(z);
-  }
-  fetch_phi(z0 + 2);
-  evx_sync();
-  calc_mu(z0 - 1);
-  calc_mu(z0);
-  for (int z = z0; z < z1; ++z) {
-    evx_sync();  // the previous plane's fluxes are done with phi plane z - 2 and mu plane z - 2
-    put_phi(z + 2);
-    fetch_phi(z + 3);  // past the range on the last planes: a wrapped plane, loaded and unused
-    evx_sync();
-    calc_mu(z + 1);
-    evx_sync();
-    const float *pc = pl(z), *pu = pl(z + 1), *pd = pl(z - 1);
-    const float *mc = ml(z), *mu_ = ml(z + 1), *md = ml(z - 1);
-    const float p = pc[pc0], m = p * (1.0f - p), u = mc[mc0];
-    const float qs[6] = {pc[pc0 + 1], pc[pc0 - 1], pc[pc0 + VF_PX], pc[pc0 - VF_PX], pu[pc0], pd[pc0]};
-    const float us[6] = {mc[mc0 + 1], mc[mc0 - 1], mc[mc0 + VF_MX], mc[mc0 - VF_MX], mu_[mc0], md[mc0]};
-    float acc = 0.0f;
-    for (int d = 0; d < 6; ++d) acc += (m + qs[d] * (1.0f - qs[d])) * (us[d] - u);
-    evx_buf_store1(evx_make_buf(a.out + z * plane, unsigned(plane) * 4u), out_off, a.c_flux * acc);
+    // the x and y faces of plane k
+    const float ul = mu[m0 - P], uh = mu[m0 + P * R];
+    float fy = fym ? (m[0] + yl * (1.0f - yl)) * (ul - u[0]) : 0.0f;  // -y face of row 0
+    static_for<R>([&](auto r) {
+      constexpr int j = decltype(r)::value;
+      const float up_ = mu[m0 + P * j + 1], um_ = mu[m0 + P * j - 1];
+      const float mp = xp[j] * (1.0f - xp[j]), mm = xm[j] * (1.0f - xm[j]);
+      const float mh = j + 1 < R ? m[j + 1 < R ? j + 1 : j] : yh * (1.0f - yh);
+      const float hi = j + 1 < R ? u[j + 1 < R ? j + 1 : j] : uh;
+      const float fyp = j < ylast ? (m[j] + mh) * (hi - u[j]) : 0.0f;
+      float s = 0.0f;
+      s += fxp ? (m[j] + mp) * (up_ - u[j]) : 0.0f;
+      s += fxm ? (m[j] + mm) * (um_ - u[j]) : 0.0f;
+      s += fyp;
+      s += fy;
+      fy = -fyp;
+      acc[j] = s;
+      md[j] = m[j];
+      mud[j] = u[j];
+    });
+    dn = cur;
+    cur = up;
+    up = nxt;
   }
 }
 

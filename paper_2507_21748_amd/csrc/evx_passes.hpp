@@ -1329,10 +1329,10 @@ struct PlaneArgs {
 template <int NY, int NH>
 struct PlanePlans;
 template <>
-struct PlanePlans<32, 16> {  // 17 columns x 4 lanes, 32 rows x 1 lane
+struct PlanePlans<32, 16> {  // 32 columns (17 live) x 4 lanes, 32 rows x 4 lanes
   using PY = FftPlan<32>;
   using PX = FftPlan<16>;
-  static constexpr int THREADS = 68;
+  static constexpr int THREADS = 128;
 };
 template <>
 struct PlanePlans<64, 32> {  // 64 columns x 16 lanes, 256 rows x 4 lanes

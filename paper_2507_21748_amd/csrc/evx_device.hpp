@@ -30,7 +30,6 @@ inline void evx_sync() { evx_emu::block_barrier->arrive_and_wait(); }
 // A value the caller knows to be the same in every lane of a wave (kept in scalar registers).
 inline int evx_wave_uniform(int v) { return v; }
 inline float evx_rcp(float x) { return 1.0f / x; }
-inline float evx_rcp_fast(float x) { return 1.0f / x; }
 constexpr bool kEmulated = true;
 
 // Buffer resource: a byte range [base, base + nbytes); accesses at or past nbytes read zero and
@@ -83,11 +82,12 @@ inline void evx_buf_store1(evx_buf r, unsigned off, float v) {
 __device__ __forceinline__ void evx_sync() { __syncthreads(); }
 // A value the caller knows to be the same in every lane of a wave (kept in scalar registers).
 __device__ __forceinline__ int evx_wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float evx_rcp(float x) { return 1.0f / x; }
-// 1 / x for 1 <= x: the hardware estimate (1 ulp) with one Newton step, about half an ulp in five
-// instructions.  The clamp keeps an infinite x from making a NaN of the step.
-__device__ __forceinline__ float evx_rcp_fast(float x) {
-  const float d = __builtin_fminf(x, 1e38f);
+// 1 / x for x >= 1, correctly rounded: the hardware estimate (1 ulp) and one Newton step with fused
+// multiply-adds give the bits of an IEEE division for every mantissa (checked over all 2^23 at eight
+// exponents), in five instructions instead of ten.  The clamp (a NaN passes it) keeps the estimate
+// normal; past it the quotient is below 1.3e-38 either way.
+__device__ __forceinline__ float evx_rcp(float x) {
+  const float d = x > 8e37f ? 8e37f : x;
   const float r = __builtin_amdgcn_rcpf(d);
   return __builtin_fmaf(r, __builtin_fmaf(-d, r, 1.0f), r);
 }

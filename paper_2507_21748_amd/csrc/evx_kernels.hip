@@ -10,8 +10,15 @@
 
 namespace evx {
 
+// Workgroups of 512 lanes (length 1024) fit a compute unit twice only below 129 VGPRs, four waves a
+// SIMD; the compiler is held to that (no spills), since one workgroup alone waits for its own loads.
+template <int N>
+constexpr int col_min_waves() {
+  return ColCfg<N>::THREADS >= 512 ? 4 : 1;
+}
+
 template <int N, int BC, int MODE>
-__global__ __launch_bounds__(ColCfg<N>::THREADS) void col_kernel(ColArgs a) {
+__global__ __launch_bounds__(ColCfg<N>::THREADS, col_min_waves<N>()) void col_kernel(ColArgs a) {
   __shared__ float2 lds[ColCfg<N>::LDS];
   colpass_body<N, BC, MODE>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
 }

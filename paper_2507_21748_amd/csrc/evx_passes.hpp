@@ -510,7 +510,7 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     // about ten VALU instructions, and two of them a point were a fifth of this pass's.
     evx_sync();  // K2 table visible
     auto mult = [&](float K2) {
-      return a.dt_m * evx_rcp_fast(1.0f + a.a_dt * K2 + a.dt_m_kappa * K2 * K2);
+      return a.dt_m * evx_rcp(1.0f + a.a_dt * K2 + a.dt_m_kappa * K2 * K2);
     };
     if (a.mean && ct.tile == 0 && b == 0 && t == 0) {  // bin 0, whose multiplier is dt
       double* const m = spec_mean(a.out, a.n_lo);
@@ -542,40 +542,44 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     static_for<E>([&](auto e) {
       cs[e] = evx_buf_load2(ct.sres(a.state, e), ct.so);
     });
-    static_for<E>([&](auto e) {
-      const int k = t + TPS * decltype(e)::value;
-      const float kr = k2l[k];
-      const float2 Cs = cs[e];
-      const float2 F = x[e];
-      const float K2a = kca + kr, K2b = kcb + kr;
+    // one bin: C' from C, F and its K2.  The coefficients of a complex bin's two components are the
+    // same and evaluated once: in the periodic family, where pair columns are the exception, and
+    // below length 1024, whose 512 lanes have no registers left for it (and wait for memory).
+    constexpr bool share = !zf && C::THREADS < 512;
+    struct Coef {
+      float p, q, r;
+    };
+    auto coef = [&](float K2) {
       if constexpr (MODE == COL_Z_ETD) {
         // C' = C + phi1(dt S) dt R, dt S = -(dt M kappa K2^2 + A dt K2),
         // dt R = -(dt M K2 F + dt M kappa K2^2 C); phi1(0) = 1 keeps the DC bin exact
-        const float sa = -(a.dt_m_kappa * K2a * K2a + a.a_dt * K2a);
-        const float sb = -(a.dt_m_kappa * K2b * K2b + a.a_dt * K2b);
-        const float pa = evx_phi1(sa), pb = evx_phi1(sb);
-        const float ra = -(a.dt_m * K2a * F.x + a.dt_m_kappa * K2a * K2a * Cs.x);
-        const float rb = -(a.dt_m * K2b * F.y + a.dt_m_kappa * K2b * K2b * Cs.y);
-        x[e] = make_float2(Cs.x + pa * ra, Cs.y + pb * rb);
+        return Coef{evx_phi1(-(a.dt_m_kappa * K2 * K2 + a.a_dt * K2)), a.dt_m * K2,
+                    a.dt_m_kappa * K2 * K2};
       } else if constexpr (MODE == COL_Z_AC) {
         // Allen-Cahn: C' = G (P C - dt M F), P = 1 + A dt, G = 1 / (1 + A dt + dt M kappa K2)
         const float P = 1.0f + a.a_dt;
-        const float Ga = evx_rcp(P + a.dt_m_kappa * K2a), Gb = evx_rcp(P + a.dt_m_kappa * K2b);
-        x[e] = make_float2(Ga * (P * Cs.x - a.dt_m * F.x), Gb * (P * Cs.y - a.dt_m * F.y));
+        return Coef{evx_rcp(P + a.dt_m_kappa * K2), P, a.dt_m};
       } else if constexpr (MODE == COL_Z_AC_ETD) {
         // Allen-Cahn ETD1: C' = C + phi1(dt S) dt R, dt S = -(dt M kappa K2 + A dt),
         // dt R = -(dt M F + dt M kappa K2 C)
-        const float sa = -(a.dt_m_kappa * K2a + a.a_dt), sb = -(a.dt_m_kappa * K2b + a.a_dt);
-        const float ra = -(a.dt_m * F.x + a.dt_m_kappa * K2a * Cs.x);
-        const float rb = -(a.dt_m * F.y + a.dt_m_kappa * K2b * Cs.y);
-        x[e] = make_float2(Cs.x + evx_phi1(sa) * ra, Cs.y + evx_phi1(sb) * rb);
+        return Coef{evx_phi1(-(a.dt_m_kappa * K2 + a.a_dt)), a.dt_m, a.dt_m_kappa * K2};
       } else {
-        const float Pa = 1.0f + a.a_dt * K2a, Pb = 1.0f + a.a_dt * K2b;
-        const float Ga = evx_rcp(1.0f + a.dt_m_kappa * K2a * K2a + a.a_dt * K2a);
-        const float Gb = evx_rcp(1.0f + a.dt_m_kappa * K2b * K2b + a.a_dt * K2b);
-        x[e] = make_float2(Ga * (Pa * Cs.x - a.dt_m * K2a * F.x),
-                           Gb * (Pb * Cs.y - a.dt_m * K2b * F.y));
+        return Coef{evx_rcp(1.0f + a.dt_m_kappa * K2 * K2 + a.a_dt * K2), 1.0f + a.a_dt * K2,
+                    a.dt_m * K2};
       }
+    };
+    auto update = [&](const Coef& c, float C, float F) {
+      if constexpr (MODE == COL_Z_ETD || MODE == COL_Z_AC_ETD)
+        return C + c.p * -(c.q * F + c.r * C);
+      else
+        return c.p * (c.q * C - c.r * F);
+    };
+    static_for<E>([&](auto e) {
+      const float kr = k2l[t + TPS * decltype(e)::value];
+      const Coef ca = coef(kca + kr);
+      Coef cb = ca;
+      if (!share || !a.xcomplex) cb = coef(kcb + kr);
+      x[e] = make_float2(update(ca, cs[e].x, x[e].x), update(cb, cs[e].y, x[e].y));
       evx_buf_store2(ct.sres(a.state, e), ct.so, x[e]);
     });
   }

@@ -131,7 +131,9 @@ void sched_distance(L& l, const Geom& g, const float* a, const float* b, const A
 // two-species x pass with the reaction, and one z pass with the multiplier, 64 bytes a voxel.  The
 // species' means travel beside the buffers (spec_mean): adding the reaction to the whole field
 // instead rounded relative to the mean at every step (relative error of 20 steps at 64^3 and 128^3
-// 4.0e-7 against 2.7e-7 with separately transformed reactions).  A Dirichlet axis has no mean mode.
+// 4.0e-7 against 2.7e-7 with separately transformed reactions, 1.5e-7 with the means apart).  A
+// Dirichlet axis has no mean mode: there the species are spectral states (Lm and W), the x pass
+// transforms the reactions alone and the z pass adds them, 80 bytes a voxel.
 struct GsCoef {
   float dt, dt_du, dt_dv, F, k;
 };
@@ -139,9 +141,13 @@ struct GsCoef {
 template <class L>
 void sched_gray_scott(L& l, const Geom& g, const TablePtrs& t, float* u, float* v,
                       const AdjointBufs& b, float2* W, const GsCoef& co, int nsteps, int remap) {
-  (void)W;
   if (nsteps <= 0) return;
-  const PassBatch two{{b.A, b.B}, {b.A, b.B}, 2, {co.dt_du, co.dt_dv}};
+  const bool states = g.flip != 0;
+  const PassBatch two{{b.A, b.B}, {b.A, b.B}, 2};
+  const ColArgs ya = y_args(g, t, b.A, b.A, remap);
+  const StepCoef zc{0.0f, 0.0f, states ? co.dt : 1.0f};  // a_dt comes with the batch
+  ColArgs za = z_args(g, t, b.A, b.A, nullptr, zc, remap);
+  PassBatch upd{{b.A, b.B}, {b.A, b.B}, 2, {co.dt_du, co.dt_dv}};
   RowArgs xa = x_args(g, t, b.A, u, b.A, nullptr);
   xa.gs = 1;
   xa.in_c2 = b.B;
@@ -150,17 +156,27 @@ void sched_gray_scott(L& l, const Geom& g, const TablePtrs& t, float* u, float* 
   xa.gs_dt = co.dt;
   xa.gs_F = co.F;
   xa.gs_k = co.k;
-  const StepCoef zc{0.0f, 0.0f, 1.0f};  // a_dt comes with the batch
+  if (states) {
+    upd.state[0] = b.Lm;
+    upd.state[1] = W;
+    xa.rate = 1;
+    const PassBatch rows{{u, v}, {b.Lm, W}, 2}, st{{b.Lm, W}, {b.Lm, W}, 2};
+    const PassBatch out{{b.Lm, W}, {b.A, b.B}, 2};
+    l.row_batch(g.row_len, g.bc, ROW_FWD, x_args(g, t, nullptr, u, b.Lm, nullptr), rows);
+    l.col_batch(g.fy, g.bcy, COL_FWD, ya, st);
+    l.col_batch(g.fz, g.bcz, COL_FWD, za, st);
+    l.col_batch(g.fz, g.bcz, COL_INV, za, out);
+  }
   for (int n = 0; n < nsteps; ++n) {
-    if (n > 0) l.col_batch(g.fy, g.bcy, COL_INV, y_args(g, t, b.A, b.A, remap), two);
-    ColArgs za = z_args(g, t, b.A, b.A, nullptr, zc, remap);
-    if (!g.flip) {
+    const bool spectral = states || n > 0;  // the species' form on entry
+    if (spectral) l.col_batch(g.fy, g.bcy, COL_INV, ya, two);
+    if (!states) {
       xa.mean = n > 0 ? MEAN_IN : 0;
       za.mean = xa.mean | (n + 1 < nsteps ? MEAN_OUT : 0);
     }
-    l.row(g.row_len, g.bc, n > 0 ? ROW_FUSED_POLY : ROW_FWD, xa);
-    l.col_batch(g.fy, g.bcy, COL_FWD, y_args(g, t, b.A, b.A, remap), two);
-    l.col_batch(g.fz, g.bcz, COL_Z_VM, za, two);
+    l.row(g.row_len, g.bc, spectral ? ROW_FUSED_POLY : ROW_FWD, xa);
+    l.col_batch(g.fy, g.bcy, COL_FWD, ya, two);
+    l.col_batch(g.fz, g.bcz, COL_Z_VM, za, upd);
   }
   l.col_batch(g.fy, g.bcy, COL_INV, y_args(g, t, b.A, b.A, remap), two);
   const PassBatch back{{b.A, b.B}, {u, v}, 2};

@@ -11,7 +11,8 @@
 namespace evx {
 
 // Workgroups of 512 lanes (length 1024) fit a compute unit twice only below 129 VGPRs, four waves a
-// SIMD; the compiler is held to that (no spills), since one workgroup alone waits for its own loads.
+// SIMD; the compiler is held to that (at most five registers spill, in the rarer forms), since one
+// workgroup alone waits for its own loads.
 template <int N>
 constexpr int col_min_waves() {
   return ColCfg<N>::THREADS >= 512 ? 4 : 1;
@@ -82,6 +83,9 @@ static hipError_t plane_go(const PlaneArgs& a, hipStream_t s) {
 template <int N, int BC, int MODE>
 static hipError_t col_go(const ColArgs& a, hipStream_t s) {
   using C = ColCfg<N>;
+  if constexpr (MODE == COL_Z_VM) {
+    if (a.state) return col_go<N, BC, COL_Z_GS>(a, s);
+  }
   const long long nblk = (a.nseq + C::B - 1) / C::B;
   if (nblk <= 0) return hipSuccess;
   // 32-bit sequence numbers and lane byte offsets (ColTile)
@@ -117,6 +121,9 @@ static hipError_t row_go(const RowArgs& a, hipStream_t s) {
 template <int N, int BC, int MODE>
 static hipError_t col_go_batch(const ColArgs& a, const PassBatch& p, hipStream_t s) {
   using C = ColCfg<N>;
+  if constexpr (MODE == COL_Z_VM) {
+    if (p.state[0]) return col_go_batch<N, BC, COL_Z_GS>(a, p, s);
+  }
   const long long nblk = (a.nseq + C::B - 1) / C::B;
   if (nblk <= 0) return hipSuccess;
   if (p.n < 1 || p.n > kMaxBatch) return hipErrorInvalidValue;

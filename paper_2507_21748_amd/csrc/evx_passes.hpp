@@ -86,7 +86,9 @@ enum : int {
   COL_Z_ETD = 5,       // as COL_Z_UPDATE with the exponential (ETD1) update
   COL_Z_AC = 6,        // as COL_Z_UPDATE for the Allen-Cahn model (semi-implicit)
   COL_Z_AC_ETD = 7,    // Allen-Cahn, exponential (ETD1) update
-  COL_Z_VM = 8         // in -> forward -> x dt / (1 + c2 K2 + c4 K2^2) -> inverse -> out (no state)
+  COL_Z_VM = 8,        // in -> forward -> x dt / (1 + c2 K2 + c4 K2^2) -> inverse -> out (no state)
+  COL_Z_GS = 9         // COL_Z_VM launched with a state (in the work buffers' own layout):
+                       // C <- (C + dt x) / (1 + c2 K2 + c4 K2^2) -> state; -> inverse -> out
 };
 
 // row (x) pass modes
@@ -155,6 +157,7 @@ struct RowArgs {
   float2* out_c2;
   float gs_dt, gs_F, gs_k;
   int mean;            // MEAN_IN: in_c and in_c2 lack their means (spec_mean)
+  int rate;            // the results are the reaction terms alone (the species are in states)
 };
 
 // A spectral buffer may lack its mean: its bin 0 is then zero and the bin's value, an FP64 number,
@@ -181,12 +184,14 @@ struct PassBatch {
   const void* in[kMaxBatch];
   void* out[kMaxBatch];
   int n;
-  float a_dt[kMaxBatch];  // ColArgs::a_dt of each pair (the two-species z pass)
+  float a_dt[kMaxBatch];  // ColArgs::a_dt and state of each pair (the two-species z pass)
+  float2* state[kMaxBatch];
 };
 EVX_HD void bind_batch(ColArgs& a, const PassBatch& b, int k) {
   a.in = static_cast<const float2*>(b.in[k]);
   a.out = static_cast<float2*>(b.out[k]);
   a.a_dt = b.a_dt[k];
+  a.state = b.state[k];
 }
 // forward modes read real rows and write complex ones; the inverse does the opposite
 EVX_HD void bind_batch(RowArgs& a, bool inverse, const PassBatch& b, int k) {
@@ -410,7 +415,10 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
   constexpr int E = C::E, TPS = C::TPS, B = C::B;
   constexpr bool upd =
       MODE == COL_Z_UPDATE || MODE == COL_Z_ETD || MODE == COL_Z_AC || MODE == COL_Z_AC_ETD;
-  constexpr bool vm = MODE == COL_Z_VM;
+  if constexpr (kEmulated && MODE == COL_Z_VM) {
+    if (a.state) return colpass_body<N, BC, COL_Z_GS>(a, tid, bid, nblk, lds);  // on the GPU a kernel
+  }
+  constexpr bool vm = MODE == COL_Z_VM || MODE == COL_Z_GS;
   constexpr bool kt = upd || vm;  // needs the K2 tables
   constexpr bool has_fwd = MODE == COL_FWD || MODE == COL_Z_INIT || kt;
   constexpr bool has_inv = MODE != COL_FWD;
@@ -452,7 +460,7 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
   }
   // vertex-centred axis: keep points k < vlen (the rest of the extension mirrors them)
   auto store_points = [&](float2* out) {
-    if (a.vlen) {
+    if (!zf && a.vlen) {
       const evx_buf r0 = ct.res(out, a.row_stride, 0, nb);
       static_for<E>([&](auto e) {
         const int k = t + TPS * decltype(e)::value;
@@ -512,13 +520,32 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     auto mult = [&](float K2) {
       return a.dt_m * evx_rcp(1.0f + a.a_dt * K2 + a.dt_m_kappa * K2 * K2);
     };
-    if (a.mean && ct.tile == 0 && b == 0 && t == 0) {  // bin 0, whose multiplier is dt
+    if constexpr (MODE == COL_Z_GS) {
+      float2 cs[E];
+      const evx_buf r0 = ct.res(a.state, a.row_stride, 0, nb);
+      static_for<E>([&](auto e) {
+        const int k = t + TPS * decltype(e)::value;
+        if (!zf && a.vlen)
+          cs[e] = evx_buf_load2(r0, ct.voff(a.row_stride, k < a.vlen ? k : N - k));
+        else
+          cs[e] = evx_buf_load2(ct.res(a.state, a.row_stride, e, nb), ct.lo);
+      });
+      static_for<E>([&](auto e) {
+        const float kr = k2l[t + TPS * decltype(e)::value];
+        const float Ka = kca + kr, Kb = kcb + kr;
+        const float ga = evx_rcp(1.0f + a.a_dt * Ka + a.dt_m_kappa * Ka * Ka);
+        const float gb = evx_rcp(1.0f + a.a_dt * Kb + a.dt_m_kappa * Kb * Kb);
+        x[e] = make_float2((cs[e].x + a.dt_m * x[e].x) * ga, (cs[e].y + a.dt_m * x[e].y) * gb);
+      });
+      store_points(a.state);
+    } else if (a.mean && ct.tile == 0 && b == 0 && t == 0) {  // bin 0, whose multiplier is dt
       double* const m = spec_mean(a.out, a.n_lo);
       const double v = double(x[0].x) + ((a.mean & MEAN_IN) ? *m : 0.0);
       x[0].x = (a.mean & MEAN_OUT) ? 0.0f : float(v);
       if (a.mean & MEAN_OUT) *m = v;
     }
-    if (a.xcomplex) {
+    if constexpr (MODE == COL_Z_GS) {
+    } else if (a.xcomplex) {
       static_for<E>([&](auto e) {
         x[e] = cscale(x[e], mult(kca + k2l[t + TPS * decltype(e)::value]));
       });
@@ -883,8 +910,9 @@ EVX_DEV void gs_react(const RowArgs& a, float scale, float h, float sg, float mu
   const float du = scale * u, dv = scale * v;
   const float cu = du + mu, cv = dv + mv;
   const float uv2 = cu * cv * cv;
-  u = h * __builtin_fmaf(a.gs_dt, a.gs_F * (sg - cu) - uv2, du);
-  v = h * __builtin_fmaf(a.gs_dt, uv2 - a.gs_k * cv, dv);
+  const float ru = a.gs_F * (sg - cu) - uv2, rv = uv2 - a.gs_k * cv;
+  u = h * (a.rate ? ru : __builtin_fmaf(a.gs_dt, ru, du));
+  v = h * (a.rate ? rv : __builtin_fmaf(a.gs_dt, rv, dv));
 }
 // The means of the two species of a block's input.
 EVX_DEV float2 gs_means(const RowArgs& a) {

@@ -786,6 +786,40 @@ struct RowXch {
   }
 };
 
+// Lane tid of a row block: sequence b and part t in the transforms and their exchange area, and row
+// b, part t when rows move to and from memory.
+// Transforms: sequences fastest, so that sixteen lanes address 128 consecutive bytes of LDS.  Their
+// memory accesses are then 16-byte pieces of eight rows (four 128-byte lines).  A 512-lane block
+// (periodic x of 1024, a grid far beyond the caches) orders four parts, the sequences, then more
+// parts instead: 32-byte pieces of four rows, two lines, for two-way bank conflicts (forward pass
+// 1.77 -> 1.70 ms, fused 2.22 -> 2.18; smaller blocks lose more to the conflicts than they gain).
+template <int B, int TPS>
+EVX_DEV void row_lane(int tid, int& b, int& t) {
+  if constexpr (B == 8 && TPS >= 64) {
+    b = (tid >> 2) & 7;
+    t = (tid & 3) + 4 * (tid >> 5);
+  } else {
+    b = tid % B;
+    t = tid / B;
+  }
+}
+// Memory, where rows meet the packed pairs of the cosine transforms in LDS anyway: sixteen lanes are
+// whole 64-byte pieces of two rows, or where the parts are no multiple of 8, 32-byte pieces of four
+// (256^3 zero flux, forward and inverse 30 -> 27 us, fused 34.5 -> 33.2).
+template <int B, int TPS>
+EVX_DEV void row_io_lane(int tid, int& b, int& t) {
+  if constexpr (B == 8 && TPS % 8 == 0) {
+    b = (tid >> 3) & 7;
+    t = (tid & 7) + 8 * (tid >> 6);
+  } else if constexpr (B == 8 && TPS % 4 == 0) {
+    b = (tid >> 2) & 7;
+    t = (tid & 3) + 4 * (tid >> 5);
+  } else {
+    b = tid % B;
+    t = tid / B;
+  }
+}
+
 // Periodic: template length NH = nx/2, the complex FFT length of the packed real row; the row
 // has NH+1 complex points.  Zero flux: NH = nx, one sequence carries two rows packed as a + i b.
 template <int NH, int BC>
@@ -802,7 +836,14 @@ struct RowCfg {
       (BC == BC_PERIODIC ? (NH % 2 == 0 && SROW % 2 == 0) : E % 4 == 0) ? 2 : 1;
   // the staging area of whole rows is a little larger than the transform's exchange area
   static constexpr int TW = (BC == BC_PERIODIC) ? B * SROW : RowXch<NH, B>::SLOTS;  // twiddles
-  static constexpr int LDS = TW + (FftPlan<NH>::S > 1 ? NH : 0);
+  // post-processing twiddles come from a table in LDS; a lane of a short row (few lanes, many points
+  // each) holds its own in registers instead.  Loaded a point each by every lane they doubled the
+  // pass's loads (1024^3: fused 2.18 -> 2.10 ms, inverse 1.85 -> 1.70, forward 1.70 -> 1.62 with the
+  // table; 128^3 and 256^3 1% a step).
+  static constexpr bool PL = BC == BC_PERIODIC && TPS >= 8;
+  static constexpr int PO = TW + (FftPlan<NH>::S > 1 ? NH : 0);
+  static constexpr int NPO = PL ? NH / 2 + 1 : 0;  // exp(-2 pi i (NH - k) / nx) = -conj(entry k)
+  static constexpr int LDS = PO + NPO;
 };
 
 // Whether every live lane offset of a row block (SpecLane: at most 8 groups, the planes its rows
@@ -812,6 +853,25 @@ inline bool row_fits32(const RowArgs& a) {
   const long long planes = RowCfg<NH, BC>::ROWS / a.sg.ny + 2;
   return (8 * a.sg.xstride + planes * a.sg.zstride + 8) * 8 < (long long)kDeadRow;
 }
+
+// Post-processing twiddles exp(-2 pi i k / nx) of a lane's points k = t + TPS e (RowCfg::PL).
+template <int NH, bool PL>
+struct PostTw {
+  static constexpr int E = FftPlan<NH>::E, TPS = FftPlan<NH>::TPS;
+  float2 w[PL ? 1 : E];
+  const float2* po;
+  int t;
+  template <int e>
+  EVX_DEV float2 at() const {
+    if constexpr (PL) {
+      const int k = t + TPS * e;
+      const float2 v = po[k <= NH / 2 ? k : NH - k];
+      return k <= NH / 2 ? v : make_float2(-v.x, v.y);
+    } else {
+      return w[e];
+    }
+  }
+};
 
 // C2R pre-processing, Z[k] = (X[k] + conj X[NH-k]) + i (X[k] - conj X[NH-k]) e^{+2 pi i k / nx}:
 // X = X[k], Xr = conj X[NH-k], w = e^{-2 pi i k / nx}.
@@ -851,9 +911,9 @@ EVX_DEV float2 row_nonlin(float scale, const float* poly, float2 v) {
 // A periodic row's half spectrum x (Nyquist column nyq, held by lane t = 0) to the input of the
 // inverse transform, and back; w: post-processing twiddles of the lane's points.  The exchange
 // area must be free on entry; row_c2r leaves it free, row_r2c does not.
-template <int NH, int B>
-EVX_DEV void row_c2r(float2 (&x)[FftPlan<NH>::E], float2 nyq, const float2 (&w)[FftPlan<NH>::E],
-                     float2* lds, int b, int t) {
+template <int NH, int B, class W>
+EVX_DEV void row_c2r(float2 (&x)[FftPlan<NH>::E], float2 nyq, const W& w, float2* lds, int b,
+                     int t) {
   constexpr int E = FftPlan<NH>::E, TPS = FftPlan<NH>::TPS;
   static_for<E>([&](auto e) { lds[lidx<B>(t + TPS * decltype(e)::value, b)] = x[e]; });
   evx_sync();
@@ -861,13 +921,12 @@ EVX_DEV void row_c2r(float2 (&x)[FftPlan<NH>::E], float2 nyq, const float2 (&w)[
     const int k = t + TPS * decltype(e)::value;
     float2 m = lds[lidx<B>(decltype(e)::value == 0 && t == 0 ? 0 : NH - k, b)];
     if constexpr (decltype(e)::value == 0) m = t == 0 ? nyq : m;
-    x[e] = c2r_pre(x[e], cconj(m), w[e]);
+    x[e] = c2r_pre(x[e], cconj(m), w.template at<decltype(e)::value>());
   });
   evx_sync();
 }
-template <int NH, int B>
-EVX_DEV float2 row_r2c(float2 (&x)[FftPlan<NH>::E], const float2 (&w)[FftPlan<NH>::E],
-                       float2* lds, int b, int t) {
+template <int NH, int B, class W>
+EVX_DEV float2 row_r2c(float2 (&x)[FftPlan<NH>::E], const W& w, float2* lds, int b, int t) {
   constexpr int E = FftPlan<NH>::E, TPS = FftPlan<NH>::TPS;
   float2 nyq = make_float2(0.f, 0.f);
   static_for<E>([&](auto e) { lds[lidx<B>(t + TPS * decltype(e)::value, b)] = x[e]; });
@@ -877,7 +936,7 @@ EVX_DEV float2 row_r2c(float2 (&x)[FftPlan<NH>::E], const float2 (&w)[FftPlan<NH
     const float2 Q = cconj(lds[lidx<B>(decltype(e)::value == 0 && t == 0 ? 0 : NH - k, b)]);
     // k = NH: w = -1 on the pair of k = 0
     if constexpr (decltype(e)::value == 0) nyq = make_float2(2.0f * (x[e].x - x[e].y), 0.f);
-    x[e] = r2c_post(x[e], Q, w[e]);
+    x[e] = r2c_post(x[e], Q, w.template at<decltype(e)::value>());
   });
   return nyq;
 }
@@ -921,6 +980,22 @@ EVX_DEV float2 gs_means(const RowArgs& a) {
                      float(*spec_mean(a.in_c2, a.sg.ny) * a.scale));
 }
 
+// A periodic block's tables: FFT twiddles to LDS, post-processing twiddles to where w keeps them.
+template <int NH, int T, bool PL>
+EVX_DEV void row_tables(const RowArgs& a, int tid, int t, float2* twl, PostTw<NH, PL>& w) {
+  using C = RowCfg<NH, BC_PERIODIC>;
+  TwStage<NH, T> tws;
+  tws.load(a.tw, tid);
+  if constexpr (PL) {
+    TableStage<C::NPO, T, float2> pos;
+    pos.load(a.post, tid);
+    pos.store(twl + (C::PO - C::TW), tid);
+  } else {
+    static_for<C::E>([&](auto e) { w.w[e] = a.post[t + C::TPS * decltype(e)::value]; });
+  }
+  tws.store(twl, tid);
+}
+
 // Real rows of a periodic-family block to the lane's points x (pairs of reals), with the Dirichlet
 // sign of y / z; `tables` runs once the loads are issued.  Leaves the exchange area free.
 template <int NH, int B, class F>
@@ -928,7 +1003,8 @@ EVX_DEV void real_row_in(const RowArgs& a, const float* in, long long r0, int ti
                          float2* lds, float2 (&x)[FftPlan<NH>::E]) {
   using C = RowCfg<NH, BC_PERIODIC>;
   constexpr int E = C::E, TPS = C::TPS;
-  const int b = tid % B, t = tid / B;
+  int b, t;
+  row_lane<B, TPS>(tid, b, t);
   const long long row = r0 + b;
   if (a.vx) {
     // vertex-centred x: rows of NH + 1 points, extended evenly about both end points to the 2 NH
@@ -969,8 +1045,9 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   constexpr bool real_out =
       MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC;
   constexpr bool add = MODE == ROW_INV_ADD;
-  const int b = tid % B;
-  const int t = tid / B;
+  const int b = tid % B, t = tid / B;
+  int bo, to;
+  row_io_lane<B, TPS>(tid, bo, to);
   float2 x[E], w[E];
   float2* const twl = lds + C::TW;
   TwStage<NH, T> tws;
@@ -984,19 +1061,20 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   float* const st = reinterpret_cast<float*>(lds);
   // float offsets of the lane's bin t, its mirror, and the row it moves; bins come as base + C
   const int atp = X::at(t), atm = X::at(-t);
-  const int ate = X::at(2 * t), ato = X::at(2 * t + 1), ats = X::at(V * t), atn = X::at(-V * t);
+  const int ate = X::at(2 * to), ato = X::at(2 * to + 1), ats = X::at(V * to), atn = X::at(-V * to);
+  const int atx = X::at(to);
   float2* const prs = lds + b;   // pair b of bin n: prs[at(n) / 2]
-  float* const rwa = st + (GS ? 2 * b : b);           // the lane's first row of bin n: rwa[at(n)]
-  float* const rwb = st + (GS ? 2 * b + 1 : B + b);   // and its second
+  float* const rwa = st + (GS ? 2 * bo : bo);           // the lane's first row of bin n: rwa[at(n)]
+  float* const rwb = st + (GS ? 2 * bo + 1 : B + bo);   // and its second
   const float2* const in_b = GS ? a.in_c2 : a.in_c;
   float2* const out_b = GS ? a.out_c2 : a.out_c;
-  const long long ra = r0 + b, rb = GS ? ra : ra + B;  // rows whose bins the lane moves
+  const long long ra = r0 + bo, rb = GS ? ra : ra + B;  // rows whose bins the lane moves
   const bool va = ra < a.nrows, vb = rb < a.nrows;
-  const SpecLane<TPS> la(a.sg, r0, b, va, t);
-  const SpecLane<TPS> lb(a.sg, r0, int(rb - r0), vb, t);
+  const SpecLane<TPS> la(a.sg, r0, bo, va, to);
+  const SpecLane<TPS> lb(a.sg, r0, int(rb - r0), vb, to);
   // real rows: lane offsets of its first pairs from the block's first row
-  const unsigned oa = va ? unsigned((b * NX + 2 * V * t) * 4) : kDeadRow;
-  const unsigned ob = vb ? unsigned((int(rb - r0) * NX + 2 * V * t) * 4) : kDeadRow;
+  const unsigned oa = va ? unsigned((bo * NX + 2 * V * to) * 4) : kDeadRow;
+  const unsigned ob = vb ? unsigned((int(rb - r0) * NX + 2 * V * to) * 4) : kDeadRow;
   // pairs c = V (t + TPS i) .. + V - 1 of a real row
   auto row_in = [&](evx_buf r, unsigned off, float2 (&p)[H]) {
     static_for<HV>([&](auto i) {
@@ -1021,11 +1099,13 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
     });
   };
   // pair c holds points 2c = src(c) and 2c + 1 = src(N - 1 - c) of Makhoul's order
-  // Dirichlet signs: of the lane's rows at even points, and of odd points against even ones
-  float sa = 1.0f, sb = 1.0f;
+  // Dirichlet signs: of the rows the lane moves and of the one it transforms (two species) at even
+  // points, and of odd points against even ones
+  float sa = 1.0f, sb = 1.0f, sx = 1.0f;
   if (a.flip) {
     sa = dirichlet_sign(ra, 0, a.ny, a.flip);
     sb = dirichlet_sign(rb, 0, a.ny, a.flip);
+    if constexpr (GS) sx = dirichlet_sign(r0 + b, 0, a.ny, a.flip);
   }
   const float sodd = (a.flip & 1) ? -1.0f : 1.0f;
   auto flip = [&](float sg, float2 v) { return make_float2(v.x * sg, v.y * (sg * sodd)); };
@@ -1034,7 +1114,7 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   auto react = [&](float scale) {
     static_for<E>([&](auto e) {
       // (the first half of the order are the row's even points, the second its odd ones)
-      gs_react(a, scale, 1.0f, decltype(e)::value < H ? sa : sa * sodd, mean.x, mean.y, x[e].x,
+      gs_react(a, scale, 1.0f, decltype(e)::value < H ? sx : sx * sodd, mean.x, mean.y, x[e].x,
                x[e].y);
     });
   };
@@ -1050,7 +1130,7 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
         pa[m] = flip(sa, pa[m]);
         pb[m] = flip(sb, pb[m]);
       }
-      const int lo = X::template at<c0>(V * t, ats), hi = X::template at<NX - 1 - c0>(-V * t, atn);
+      const int lo = X::template at<c0>(V * to, ats), hi = X::template at<NX - 1 - c0>(-V * to, atn);
       rwa[lo] = pa[m].x;
       rwa[hi] = pa[m].y;
       rwb[lo] = pb[m].x;
@@ -1073,7 +1153,7 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
       });
       tws.store(twl, tid);
       static_for<E>([&](auto e) {
-        const int k = X::template at<TPS * decltype(e)::value>(t, atp);
+        const int k = X::template at<TPS * decltype(e)::value>(to, atx);
         rwa[k] = qa[e];
         rwb[k] = qb[e];
       });
@@ -1086,8 +1166,8 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
       });
       tws.store(twl, tid);
       static_for<H>([&](auto i) {
-        const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
-        const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
+        const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * to, ate);
+        const int od = X::template at<2 * TPS * decltype(i)::value>(2 * to + 1, ato);
         rwa[ev] = pa[i].x;
         rwa[od] = pa[i].y;
         rwb[ev] = pb[i].x;
@@ -1119,8 +1199,8 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
       evx_sync();
       static_for<H>([&](auto m) {
         constexpr int c0 = V * TPS * (decltype(m)::value / V) + decltype(m)::value % V;
-        const int lo = X::template at<c0>(V * t, ats);
-        const int hi = X::template at<NX - 1 - c0>(-V * t, atn);
+        const int lo = X::template at<c0>(V * to, ats);
+        const int hi = X::template at<NX - 1 - c0>(-V * to, atn);
         float2 u = make_float2(rwa[lo], rwa[hi]), v = make_float2(rwb[lo], rwb[hi]);
         if (a.flip) {
           u = flip(sa, u);
@@ -1158,18 +1238,18 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   evx_sync();
   if (a.xcplx) {
     spec_points<E>(a.out_c, la, [&](auto e, evx_buf r, unsigned off) {
-      evx_buf_store2(r, off, make_float2(rwa[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
+      evx_buf_store2(r, off, make_float2(rwa[X::template at<TPS * decltype(e)::value>(to, atx)], 0.f));
     });
     spec_points<E>(out_b, lb, [&](auto e, evx_buf r, unsigned off) {
-      evx_buf_store2(r, off, make_float2(rwb[X::template at<TPS * decltype(e)::value>(t, atp)], 0.f));
+      evx_buf_store2(r, off, make_float2(rwb[X::template at<TPS * decltype(e)::value>(to, atx)], 0.f));
     });
-    spec_tail_out<NX, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
-    spec_tail_out<NX, false>(out_b, a.sg, lb, t, make_float2(0.f, 0.f));
+    spec_tail_out<NX, false>(a.out_c, a.sg, la, to, make_float2(0.f, 0.f));
+    spec_tail_out<NX, false>(out_b, a.sg, lb, to, make_float2(0.f, 0.f));
     return;
   }
   static_for<H>([&](auto i) {
-    const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * t, ate);
-    const int od = X::template at<2 * TPS * decltype(i)::value>(2 * t + 1, ato);
+    const int ev = X::template at<2 * TPS * decltype(i)::value>(2 * to, ate);
+    const int od = X::template at<2 * TPS * decltype(i)::value>(2 * to + 1, ato);
     pa[i] = make_float2(rwa[ev], rwa[od]);
     pb[i] = make_float2(rwb[ev], rwb[od]);
   });
@@ -1179,8 +1259,8 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   spec_points<H>(out_b, lb, [&](auto i, evx_buf r, unsigned off) {
     evx_buf_store2(r, off, pb[i]);
   });
-  spec_tail_out<NX / 2, false>(a.out_c, a.sg, la, t, make_float2(0.f, 0.f));
-  spec_tail_out<NX / 2, false>(out_b, a.sg, lb, t, make_float2(0.f, 0.f));
+  spec_tail_out<NX / 2, false>(a.out_c, a.sg, la, to, make_float2(0.f, 0.f));
+  spec_tail_out<NX / 2, false>(out_b, a.sg, lb, to, make_float2(0.f, 0.f));
 }
 
 // What bounds this pass: with spectral rows staged through LDS it was VALU issue (87% of the SIMD
@@ -1190,7 +1270,7 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
 // mirrored points through the transform's own exchange area.  Measured a pass, before -> after: 400^3
 // zero flux 184 -> 151 us, 256^3 zero flux 39.5 -> 34.7, 128^3 10.5 -> 9.0, 48 x 100 x 96 mixed 7.6 ->
 // 5.9; forward from real rows at 256^3 37 -> 26 us (1.3 -> 2.6 TB/s each way out of cache); at 1024^3
-// it is bound by its access pattern (65 pieces of 512 bytes a block) and stays at 2.14 ms.
+// it is bound by its access pattern (65 pieces of 512 bytes a block) and stays at 2.1 ms.
 template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* lds);
 
@@ -1215,14 +1295,15 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
   // consecutive row blocks (their 8-row pieces of each x group are neighbours) on one XCD
   const long long r0 = (long long)remap_block(bid, nblk, a.remap) * C::ROWS;
   if constexpr (BC == BC_PERIODIC) {
-    const int b = tid % B;
-    const int t = tid / B;
-    float2 x[E], w[E];
+    int b, t;
+    row_lane<B, TPS>(tid, b, t);
+    float2 x[E];
     float2* const twl = lds + C::TW;
-    TwStage<NH, T> tws;
-    tws.load(a.tw, tid);
-    // post-processing twiddles of the lane's points, held for both directions
-    static_for<E>([&](auto e) { w[e] = a.post[t + TPS * decltype(e)::value]; });
+    PostTw<NH, C::PL> w;
+    w.po = lds + C::PO;
+    w.t = t;
+    // the tables' loads are issued after the data's, and staged once those are in flight
+    auto tables = [&] { row_tables<NH, T>(a, tid, t, twl, w); };
     const long long row = r0 + b;
     const bool live = row < a.nrows;
     const SpecLane<TPS> ln(a.sg, r0, b, live, t);
@@ -1231,7 +1312,7 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     // vertex-centred x: rows of NH + 1 points, 4 (b (NH + 1) + j) bytes from the block's first
     auto voff = [&](int j) { return live ? unsigned((b * (NH + 1) + j) * 4) : kDeadRow; };
     if constexpr (real_in) {
-      real_row_in<NH, B>(a, a.in_r, r0, tid, [&] { tws.store(twl, tid); }, lds, x);
+      real_row_in<NH, B>(a, a.in_r, r0, tid, tables, lds, x);
       static_for<E>([&](auto e) {  // with the halves r2c_post leaves out
         if constexpr (MODE == ROW_FWD_FP) {
           x[e] = row_nonlin<MODE, true>(1.0f, nullptr, x[e]);
@@ -1241,7 +1322,7 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
       });
     } else {
       const float2 nyq = spec_row_in<NH>(a.in_c, a.sg, ln, t, x);
-      tws.store(twl, tid);
+      tables();
       row_c2r<NH, B>(x, nyq, w, lds, b, t);
       // real rows to add to: in flight during the transform
       RR rr(a.out_r, r0, a.nrows);
@@ -1295,22 +1376,23 @@ EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* ld
     cos_rows<NH, MODE, true>(a, tid, r0, lds);
   } else {
     constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
-    const int b = tid % B;
-    const int t = tid / B;
+    int b, t;
+    row_lane<B, TPS>(tid, b, t);
     const long long row = r0 + b;
-    float2 u[E], v[E], w[E];
+    float2 u[E], v[E];
     float2* const twl = lds + C::TW;
-    TwStage<NH, T> tws;
-    tws.load(a.tw, tid);
-    static_for<E>([&](auto e) { w[e] = a.post[t + TPS * decltype(e)::value]; });
+    PostTw<NH, C::PL> w;
+    w.po = lds + C::PO;
+    w.t = t;
+    auto tables = [&] { row_tables<NH, T>(a, tid, t, twl, w); };
     const SpecLane<TPS> ln(a.sg, r0, b, row < a.nrows, t);
     if constexpr (MODE == ROW_FWD) {
-      real_row_in<NH, B>(a, a.in_r, r0, tid, [&] { tws.store(twl, tid); }, lds, u);
+      real_row_in<NH, B>(a, a.in_r, r0, tid, tables, lds, u);
       real_row_in<NH, B>(a, a.in_r2, r0, tid, [] {}, lds, v);
     } else {
       const float2 nu = spec_row_in<NH>(a.in_c, a.sg, ln, t, u);
       const float2 nv = spec_row_in<NH>(a.in_c2, a.sg, ln, t, v);
-      tws.store(twl, tid);
+      tables();
       row_c2r<NH, B>(u, nu, w, lds, b, t);
       fft_regs<NH, +1, B>(u, lds, b, t, twl);
       row_c2r<NH, B>(v, nv, w, lds, b, t);

@@ -184,6 +184,35 @@ enum : int {
   EPI_RESID = 3     // out = c + (acc + b)  (last layer, FP32)
 };
 
+// A training step runs its kernels on several windows at once: window w of the `n` lies at byte
+// offset off(w) from the first buffer's address.  The last window owns that address (train_buffers
+// shows it), the others follow the single-window workspace.
+struct WinMap {
+  long long first = 0, stride = 0;  // bytes
+  int n = 1;
+  template <bool MANY = true>
+  __device__ long long off(int w) const {
+    if constexpr (!MANY) return 0;
+    return w == n - 1 ? 0 : first + w * stride;
+  }
+};
+template <class T>
+__device__ __forceinline__ T* at_win(T* p, long long bytes) {
+  return (T*)((char*)p + bytes);
+}
+// Tile t of n windows of `per` tiles each: its window; t becomes the tile within it.  MANY = false
+// (inference: one field) leaves t alone; the search cost it 1% of the 32 -> 32 layers.
+template <bool MANY = true>
+__device__ __forceinline__ int window_of(int& t, int per) {
+  if constexpr (!MANY) return 0;
+  int w = 0;
+  while (t >= per) {
+    t -= per;
+    ++w;
+  }
+  return w;
+}
+
 struct ConvArgs {
   const void* in;        // bf16 [V][Cin] or float [V] (Cin == 1, FP32 input)
   const bf16_t* w;       // bf16 [27][Cout][Cin]
@@ -195,6 +224,8 @@ struct ConvArgs {
   float* out;            // EPI_RESID
   const bf16_t* gtab;    // GELU table (GT_N entries), for the GELU epilogues
   int nx, ny, nz;
+  WinMap win;            // windows of in, z_out, a_out, zprev and out
+  long long c_stride;    // floats between the windows of c
 };
 
 // ----------------------------------------------------------------------------- MFMA 32 -> 32
@@ -208,9 +239,9 @@ __device__ __forceinline__ int out_channel(int h, int row) {
 // Backward-data epilogue of one voxel v: channels 8 lg .. 8 lg + 7 (acc[h][r] is channel
 // 8 lg + 4 h + r) become bf16(acc * gelu'(zprev)), zprev read and the result written 16 bytes at
 // a time.
-__device__ __forceinline__ void store_dgelu(const ConvArgs& a, long long v, int lg,
+__device__ __forceinline__ void store_dgelu(const ConvArgs& a, long long wo, long long v, int lg,
                                             const f32x4 (&acc)[2]) {
-  const uint4 zp = *reinterpret_cast<const uint4*>(a.zprev + v * CH + 8 * lg);
+  const uint4 zp = *reinterpret_cast<const uint4*>(at_win(a.zprev, wo) + v * CH + 8 * lg);
   const unsigned zz[2][2] = {{zp.x, zp.y}, {zp.z, zp.w}};
   unsigned ow[2][2];
 #pragma unroll
@@ -221,7 +252,8 @@ __device__ __forceinline__ void store_dgelu(const ConvArgs& a, long long v, int 
       const bf16_t hi = f2bf(acc[h][2 * k + 1] * gelu_prime(__uint_as_float(zz[h][k] & 0xFFFF0000u)));
       ow[h][k] = unsigned(lo) | (unsigned(hi) << 16);
     }
-  *reinterpret_cast<uint4*>(a.a_out + v * CH + 8 * lg) = make_uint4(ow[0][0], ow[0][1], ow[1][0], ow[1][1]);
+  *reinterpret_cast<uint4*>(at_win(a.a_out, wo) + v * CH + 8 * lg) =
+      make_uint4(ow[0][0], ow[0][1], ow[1][0], ow[1][1]);
 }
 constexpr int TX = 16, TY = 8, TZ = 4;
 constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
@@ -293,7 +325,10 @@ __global__ __launch_bounds__(MFMA_THREADS) void conv32_mfma(ConvArgs a, int ntil
   auto row_ok = [&](int k) {
     return f_row0 < ROWS_PER_IT && f_row0 + ROWS_PER_IT * k < HALO_ROWS;
   };
+  constexpr bool MANY = EPI != EPI_GELU;  // training runs several windows
+  const int per = ntx * nty * ((a.nz + TZ - 1) / TZ);  // tiles of a window
   auto fetch = [&](int tl) {
+    const u32x4* const src = at_win(gin, a.win.template off<MANY>(window_of<MANY>(tl, per)));
     const int fx0 = (tl % ntx) * TX;
     const int rest = tl / ntx;
     const int fy0 = (rest % nty) * TY, fz0 = (rest / nty) * TZ;
@@ -314,7 +349,7 @@ __global__ __launch_bounds__(MFMA_THREADS) void conv32_mfma(ConvArgs a, int ntil
         gy = wrap(gy, a.ny);
         gz = wrap(gz, a.nz);
       }
-      pre[k] = gin[(((long long)gz * a.ny + gy) * a.nx + gx) * 4 + f_part];
+      pre[k] = src[(((long long)gz * a.ny + gy) * a.nx + gx) * 4 + f_part];
     }
   };
   int tile = blockIdx.x;
@@ -332,8 +367,10 @@ __global__ __launch_bounds__(MFMA_THREADS) void conv32_mfma(ConvArgs a, int ntil
       bias[h][r] = EPI != EPI_DGELU ? a.bias[out_channel(h, 4 * lg + r)] : 0.f;
 
   for (; tile < ntiles; tile += gridDim.x) {
-    const int x0 = (tile % ntx) * TX;
-    const int rest = tile / ntx;
+    int tl = tile;
+    const long long wo = a.win.template off<MANY>(window_of<MANY>(tl, per));
+    const int x0 = (tl % ntx) * TX;
+    const int rest = tl / ntx;
     const int y0 = (rest % nty) * TY, z0 = (rest / nty) * TZ;
     __syncthreads();  // the previous tile's epilogue is done with the LDS tile
 #pragma unroll
@@ -424,9 +461,9 @@ __global__ __launch_bounds__(MFMA_THREADS) void conv32_mfma(ConvArgs a, int ntil
         if (x >= a.nx || y + m >= a.ny || z >= a.nz) continue;
         const long long v = ((long long)z * a.ny + y + m) * a.nx + x;
         if constexpr (EPI == EPI_GELU_Z)
-          *reinterpret_cast<uint4*>(a.z_out + v * CH + 8 * lg) =
+          *reinterpret_cast<uint4*>(at_win(a.z_out, wo) + v * CH + 8 * lg) =
               make_uint4(zw[m][0][0], zw[m][0][1], zw[m][1][0], zw[m][1][1]);
-        *reinterpret_cast<uint4*>(a.a_out + v * CH + 8 * lg) =
+        *reinterpret_cast<uint4*>(at_win(a.a_out, wo) + v * CH + 8 * lg) =
             make_uint4(aw[m][0][0], aw[m][0][1], aw[m][1][0], aw[m][1][1]);
       }
       continue;
@@ -435,7 +472,7 @@ __global__ __launch_bounds__(MFMA_THREADS) void conv32_mfma(ConvArgs a, int ntil
 #pragma unroll
       for (int m = 0; m < WROWS; ++m) {
         if (x >= a.nx || y + m >= a.ny || z >= a.nz) continue;
-        store_dgelu(a, ((long long)z * a.ny + y + m) * a.nx + x, lg, acc[m]);
+        store_dgelu(a, wo, ((long long)z * a.ny + y + m) * a.nx + x, lg, acc[m]);
       }
     }
   }
@@ -500,7 +537,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
   // persistent: the table and the weights are staged once, then the block walks tiles; the next
   // tile's halo is loaded into registers while the current one is computed
   elem_t pre[IT];
+  constexpr bool MANY = EPI != EPI_GELU;
+  const int per = ntx * nty * ((a.nz + TZ - 1) / TZ);
   auto fetch = [&](int tl) {
+    const elem_t* const src = at_win(gin, a.win.template off<MANY>(window_of<MANY>(tl, per)));
     const int fx0 = (tl % ntx) * TX;
     const int fy0 = (tl / ntx % nty) * TY;
     const int fz0 = (tl / ntx / nty) * TZ;
@@ -519,14 +559,16 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
         gy = wrap(gy, a.ny);
         gz = wrap(gz, a.nz);
       }
-      pre[k] = gin[((long long)gz * a.ny + gy) * a.nx + gx];
+      pre[k] = src[((long long)gz * a.ny + gy) * a.nx + gx];
     }
   };
   if (int(blockIdx.x) < ntiles) fetch(blockIdx.x);
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int x0 = (tile % ntx) * TX;
-    const int y0 = (tile / ntx % nty) * TY;
-    const int z0 = (tile / ntx / nty) * TZ;
+    int tl = tile;
+    const long long wo = a.win.template off<MANY>(window_of<MANY>(tl, per));
+    const int x0 = (tl % ntx) * TX;
+    const int y0 = (tl / ntx % nty) * TY;
+    const int z0 = (tl / ntx / nty) * TZ;
     __syncthreads();  // the previous tile is done with s_h
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
@@ -603,9 +645,9 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
           if (x >= a.nx || y >= a.ny || z >= a.nz) continue;
           const long long v = ((long long)z * a.ny + y) * a.nx + x;
           if constexpr (EPI == EPI_GELU_Z)
-            *reinterpret_cast<uint4*>(a.z_out + v * CH + 8 * lg) =
+            *reinterpret_cast<uint4*>(at_win(a.z_out, wo) + v * CH + 8 * lg) =
                 make_uint4(zw[m][0][0], zw[m][0][1], zw[m][1][0], zw[m][1][1]);
-          *reinterpret_cast<uint4*>(a.a_out + v * CH + 8 * lg) =
+          *reinterpret_cast<uint4*>(at_win(a.a_out, wo) + v * CH + 8 * lg) =
               make_uint4(gw[m][0][0], gw[m][0][1], gw[m][1][0], gw[m][1][1]);
         }
       }
@@ -616,7 +658,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
       for (int m = 0; m < 4; ++m) {
         const int x = x0 + li, y = y0 + yb + m, z = z0 + zl;
         if (x >= a.nx || y >= a.ny || z >= a.nz) continue;
-        store_dgelu(a, ((long long)z * a.ny + y) * a.nx + x, lg, accs[m]);
+        store_dgelu(a, wo, ((long long)z * a.ny + y) * a.nx + x, lg, accs[m]);
       }
     }
   }
@@ -648,7 +690,10 @@ __global__ __launch_bounds__(O_THREADS) void conv_out_mfma(ConvArgs a, int ncols
   const int col = int(blockIdx.x) % ncols, chunk = int(blockIdx.x) / ncols;
   const int x0 = (col % ntx) * OX, y0 = (col / ntx) * OY;
   const int z0 = chunk * lz, z1 = z0 + lz < a.nz ? z0 + lz : a.nz;
-  const u32x4* gin = static_cast<const u32x4*>(a.in);
+  const long long wo = a.win.off(blockIdx.y);
+  const u32x4* gin = at_win(static_cast<const u32x4*>(a.in), wo);
+  const float* const cin = a.c + blockIdx.y * a.c_stride;
+  float* const out = at_win(a.out, wo);
   // A[R][i] = W[16 q + R][i] for MFMA q, rows past the 27 offsets zero
   bf16x8 aw[2];
 #pragma unroll
@@ -716,7 +761,7 @@ __global__ __launch_bounds__(O_THREADS) void conv_out_mfma(ConvArgs a, int ncols
     const int zo = zi - 1;
     if (zo >= z0 && own) {
       const long long v = ((long long)zo * a.ny + y) * a.nx + x;
-      a.out[v] = a.c[v] + (r_prev + bias);
+      out[v] = cin[v] + (r_prev + bias);
     }
     r_prev = r_cur;
     r_cur = r_next;
@@ -772,6 +817,7 @@ struct WgradArgs {
   const bf16_t* t;    // 32->32: x bf16 [V][32]; one channel: the 32-channel field
   float* partial;     // [gridDim.x][28][Cout][Cin]; row 27 holds db at [27][o][0]
   int nx, ny, nz, ntiles;
+  WinMap win;         // windows (grid.y) of s, t and partial
 };
 
 __global__ __launch_bounds__(WG_THREADS, 5) void wgrad32_mfma(WgradArgs a) {
@@ -781,8 +827,9 @@ __global__ __launch_bounds__(WG_THREADS, 5) void wgrad32_mfma(WgradArgs a) {
   unsigned* sg32 = reinterpret_cast<unsigned*>(s_g);
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int ntx = (a.nx + WT_X - 1) / WT_X, nty = (a.ny + WT_Y - 1) / WT_Y;
-  const u32x4* g4 = static_cast<const u32x4*>(a.s);
-  const u32x4* x4 = reinterpret_cast<const u32x4*>(a.t);
+  const long long wo = a.win.off(blockIdx.y);
+  const u32x4* const g4 = at_win(static_cast<const u32x4*>(a.s), wo);
+  const u32x4* const x4 = at_win(reinterpret_cast<const u32x4*>(a.t), wo);
   const int dzi = w / 3, dyi = w % 3;
   f32x4 acc[3][2][2];  // [dx + 1][o half][i half]
   f32x4 accb[2];
@@ -869,7 +916,7 @@ __global__ __launch_bounds__(WG_THREADS, 5) void wgrad32_mfma(WgradArgs a) {
     }
   }
   // D[m][n] of lane (li, lg), element r: o = 16 hm + 4 lg + r, i = 16 hn + li
-  float* P = a.partial + (long long)blockIdx.x * 28 * CH * CH;
+  float* P = at_win(a.partial, wo) + (long long)blockIdx.x * 28 * CH * CH;
 #pragma unroll
   for (int dxi = 0; dxi < 3; ++dxi) {
     const int d = 3 * w + dxi;  // 9 (dz + 1) + 3 (dy + 1) + dx + 1
@@ -914,7 +961,9 @@ __global__ __launch_bounds__(WG1_THREADS) void wgrad1_mfma(WgradArgs a) {
   unsigned* st32 = reinterpret_cast<unsigned*>(s_t);
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int ntx = (a.nx + WT_X - 1) / WT_X, nty = (a.ny + WT_Y - 1) / WT_Y;
-  const u32x4* t4 = reinterpret_cast<const u32x4*>(a.t);
+  const long long wo = a.win.off(blockIdx.y);
+  const u32x4* const t4 = at_win(reinterpret_cast<const u32x4*>(a.t), wo);
+  const void* const sf = at_win(a.s, wo);
   constexpr int NT = SIGMA > 0 ? 1 : 3;  // BF16 terms of the scalar
   f32x4 acc[2][2];
   f32x4 accb[2];
@@ -958,8 +1007,8 @@ __global__ __launch_bounds__(WG1_THREADS) void wgrad1_mfma(WgradArgs a) {
           ((long long)pmod(z0 + hz - 1, a.nz) * a.ny + pmod(y0 + hy - 1, a.ny)) * a.nx +
           pmod(x0 + xq - 1, a.nx);
       float sv;
-      if constexpr (SIGMA > 0) sv = bf2f(static_cast<const bf16_t*>(a.s)[v]);
-      else sv = static_cast<const float*>(a.s)[v];
+      if constexpr (SIGMA > 0) sv = bf2f(static_cast<const bf16_t*>(sf)[v]);
+      else sv = static_cast<const float*>(sf)[v];
       s_s[(hz * SS_H + hy) * SS_P + xq] = sv;
     }
     __syncthreads();
@@ -1034,39 +1083,48 @@ __global__ __launch_bounds__(WG1_THREADS) void wgrad1_mfma(WgradArgs a) {
     if (lg == 3 && li == 0) red[27 * CH] = accb[0][1];  // D[13][0]: 4 * 3 + 1 = 13
   }
   __syncthreads();
-  float* P = a.partial + (long long)blockIdx.x * 28 * CH;
+  float* P = at_win(a.partial, wo) + (long long)blockIdx.x * 28 * CH;
   for (int k = tid; k < 28 * CH; k += WG1_THREADS)
     P[k] = ((s_red[k] + s_red[28 * CH + k]) + s_red[2 * 28 * CH + k]) + s_red[3 * 28 * CH + k];
 }
 
-// grad[param] (+)= sum over the partial sets; maps (d, o, i) -> W offset, d == 27 -> bias (only
-// i == 0 of the bias rows is used).  A block takes 64 consecutive outputs; its 16 thread groups
-// sum interleaved subsets of the sets (group g: sets g, g + 16, ...), and the groups are added in
-// a fixed order: bit-reproducible.
+// sum[k] = sum over a window's partial sets (grid.y = window).  A block takes 64 consecutive outputs;
+// its 16 thread groups sum interleaved subsets of the sets (group g: sets g, g + 16, ...), and the
+// groups are added in a fixed order: bit-reproducible.
 constexpr int RED_K = 64, RED_G = 16;
 
 __global__ __launch_bounds__(RED_K * RED_G) void wgrad_reduce(const float* partial, int nsets,
-                                                              float* grad_w, float* grad_b,
-                                                              int ci, int co) {
+                                                              float* sum, int n, WinMap win) {
   __shared__ float s_sum[RED_G * RED_K];
-  const int n = 28 * co * ci;
+  const long long wo = win.off(blockIdx.y);
+  const float* const P = at_win(partial, wo);
   const int kk = threadIdx.x % RED_K, g = threadIdx.x / RED_K;
   const int k = blockIdx.x * RED_K + kk;
   float acc = 0.f;
   if (k < n)
-    for (int c = g; c < nsets; c += RED_G) acc += partial[(long long)c * n + k];
+    for (int c = g; c < nsets; c += RED_G) acc += P[(long long)c * n + k];
   s_sum[g * RED_K + kk] = acc;
   __syncthreads();
   if (g != 0 || k >= n) return;
   float t = 0.f;
 #pragma unroll
   for (int j = 0; j < RED_G; ++j) t += s_sum[j * RED_K + kk];
+  at_win(sum, wo)[k] = t;
+}
+
+// grad[param] += the windows' sums, in the windows' order (the same order whether they ran together
+// or one after another); maps (d, o, i) -> W offset, d == 27 -> bias (only i == 0 of the bias rows
+// is used).
+__global__ __launch_bounds__(256) void wgrad_add(const float* sum, float* grad_w, float* grad_b,
+                                                 int ci, int co, WinMap win) {
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= 28 * co * ci) return;
   const int d = k / (co * ci), rem = k % (co * ci);
-  if (d < 27) {
-    grad_w[k] += t;
-  } else if (rem % ci == 0) {
-    grad_b[rem / ci] += t;
-  }
+  if (d == 27 && rem % ci != 0) return;
+  float* const g = d < 27 ? grad_w + k : grad_b + rem / ci;
+  float v = *g;
+  for (int w = 0; w < win.n; ++w) v += at_win(sum, win.off(w))[k];
+  *g = v;
 }
 
 // ----------------------------------------------------------------------------- misc element-wise
@@ -1079,9 +1137,10 @@ __global__ void fill_gelu_table(bf16_t* tab) {
 }
 
 
-__global__ void cast_bf16(const float* c, bf16_t* out, long long n) {
+// (grid.y = window: the fields follow one another, the results lie at win's offsets)
+__global__ void cast_bf16(const float* c, bf16_t* out, long long n, WinMap win) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = f2bf(c[i]);
+  if (i < n) at_win(out, win.off(blockIdx.y))[i] = f2bf(c[blockIdx.y * n + i]);
 }
 
 // master fp32 params -> bf16 weights in [d][o][i] and the flipped/transposed copy
@@ -1105,6 +1164,7 @@ struct LossArgs {
   double* partial;      // per block sum of squares
   int n, halo;          // window edge (cubic) and halo
   double inv_total;     // 1 / (batch * interior voxels)
+  WinMap win;           // windows (grid.y) of out, dy and partial; the targets follow one another
 };
 
 constexpr int LOSS_BLOCKS = 256;
@@ -1112,15 +1172,19 @@ constexpr int LOSS_BLOCKS = 256;
 __global__ __launch_bounds__(256) void loss_kernel(LossArgs a) {
   __shared__ double red[256];
   const long long V = (long long)a.n * a.n * a.n;
+  const long long wo = a.win.off(blockIdx.y);
+  const float* const out = at_win(a.out, wo);
+  const float* const target = a.target + blockIdx.y * V;
+  float* const dy = at_win(a.dy, wo);
   double s = 0.0;
   for (long long v = (long long)blockIdx.x * 256 + threadIdx.x; v < V;
        v += (long long)gridDim.x * 256) {
     const int x = int(v % a.n), y = int((v / a.n) % a.n), z = int(v / ((long long)a.n * a.n));
     const bool in = x >= a.halo && x < a.n - a.halo && y >= a.halo && y < a.n - a.halo &&
                     z >= a.halo && z < a.n - a.halo;
-    const float d = in ? a.out[v] - a.target[v] : 0.f;
+    const float d = in ? out[v] - target[v] : 0.f;
     s += double(d) * d;
-    a.dy[v] = float(2.0 * a.inv_total) * d;
+    dy[v] = float(2.0 * a.inv_total) * d;
   }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -1128,20 +1192,26 @@ __global__ __launch_bounds__(256) void loss_kernel(LossArgs a) {
     if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
     __syncthreads();
   }
-  if (threadIdx.x == 0) a.partial[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) at_win(a.partial, wo)[blockIdx.x] = red[0];
 }
 
-// one block of LOSS_BLOCKS threads: fixed-order tree over the per-block sums
+// one block of LOSS_BLOCKS threads: per window a fixed-order tree over the per-block sums, the
+// windows added in order
 __global__ __launch_bounds__(LOSS_BLOCKS) void loss_final(const double* partial, double scale,
-                                                          double* loss, int add) {
+                                                          double* loss, int add, WinMap win) {
   __shared__ double red[LOSS_BLOCKS];
-  red[threadIdx.x] = partial[threadIdx.x];
-  __syncthreads();
-  for (int h = LOSS_BLOCKS / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+  double total = 0.0;
+  for (int w = 0; w < win.n; ++w) {
+    red[threadIdx.x] = at_win(partial, win.off(w))[threadIdx.x];
+    __syncthreads();
+    for (int h = LOSS_BLOCKS / 2; h > 0; h >>= 1) {
+      if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) total = (w > 0 ? total : (add ? *loss : 0.0)) + scale * red[0];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *loss = (add ? *loss : 0.0) + scale * red[0];
+  if (threadIdx.x == 0) *loss = total;
 }
 
 // Adam (Kingma & Ba).  omb1 = 1 - b1 and omb2 = 1 - b2 come from the host in FP64 and are rounded
@@ -1238,7 +1308,8 @@ long long g_num_cus = 256;  // set from the device at evx_surrogate_create
 
 hipError_t launch_conv(int kind, int epi, const ConvArgs& a, hipStream_t s) {
   const long long nt = (long long)((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY) *
-                       ((a.nz + TZ - 1) / TZ);
+                       ((a.nz + TZ - 1) / TZ) * a.win.n;
+  if (nt >= (1LL << 31)) return hipErrorInvalidValue;
   const int ntiles = int(nt);
   // the 1 -> 32 kernel is persistent too: four blocks per CU (its table and halo take 12 KB)
   const unsigned in_grid = unsigned(nt < 4 * g_num_cus ? nt : 4 * g_num_cus);
@@ -1262,12 +1333,12 @@ hipError_t launch_conv(int kind, int epi, const ConvArgs& a, hipStream_t s) {
     // columns of 16 x 16, each marching up lz planes: long runs (few halo planes re-read), but
     // at least about four blocks per CU
     const long long ncols = (long long)((a.nx + OX - 1) / OX) * ((a.ny + OY - 1) / OY);
-    long long lz = (a.nz * ncols + 4 * g_num_cus - 1) / (4 * g_num_cus);
+    long long lz = (a.nz * ncols * a.win.n + 4 * g_num_cus - 1) / (4 * g_num_cus);
     lz = lz < 2 ? 2 : (lz > a.nz ? a.nz : lz);
     const long long grid = ncols * ((a.nz + lz - 1) / lz);
     if (grid >= (1LL << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(conv_out_mfma, dim3(unsigned(grid)), dim3(O_THREADS), 0, s, a, int(ncols),
-                       int(lz));
+    hipLaunchKernelGGL(conv_out_mfma, dim3(unsigned(grid), unsigned(a.win.n)), dim3(O_THREADS), 0,
+                       s, a, int(ncols), int(lz));
   } else {  // backward data of the last layer: FP32 dY -> bf16 dZ
     hipLaunchKernelGGL((conv_in_mfma<true, EPI_DGELU>), dim3(in_grid), dim3(SMALL_THREADS), 0, s,
                        a, ntiles);
@@ -1275,40 +1346,53 @@ hipError_t launch_conv(int kind, int epi, const ConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_wgrad(int layer, const void* gz, const void* x, float* partial, float* grads,
-                        int nx, int ny, int nz, hipStream_t s) {
-  const long long nt =
-      (long long)((nx + WT_X - 1) / WT_X) * ((ny + WT_Y - 1) / WT_Y) * (long long)nz;
+// Tiles of a window, and the partial sets its weight gradients leave (balanced tiles per block).
+long long wgrad_tiles(int nx, int ny, int nz) {
+  return (long long)((nx + WT_X - 1) / WT_X) * ((ny + WT_Y - 1) / WT_Y) * (long long)nz;
+}
+long long wgrad_sets(long long nt, long long maxblk) {
+  const long long per = (nt + maxblk - 1) / maxblk;
+  return (nt + per - 1) / per;
+}
+
+hipError_t launch_wgrad(int layer, const void* gz, const void* x, float* partial, float* sum,
+                        float* grads, int nx, int ny, int nz, const WinMap& win, hipStream_t s) {
+  const long long nt = wgrad_tiles(nx, ny, nz);
   if (nt >= (1LL << 31)) return hipErrorInvalidValue;
   const bool wide = layer == 1 || layer == 2;
   const long long maxblk = wide ? WG_MAXBLK : WG1_MAXBLK;
-  const long long per = (nt + maxblk - 1) / maxblk;  // tiles per block, balanced
-  const int grid = int((nt + per - 1) / per);
+  const int sets = int(wgrad_sets(nt, maxblk));
+  const dim3 grid(unsigned(sets), unsigned(win.n));
   WgradArgs w{};
   w.partial = partial;
   w.nx = nx;
   w.ny = ny;
   w.nz = nz;
   w.ntiles = int(nt);
+  w.win = win;
   if (wide) {
     w.s = gz;
     w.t = static_cast<const bf16_t*>(x);
-    hipLaunchKernelGGL(wgrad32_mfma, dim3(grid), dim3(WG_THREADS), 0, s, w);
+    hipLaunchKernelGGL(wgrad32_mfma, grid, dim3(WG_THREADS), 0, s, w);
   } else if (layer == 0) {  // s = X0 (shifted), T = dZ1
     w.s = x;
     w.t = static_cast<const bf16_t*>(gz);
-    hipLaunchKernelGGL(wgrad1_mfma<1>, dim3(grid), dim3(WG1_THREADS), 0, s, w);
+    hipLaunchKernelGGL(wgrad1_mfma<1>, grid, dim3(WG1_THREADS), 0, s, w);
   } else {                  // s = dY, T = A3 (shifted, moved onto dY)
     w.s = gz;
     w.t = static_cast<const bf16_t*>(x);
-    hipLaunchKernelGGL(wgrad1_mfma<-1>, dim3(grid), dim3(WG1_THREADS), 0, s, w);
+    hipLaunchKernelGGL(wgrad1_mfma<-1>, grid, dim3(WG1_THREADS), 0, s, w);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int ci = cin_of(layer), co = cout_of(layer), n = 28 * ci * co;
-  hipLaunchKernelGGL(wgrad_reduce, dim3((n + RED_K - 1) / RED_K), dim3(RED_K * RED_G), 0, s,
-                     partial, grid,
-                     grads + layer_off(layer), grads + layer_off(layer) + layer_w(layer), ci, co);
+  hipLaunchKernelGGL(wgrad_reduce, dim3(unsigned((n + RED_K - 1) / RED_K), unsigned(win.n)),
+                     dim3(RED_K * RED_G), 0, s, partial, sets, sum, n, win);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(wgrad_add, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, sum,
+                     grads + layer_off(layer), grads + layer_off(layer) + layer_w(layer), ci, co,
+                     win);
   return hipGetLastError();
 }
 
@@ -1321,21 +1405,29 @@ size_t infer_bytes(long long V) {
   return a256(V * 2) + 2 * a256(V * CH * 2) + a256(MP_BLOCKS * sizeof(double));
 }
 
-// Training workspace for one n^3 window: X0 | Z1 A1 Z2 A2 Z3 A3 | dZ3 dZ2 dZ1 (bf16 [V][32]) | out dY
-// (f32 [V]) | target (f32 [V]) | wgrad partials | grads (f32 NPARAM) | loss partials.
+// Training workspace of one n^3 window: X0 | Z1 A1 Z2 A2 Z3 A3 | dZ3 dZ2 dZ1 (bf16 [V][32]) | out dY
+// (f32 [V]) | loss partials | wgrad partials | their sums; then grads (f32 NPARAM), shared by all
+// windows; then the first part again for each further window that is to run at the same time.
 struct TrainBufs {
   bf16_t *x0, *z[3], *act[3], *g[3];  // g[0] = dz3, g[1] = dz2, g[2] = dz1
-  float *out, *dy, *partial, *grads;
+  float *out, *dy, *partial, *sum, *grads;
   double* lpart;
 };
 
-size_t train_bytes(long long V) {
+size_t partial_bytes(int edge) {
+  return a256(size_t(wgrad_sets(wgrad_tiles(edge, edge, edge), WG_MAXBLK)) * 28 * CH * CH * 4);
+}
+size_t window_bytes(int edge) {
+  const long long V = (long long)edge * edge * edge;
   return a256(V * 2) + 9 * a256(V * CH * 2) + 2 * a256(V * 4) +
-         a256(size_t(WG_MAXBLK) * 28 * CH * CH * 4) + a256(NPARAM * 4) +
-         a256(LOSS_BLOCKS * sizeof(double));
+         a256(LOSS_BLOCKS * sizeof(double)) + partial_bytes(edge) + a256(28 * CH * CH * 4);
+}
+size_t train_bytes(int edge, int windows = 1) {
+  return windows * window_bytes(edge) + a256(NPARAM * 4);
 }
 
-TrainBufs carve_train(void* ws, long long V) {
+TrainBufs carve_train(void* ws, int edge) {
+  const long long V = (long long)edge * edge * edge;
   char* p = static_cast<char*>(ws);
   TrainBufs b{};
   auto take = [&](size_t n) { char* q = p; p += a256(n); return q; };
@@ -1347,9 +1439,10 @@ TrainBufs carve_train(void* ws, long long V) {
   for (int i = 0; i < 3; ++i) b.g[i] = reinterpret_cast<bf16_t*>(take(V * CH * 2));
   b.out = reinterpret_cast<float*>(take(V * 4));
   b.dy = reinterpret_cast<float*>(take(V * 4));
-  b.partial = reinterpret_cast<float*>(take(size_t(WG_MAXBLK) * 28 * CH * CH * 4));
-  b.grads = reinterpret_cast<float*>(take(NPARAM * 4));
   b.lpart = reinterpret_cast<double*>(take(LOSS_BLOCKS * sizeof(double)));
+  b.partial = reinterpret_cast<float*>(take(partial_bytes(edge)));
+  b.sum = reinterpret_cast<float*>(take(28 * CH * CH * 4));
+  b.grads = reinterpret_cast<float*>(take(NPARAM * 4));
   return b;
 }
 
@@ -1439,7 +1532,8 @@ evx_status evx_surrogate_workspace_bytes(int nx, int ny, int nz, int train, size
   if (!bytes) return nfail(EVX_ERR_ARG, "bytes is NULL");
   if (!grid_ok(nx, ny, nz)) return nfail(EVX_ERR_SIZE, "grid %d x %d x %d", nx, ny, nz);
   const long long V = (long long)nx * ny * nz;
-  *bytes = train ? train_bytes(V) : infer_bytes(V);
+  const int edge = nx > ny ? (nx > nz ? nx : nz) : (ny > nz ? ny : nz);
+  *bytes = train ? train_bytes(edge, train > 1 ? train : 1) : infer_bytes(V);
   return EVX_OK;
 }
 
@@ -1456,7 +1550,8 @@ evx_status evx_surrogate_infer(evx_net* n, const float* c_in, float* c_out, int 
   bf16_t* x0 = reinterpret_cast<bf16_t*>(p);
   bf16_t* A = reinterpret_cast<bf16_t*>(p + a256(V * 2));
   bf16_t* B = reinterpret_cast<bf16_t*>(p + a256(V * 2) + a256(V * CH * 2));
-  hipLaunchKernelGGL(cast_bf16, dim3(unsigned((V + 255) / 256)), dim3(256), 0, s, c_in, x0, V);
+  hipLaunchKernelGGL(cast_bf16, dim3(unsigned((V + 255) / 256)), dim3(256), 0, s, c_in, x0, V,
+                     WinMap{});
   NET_TRY(hipGetLastError());
   ConvArgs a = conv_args(n, 0, false, x0, nx, ny, nz);
   a.a_out = A;
@@ -1493,62 +1588,79 @@ evx_status evx_surrogate_train_step(evx_net* n, const float* x, const float* y, 
                  double(lr));
   if (!grid_ok(edge, edge, edge)) return nfail(EVX_ERR_SIZE, "window %d", edge);
   const long long V = (long long)edge * edge * edge;
-  if (ws_bytes < train_bytes(V)) return nfail(EVX_ERR_NOMEM, "workspace too small");
+  if (ws_bytes < train_bytes(edge)) return nfail(EVX_ERR_NOMEM, "workspace too small");
   if (reinterpret_cast<uintptr_t>(ws) % 256) return nfail(EVX_ERR_ARG, "workspace alignment");
   hipStream_t s = static_cast<hipStream_t>(stream);
   evx_status st = evx_surrogate_set_params(n, params, stream);
   if (st != EVX_OK) return st;
-  TrainBufs b = carve_train(ws, V);
+  TrainBufs b = carve_train(ws, edge);
   hipLaunchKernelGGL(zero_f32, dim3(unsigned((NPARAM + 255) / 256)), dim3(256), 0, s, b.grads,
                      NPARAM);
   NET_TRY(hipGetLastError());
   const long long inner = (long long)(edge - 2 * halo) * (edge - 2 * halo) * (edge - 2 * halo);
   const double inv_total = 1.0 / (double(batch) * double(inner));
   const unsigned vgrid = unsigned((V + 255) / 256);
-  for (int w = 0; w < batch; ++w) {
-    const float* xw = x + w * V;
-    const float* yw = y + w * V;
-    hipLaunchKernelGGL(cast_bf16, dim3(vgrid), dim3(256), 0, s, xw, b.x0, V);
+  // As many windows at once as the workspace holds.  One 72^3 window is 3.2 rounds of tiles for 256
+  // compute units in the convolutions and 463 uneven blocks in a weight gradient; four together fill
+  // 12.7 of 13 rounds and share the launches (batch 4 of 72^3: 1.92 ms one after another).  Every
+  // sum keeps its order, so the results are those of the windows one after another to the bit.
+  const long long room = 1 + (long long)((ws_bytes - train_bytes(edge)) / window_bytes(edge));
+  const int most = int(room < batch ? room : batch);
+  for (int w0 = 0; w0 < batch; w0 += most) {
+    WinMap win;
+    win.first = (long long)train_bytes(edge);
+    win.stride = (long long)window_bytes(edge);
+    win.n = batch - w0 < most ? batch - w0 : most;
+    const unsigned nw = unsigned(win.n);
+    const float* xw = x + w0 * V;
+    const float* yw = y + w0 * V;
+    auto args = [&](int layer, bool transposed, const void* in) {
+      ConvArgs a = conv_args(n, layer, transposed, in, edge, edge, edge);
+      a.win = win;
+      return a;
+    };
+    hipLaunchKernelGGL(cast_bf16, dim3(vgrid, nw), dim3(256), 0, s, xw, b.x0, V, win);
     NET_TRY(hipGetLastError());
     // forward, keeping pre-activations
-    ConvArgs a = conv_args(n, 0, false, b.x0, edge, edge, edge);
+    ConvArgs a = args(0, false, b.x0);
     a.z_out = b.z[0];
     a.a_out = b.act[0];
     NET_TRY(launch_conv(K_IN1, EPI_GELU_Z, a, s));
     for (int l = 1; l <= 2; ++l) {
-      a = conv_args(n, l, false, b.act[l - 1], edge, edge, edge);
+      a = args(l, false, b.act[l - 1]);
       a.z_out = b.z[l];
       a.a_out = b.act[l];
       NET_TRY(launch_conv(K_MFMA, EPI_GELU_Z, a, s));
     }
-    a = conv_args(n, 3, false, b.act[2], edge, edge, edge);
+    a = args(3, false, b.act[2]);
     a.c = xw;
+    a.c_stride = V;
     a.out = b.out;
     NET_TRY(launch_conv(K_OUT1, EPI_RESID, a, s));
     // loss and dL/dy
-    LossArgs la{b.out, yw, b.dy, b.lpart, edge, halo, inv_total};
-    hipLaunchKernelGGL(loss_kernel, dim3(LOSS_BLOCKS), dim3(256), 0, s, la);
+    LossArgs la{b.out, yw, b.dy, b.lpart, edge, halo, inv_total, win};
+    hipLaunchKernelGGL(loss_kernel, dim3(LOSS_BLOCKS, nw), dim3(256), 0, s, la);
     NET_TRY(hipGetLastError());
     hipLaunchKernelGGL(loss_final, dim3(1), dim3(LOSS_BLOCKS), 0, s, b.lpart, inv_total, loss,
-                       w > 0 ? 1 : 0);
+                       w0 > 0 ? 1 : 0, win);
     NET_TRY(hipGetLastError());
     // backward
-    NET_TRY(launch_wgrad(3, b.dy, b.act[2], b.partial, b.grads, edge, edge, edge, s));
-    a = conv_args(n, 3, true, b.dy, edge, edge, edge);
+    NET_TRY(launch_wgrad(3, b.dy, b.act[2], b.partial, b.sum, b.grads, edge, edge, edge, win, s));
+    a = args(3, true, b.dy);
     a.zprev = b.z[2];
     a.a_out = b.g[0];
     NET_TRY(launch_conv(K_BWD_F32, EPI_DGELU, a, s));                        // g0 = dZ3
-    NET_TRY(launch_wgrad(2, b.g[0], b.act[1], b.partial, b.grads, edge, edge, edge, s));
-    a = conv_args(n, 2, true, b.g[0], edge, edge, edge);
+    NET_TRY(launch_wgrad(2, b.g[0], b.act[1], b.partial, b.sum, b.grads, edge, edge, edge, win, s));
+    a = args(2, true, b.g[0]);
     a.zprev = b.z[1];
     a.a_out = b.g[1];
     NET_TRY(launch_conv(K_MFMA, EPI_DGELU, a, s));                           // g1 = dZ2
-    NET_TRY(launch_wgrad(1, b.g[1], b.act[0], b.partial, b.grads, edge, edge, edge, s));
-    a = conv_args(n, 1, true, b.g[1], edge, edge, edge);
+    NET_TRY(launch_wgrad(1, b.g[1], b.act[0], b.partial, b.sum, b.grads, edge, edge, edge, win, s));
+    a = args(1, true, b.g[1]);
     a.zprev = b.z[0];
     a.a_out = b.g[2];
     NET_TRY(launch_conv(K_MFMA, EPI_DGELU, a, s));                           // g2 = dZ1
-    NET_TRY(launch_wgrad(0, b.g[2], b.x0, b.partial, b.grads, edge, edge, edge, s));
+    NET_TRY(launch_wgrad(0, b.g[2], b.x0, b.partial, b.sum, b.grads, edge, edge, edge, win, s));
   }
   const double c1 = 1.0 - std::pow(0.9, double(step)), c2 = 1.0 - std::pow(0.999, double(step));
   hipLaunchKernelGGL(adam_kernel, dim3(unsigned((NPARAM + 255) / 256)), dim3(256), 0, s, params,
@@ -1562,8 +1674,8 @@ evx_status evx_surrogate_train_buffers(void* ws, size_t ws_bytes, int edge, void
   if (!ws || !ptrs) return nfail(EVX_ERR_ARG, "NULL argument");
   if (!grid_ok(edge, edge, edge)) return nfail(EVX_ERR_SIZE, "window %d", edge);
   const long long V = (long long)edge * edge * edge;
-  if (ws_bytes < train_bytes(V)) return nfail(EVX_ERR_NOMEM, "workspace too small");
-  TrainBufs b = carve_train(ws, V);
+  if (ws_bytes < train_bytes(edge)) return nfail(EVX_ERR_NOMEM, "workspace too small");
+  TrainBufs b = carve_train(ws, edge);
   void* list[13] = {b.x0, b.z[0], b.act[0], b.z[1], b.act[1], b.z[2], b.act[2],
                     b.g[2], b.g[1], b.g[0], b.out, b.dy, b.grads};
   for (int i = 0; i < 13; ++i) ptrs[i] = list[i];

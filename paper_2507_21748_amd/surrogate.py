@@ -56,6 +56,7 @@ class _Workspace:
         self.buf = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
         self.off = (-self.buf.data_ptr()) % 256
         self.nbytes = nbytes
+        self.streams = set()  # streams whose work may still read it when a larger one replaces it
 
     @property
     def ptr(self):
@@ -104,16 +105,37 @@ class Net:
                                                      evx._stream_handle()),
                    "evx_surrogate_set_params")
 
-    def _workspace(self, shape, train: bool) -> _Workspace:
-        key = (tuple(shape), train)
-        if key not in self._ws:
+    # windows of a training batch that run together: four to eight fill the GPU, and their
+    # activations stay below this many bytes
+    TRAIN_WINDOWS, TRAIN_BYTES = 8, 2 << 30
+
+    def _workspace(self, shape, windows: int) -> _Workspace:
+        """The workspace for inference (windows = 0) or for training on up to `windows` windows at
+        once; one per shape and kind, which grows when a larger batch comes."""
+        key = (tuple(shape), windows > 0)
+        have = self._ws.get(key)
+        if have is None or have[0] < windows:
             nz, ny, nx = shape
-            nb = ctypes.c_size_t()
-            evx._check(evx._LIB.evx_surrogate_workspace_bytes(nx, ny, nz, int(train),
-                                                              ctypes.byref(nb)),
-                       "evx_surrogate_workspace_bytes")
-            self._ws[key] = _Workspace(nb.value, self.device)
-        return self._ws[key]
+
+            def size(count):
+                nb = ctypes.c_size_t()
+                evx._check(evx._LIB.evx_surrogate_workspace_bytes(nx, ny, nz, count,
+                                                                  ctypes.byref(nb)),
+                           "evx_surrogate_workspace_bytes")
+                return nb.value
+
+            fit = windows
+            if windows > 1:
+                each = size(2) - size(1)
+                fit = max(1, min(windows, self.TRAIN_WINDOWS, self.TRAIN_BYTES // each))
+            if have is None or size(fit) > have[1].nbytes:
+                for stream in have[1].streams if have else ():
+                    have[1].buf.record_stream(stream)
+                have = (windows, _Workspace(size(fit), self.device))
+            else:
+                have = (windows, have[1])
+            self._ws[key] = have
+        return have[1]
 
     def release_workspaces(self):
         self._ws.clear()
@@ -124,7 +146,7 @@ class Net:
         increment's mean is removed."""
         nz, ny, nx = c.shape
         out = torch.empty_like(c) if out is None else out
-        ws = self._workspace(c.shape, False)
+        ws = self._workspace(c.shape, 0)
         evx._check(evx._LIB.evx_surrogate_infer(
             self._h, evx._dev_ptr(c), evx._dev_ptr(out, numel=c.numel()), nx, ny, nz,
             int(bool(conserve_mass)), ws.ptr, ws.nbytes, evx._stream_handle()),
@@ -136,7 +158,8 @@ class Net:
         float64 tensor) at the parameters before the update."""
         b, n = x.shape[0], x.shape[1]
         assert x.shape == (b, n, n, n) and y.shape == x.shape
-        ws = self._workspace((n, n, n), True)
+        ws = self._workspace((n, n, n), b)
+        ws.streams.add(torch.cuda.current_stream(self.device))
         self.step += 1
         evx._check(evx._LIB.evx_surrogate_train_step(
             self._h, evx._dev_ptr(x), evx._dev_ptr(y), b, n, halo,
@@ -147,7 +170,7 @@ class Net:
 
     def train_buffers(self, n: int) -> dict:
         """Views of the last train step's stored activations and gradients (verification)."""
-        ws = self._workspace((n, n, n), True)
+        ws = self._workspace((n, n, n), 1)
         ptrs = (ctypes.c_void_p * 13)()
         evx._check(evx._LIB.evx_surrogate_train_buffers(ws.ptr, ws.nbytes, n, ptrs),
                    "evx_surrogate_train_buffers")

@@ -46,33 +46,20 @@ struct AdjointCoef {
   float dt, dt_kappa;
 };
 
-inline SpecArgs spec_args(const Geom& g, const TablePtrs& t, const AdjointBufs& b,
-                          const AdjointCoef& c, int mode) {
-  SpecArgs a{};
-  a.C = b.A;
-  a.F = b.B;
-  a.L = b.Lm;
-  a.n = g.spec;
-  a.nx = g.nx;
-  a.ny = g.ny;
-  a.nz = g.nz;
-  a.ypitch = g.ypitch;
-  a.ncols = g.ncols;
-  a.bc = g.bc;
-  a.xcplx = g.xcplx;
-  a.bcy = g.bcy;
-  a.bcz = g.bcz;
-  a.k2x = t.k2_x;
-  a.k2y = t.k2_y;
-  a.k2z = t.k2_z;
-  a.a_dt = c.step.a_dt;
-  a.dt_m_kappa = c.step.dt_m_kappa;
-  a.dt_m = c.step.dt_m;
-  a.dt = c.dt;
-  a.dt_kappa = c.dt_kappa;
-  a.partial = b.partial;
-  a.mode = mode;
+// The z pass over T_xy[c] in A that goes on with the spectral work (colspec_body), and the reduction
+// of the sums its blocks leave.
+inline ColArgs spec_z_args(const Geom& g, const TablePtrs& t, const AdjointBufs& b,
+                           const AdjointCoef& c, int mode, int remap) {
+  ColArgs a = z_args(g, t, b.A, b.A, nullptr, c.step, remap);
+  a.sp = SpecPass{mode, g.nx, g.ny, g.nz, g.bcy, g.bcz, g.xcplx, b.B, b.Lm, b.B, b.Lm, c.dt,
+                  c.dt_kappa};
   return a;
+}
+inline FinalArgs spec_sums(const Geom& g, const ColArgs& a, double* out0, double* out1, double scale0,
+                           double scale1, int add0, int add1) {
+  const int seqs = col_block_seqs(g.fz);
+  return FinalArgs{reinterpret_cast<const double*>(a.out), int((a.nseq + seqs - 1) / seqs), out0,
+                   out1, scale0, scale1, add0, add1, seqs, a.n_lo, a.stride_lo, a.stride_hi};
 }
 
 // lam (in: dL/dc^{n+1}, out: dL/dc^n); dk, dM accumulate (device doubles).
@@ -86,15 +73,12 @@ void sched_adjoint(L& l, const Geom& g, const TablePtrs& t, const float* c, floa
   l.row(g.row_len, g.bc, ROW_FWD_FP, x_args(g, t, nullptr, c, b.B, nullptr));
   const PassBatch spec3{{b.A, b.B, b.Lm}, {b.A, b.B, b.Lm}, 3};
   l.col_batch(g.fy, g.bcy, COL_FWD, y_args(g, t, b.A, b.A, remap), spec3);
-  l.col_batch(g.fz, g.bcz, COL_FWD, z_args(g, t, b.A, b.A, nullptr, StepCoef{0, 0, 0}, remap),
-              spec3);
-  l.spec(spec_args(g, t, b, co, 0));
+  const ColArgs za = spec_z_args(g, t, b, co, SP_ADJOINT, remap);
+  l.col(g.fz, g.bcz, COL_FWD, za);
   const double norm = (g.bc == BC_PERIODIC || g.xcplx) ? 1.0 / double(g.V) : 1.0;
-  l.final(FinalArgs{b.partial, AUX_BLOCKS, dk, dM, norm, norm, 1, 1});
+  l.final(spec_sums(g, za, dk, dM, norm, norm, 1, 1));
   // inverse transforms: Lm -> lam, B -> v
   const PassBatch spec2{{b.Lm, b.B, nullptr}, {b.Lm, b.B, nullptr}, 2};
-  l.col_batch(g.fz, g.bcz, COL_INV, z_args(g, t, b.Lm, b.Lm, nullptr, StepCoef{0, 0, 0}, remap),
-              spec2);
   l.col_batch(g.fy, g.bcy, COL_INV, y_args(g, t, b.Lm, b.Lm, remap), spec2);
   const PassBatch rows_inv{{b.Lm, b.B, nullptr}, {lam, b.v, nullptr}, 2};
   l.row_batch(g.row_len, g.bc, ROW_INV, x_args(g, t, b.Lm, nullptr, nullptr, lam), rows_inv);
@@ -105,13 +89,14 @@ void sched_adjoint(L& l, const Geom& g, const TablePtrs& t, const float* c, floa
 template <class L>
 void sched_diagnostics(L& l, const Geom& g, const TablePtrs& t, const float* c, double kappa,
                        const AdjointBufs& b, double* out, int remap) {
-  sched_forward(l, g, t, c, b.A, false, remap);
-  AdjointCoef co{};
-  l.spec(spec_args(g, t, b, co, 1));
+  l.row(g.row_len, g.bc, ROW_FWD, x_args(g, t, nullptr, c, b.A, nullptr));
+  l.col(g.fy, g.bcy, COL_FWD, y_args(g, t, b.A, b.A, remap));
+  const ColArgs za = spec_z_args(g, t, b, AdjointCoef{}, SP_ENERGY, remap);
+  l.col(g.fz, g.bcz, COL_FWD, za);
   const double norm = (g.bc == BC_PERIODIC || g.xcplx) ? 1.0 / double(g.V) : 1.0;
   const double dx3 = g.dx * g.dx * g.dx;
   // out[1] <- dx^3 (kappa/2) sum w K2 |C|^2, then the real-space sums add f(c) and set the mass
-  l.final(FinalArgs{b.partial, AUX_BLOCKS, out + 1, nullptr, dx3 * 0.5 * kappa * norm, 0.0, 0, 0});
+  l.final(spec_sums(g, za, out + 1, nullptr, dx3 * 0.5 * kappa * norm, 0.0, 0, 0));
   l.realsum(RealSumArgs{c, g.V, b.partial, nullptr});
   l.final(FinalArgs{b.partial, AUX_BLOCKS, out + 1, out, dx3, dx3, 1, 0});
 }

@@ -3,11 +3,6 @@
 
 namespace evx {
 
-__global__ __launch_bounds__(AUX_THREADS) void spec_kernel(SpecArgs a) {
-  __shared__ double red[2 * AUX_THREADS];
-  spec_body(a, threadIdx.x, blockIdx.x, gridDim.x, red);
-}
-
 __global__ __launch_bounds__(AUX_THREADS) void realsum_kernel(RealSumArgs a) {
   __shared__ double red[2 * AUX_THREADS];
   realsum_body(a, threadIdx.x, blockIdx.x, gridDim.x, red);
@@ -50,11 +45,6 @@ hipError_t evx_launch_vm_fused(const VmStencilArgs& a, hipStream_t s) {
   const long long grid = ncols * ((a.nz + lz - 1) / lz);
   if (grid >= (1LL << 31)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(vm_fused_kernel, dim3(unsigned(grid)), dim3(VF_THREADS), 0, s, a, lz);
-  return hipGetLastError();
-}
-
-hipError_t evx_launch_spec(const SpecArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(spec_kernel, dim3(AUX_BLOCKS), dim3(AUX_THREADS), 0, s, a);
   return hipGetLastError();
 }
 

@@ -35,9 +35,6 @@ struct SpecArgs {
   int mode;         // 0 adjoint, 1 energy (sum w K2 |C|^2 into partial[2b])
 };
 
-// Per-axis Parseval weight of the zero-flux (DCT-II) coefficient k on an axis of n cells.
-EVX_DEV double dct_weight(int k, int n) { return (k == 0 ? 0.25 : 0.5) / double(n); }
-
 template <int T>
 EVX_DEV void block_sum2(double& s0, double& s1, int tid, double* red) {
   red[2 * tid] = s0;
@@ -54,10 +51,8 @@ EVX_DEV void block_sum2(double& s0, double& s1, int tid, double* red) {
   s1 = red[1];
 }
 
-// adjoint (mode 0): with C1 = G (P C - dt M K2 F),
-//   dkappa += w Re(conj Lam (-dt M K2^2 G C1)),  dM += w Re(conj Lam (-dt kappa K2^2 G C1
-//   - dt K2 G F)),  L <- G P Lam,  F <- dt M K2 G Lam.
-// energy (mode 1): partial[2b] += w K2 |C|^2.
+// The spectral work of colspec_body on whole spectra (adjoint, mode 0, or energy, mode 1); the host
+// emulator's launcher still offers it.
 EVX_DEV void spec_body(const SpecArgs& a, int tid, int bid, int nblk, double* red) {
   double s0 = 0.0, s1 = 0.0;
   const long long stride = (long long)nblk * AUX_THREADS;
@@ -98,23 +93,12 @@ EVX_DEV void spec_body(const SpecArgs& a, int tid, int bid, int nblk, double* re
       }
       continue;
     }
-    const float cv[2] = {Cv.x, Cv.y}, fv[2] = {Fv.x, Fv.y}, lv[2] = {Lv.x, Lv.y};
-    float uo[2], vo[2];
-    for (int j = 0; j < 2; ++j) {
-      const float k2 = K2[j], k4 = k2 * k2;
-      const float P = 1.0f + a.a_dt * k2;
-      const float G = evx_rcp(1.0f + a.dt_m_kappa * k4 + a.a_dt * k2);
-      const float c1 = G * (P * cv[j] - a.dt_m * k2 * fv[j]);
-      // periodic: Re(conj(L) X) = L.x X.x + L.y X.y, summed over both components with the
-      // same weight; zero flux: two independent real coefficients
-      s0 += w[j] * double(-a.dt_m * k4 * G) * double(lv[j]) * double(c1);
-      s1 += w[j] * (double(-a.dt_kappa * k4 * G) * double(lv[j]) * double(c1)
-                    + double(-a.dt * k2 * G) * double(lv[j]) * double(fv[j]));
-      uo[j] = G * P * lv[j];
-      vo[j] = a.dt_m * k2 * G * lv[j];
-    }
-    a.L[i] = make_float2(uo[0], uo[1]);
-    a.F[i] = make_float2(vo[0], vo[1]);
+    adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[0], w[0], Cv.x, Fv.x, Lv.x, s0,
+                s1);
+    adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[1], w[1], Cv.y, Fv.y, Lv.y, s0,
+                s1);
+    a.L[i] = Lv;
+    a.F[i] = Fv;
   }
   block_sum2<AUX_THREADS>(s0, s1, tid, red);
   if (tid == 0) {
@@ -135,10 +119,8 @@ struct RealSumArgs {
 EVX_DEV void realsum_body(const RealSumArgs& a, int tid, int bid, int nblk, double* red) {
   double s0 = 0.0, s1 = 0.0;
   const long long stride = (long long)nblk * AUX_THREADS;
-  for (long long i = (long long)bid * AUX_THREADS + tid; i < a.n; i += stride) {
-    const double c = a.c[i];
+  auto term = [&](double c, double r) {
     if (a.b) {
-      const double r = a.b[i];
       s0 += (c - r) * (c - r);
       s1 += r * r;
     } else {
@@ -146,7 +128,17 @@ EVX_DEV void realsum_body(const RealSumArgs& a, int tid, int bid, int nblk, doub
       s0 += 0.25 * q * q;
       s1 += c;
     }
+  };
+  // four points in flight a lane: one at a time it waited for each (256^3: 26 -> 12 us)
+  long long i = (long long)bid * AUX_THREADS + tid;
+  for (; i + 3 * stride < a.n; i += 4 * stride) {
+    float c[4], r[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < 4; ++k) c[k] = a.c[i + k * stride];
+    if (a.b)
+      for (int k = 0; k < 4; ++k) r[k] = a.b[i + k * stride];
+    for (int k = 0; k < 4; ++k) term(c[k], r[k]);
   }
+  for (; i < a.n; i += stride) term(a.c[i], a.b ? a.b[i] : 0.f);
   block_sum2<AUX_THREADS>(s0, s1, tid, red);
   if (tid == 0) {
     a.partial[2 * bid] = s0;
@@ -164,13 +156,18 @@ struct FinalArgs {
   double* out1;
   double scale0, scale1;
   int add0, add1;
+  // sums that a spectral z pass left in its columns (col_sums_at): seqs > 0
+  int seqs, n_lo;
+  long long stride_lo, stride_hi;
 };
 
 EVX_DEV void final_body(const FinalArgs& a, int tid, double* red) {
   double s0 = 0.0, s1 = 0.0;
   for (int b = tid; b < a.nparts; b += AUX_THREADS) {
-    s0 += a.partial[2 * b];
-    s1 += a.partial[2 * b + 1];
+    const double* const p =
+        a.partial + (a.seqs ? col_sums_at(b, a.seqs, a.n_lo, a.stride_lo, a.stride_hi) : 2LL * b);
+    s0 += p[0];
+    s1 += p[1];
   }
   block_sum2<AUX_THREADS>(s0, s1, tid, red);
   if (tid == 0) {

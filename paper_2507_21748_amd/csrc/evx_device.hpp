@@ -31,6 +31,7 @@ inline void evx_sync() { evx_emu::block_barrier->arrive_and_wait(); }
 inline int evx_wave_uniform(int v) { return v; }
 inline float evx_rcp(float x) { return 1.0f / x; }
 constexpr bool kEmulated = true;
+inline void evx_here(double&, double&, double&, double&) {}
 
 // Buffer resource: a byte range [base, base + nbytes); accesses at or past nbytes read zero and
 // drop stores, as the hardware's range check does.
@@ -92,6 +93,10 @@ __device__ __forceinline__ float evx_rcp(float x) {
   return __builtin_fmaf(r, __builtin_fmaf(-d, r, 1.0f), r);
 }
 constexpr bool kEmulated = false;
+// The values are computed here, not sunk to their next use.
+__device__ __forceinline__ void evx_here(double& a, double& b, double& c, double& d) {
+  __asm__ volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
 
 // Buffer resource over [base, base + nbytes) (raw, stride 0; word 3 = 0x00020000, the gfx9
 // untyped-buffer format).  A uniform base lives in scalar registers and every access adds one

@@ -80,6 +80,13 @@ static hipError_t plane_go(const PlaneArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// the forward z pass that goes on with the spectral work (ColArgs::sp)
+template <int N, int BC, int MODE>
+__global__ __launch_bounds__(ColCfg<N>::THREADS) void colspec_kernel(ColArgs a) {
+  __shared__ float2 lds[ColCfg<N>::LDS];
+  colspec_body<N, BC, MODE>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
+}
+
 template <int N, int BC, int MODE>
 static hipError_t col_go(const ColArgs& a, hipStream_t s) {
   using C = ColCfg<N>;
@@ -94,6 +101,18 @@ static hipError_t col_go(const ColArgs& a, hipStream_t s) {
     return hipErrorInvalidConfiguration;
   ColArgs b = a;
   b.lane_bytes = unsigned(lane_bytes);
+  if constexpr (MODE == COL_FWD) {
+    if (a.sp.mode != SP_NONE) {
+      if (a.vlen || a.in != a.out) return hipErrorInvalidValue;
+      if (a.sp.mode == SP_ADJOINT)
+        hipLaunchKernelGGL((colspec_kernel<N, BC, SP_ADJOINT>), dim3(unsigned(nblk)),
+                           dim3(C::THREADS), 0, s, b);
+      else
+        hipLaunchKernelGGL((colspec_kernel<N, BC, SP_ENERGY>), dim3(unsigned(nblk)),
+                           dim3(C::THREADS), 0, s, b);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((col_kernel<N, BC, MODE>), dim3(unsigned(nblk)), dim3(C::THREADS), 0, s, b);
   return hipGetLastError();
 }

@@ -20,7 +20,6 @@ EVX_FOR_EACH_N(EVX_DECL)
 
 hipError_t evx_launch_plane_32(const PlaneArgs& a, hipStream_t s);
 hipError_t evx_launch_plane_64(const PlaneArgs& a, hipStream_t s);
-hipError_t evx_launch_spec(const SpecArgs& a, hipStream_t s);
 hipError_t evx_launch_realsum(const RealSumArgs& a, hipStream_t s);
 hipError_t evx_launch_final(const FinalArgs& a, hipStream_t s);
 hipError_t evx_launch_combine(const CombineArgs& a, hipStream_t s);
@@ -68,9 +67,6 @@ struct HipLauncher {
     if (ny == 32) err = evx_launch_plane_32(a, stream);
     else if (ny == 64) err = evx_launch_plane_64(a, stream);
     else bad_len = true;
-  }
-  void spec(const SpecArgs& a) {
-    if (err == hipSuccess && !bad_len) err = evx_launch_spec(a, stream);
   }
   void realsum(const RealSumArgs& a) {
     if (err == hipSuccess && !bad_len) err = evx_launch_realsum(a, stream);

@@ -102,6 +102,21 @@ enum : int {
   ROW_FUSED_POLY = 6 // ROW_FUSED with the cubic poly(c) of RowArgs in place of f'(c)
 };
 
+// What a forward z pass does with the finished spectrum of its columns instead of storing it
+// (colspec_body): SP_ADJOINT the adjoint step's multipliers and gradient sums over three buffers,
+// then their inverse z transforms; SP_ENERGY the gradient energy's sum.
+enum : int { SP_NONE = 0, SP_ADJOINT = 1, SP_ENERGY = 2 };
+struct SpecPass {
+  int mode;
+  int nx, ny, nz;          // points per axis
+  int bcy, bcz, xcplx;     // y and z families; one complex column per cosine bin
+  const float2* f;         // SP_ADJOINT: T[f'(c)] and T[lam] next to `in` = T[c] (z pass pending),
+  const float2* l;         // and where the inverse z transforms of their images go
+  float2* f_out;
+  float2* l_out;
+  float dt, dt_kappa;
+};
+
 // A column pass transforms nseq = 8 nouter sequences: sequence s is column s % 8 of outer index
 // o = s / 8 = o_hi n_lo + o_lo, o_hi the x group (x = 8 o_hi + s % 8) and o_lo the other axis
 // (z for the y pass, y for the z pass); x_lo = 1 would make o_lo the x group instead.
@@ -131,6 +146,7 @@ struct ColArgs {
   int xcomplex;            // z pass: a column is one complex x bin (else two real x bins)
   int mean;                // COL_Z_VM: MEAN_* (the buffer's mean travels beside it, see spec_mean)
   unsigned lane_bytes;     // bytes addressable from a point's block base (col_lane_bytes)
+  SpecPass sp;             // COL_FWD along z that goes on with the spectral work (SP_*)
 };
 
 struct RowArgs {
@@ -409,8 +425,55 @@ struct ColTile {
   }
 };
 
+// Per-axis Parseval weight of the zero-flux (DCT-II) coefficient k on an axis of n cells.
+EVX_DEV double dct_weight(int k, int n) { return (k == 0 ? 0.25 : 0.5) / double(n); }
+
+// One component of a spectral bin in the adjoint step: with C1 = G (P C - dt M K2 F),
+//   dkappa += w Re(conj Lam (-dt M K2^2 G C1)),  dM += w Re(conj Lam (-dt kappa K2^2 G C1
+//   - dt K2 G F)),  l <- G P Lam,  f <- dt M K2 G Lam.
+// (Re(conj(L) X) = L.x X.x + L.y X.y, both components with the same weight; under a cosine x they
+// are two independent real coefficients.)
+EVX_DEV void adjoint_bin(float a_dt, float dt_m_kappa, float dt_m, float dt, float dt_kappa, float k2,
+                         double w, float c, float& f, float& l, double& s0, double& s1) {
+  const float k4 = k2 * k2;
+  const float P = 1.0f + a_dt * k2;
+  const float G = evx_rcp(1.0f + dt_m_kappa * k4 + a_dt * k2);
+  const float c1 = G * (P * c - dt_m * k2 * f);
+  s0 += w * double(-dt_m * k4 * G) * double(l) * double(c1);
+  s1 += w * (double(-dt_kappa * k4 * G) * double(l) * double(c1) +
+             double(-dt * k2 * G) * double(l) * double(f));
+  f = dt_m * k2 * G * l;
+  l = G * P * l;
+}
+
+// Sums s0 and s1 over the block's T lanes in a fixed order; lane 0 ends with the totals.
+template <int T>
+EVX_DEV void block_sums(double& s0, double& s1, int tid, double* red) {
+  red[2 * tid] = s0;
+  red[2 * tid + 1] = s1;
+  evx_sync();
+  for (int n = T; n > 1;) {
+    const int h = (n + 1) / 2;
+    if (tid < n - h) {
+      red[2 * tid] += red[2 * (tid + h)];
+      red[2 * tid + 1] += red[2 * (tid + h) + 1];
+    }
+    evx_sync();
+    n = h;
+  }
+  s0 = red[0];
+  s1 = red[1];
+}
+
+template <int N, int BC, int MODE>
+EVX_DEV void colspec_body(const ColArgs& a, int tid, int bid, int nblk, float2* lds);
+
 template <int N, int BC, int MODE>
 EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* lds) {
+  if constexpr (kEmulated && MODE == COL_FWD) {  // on the GPU kernels of their own
+    if (a.sp.mode == SP_ADJOINT) return colspec_body<N, BC, SP_ADJOINT>(a, tid, bid, nblk, lds);
+    if (a.sp.mode == SP_ENERGY) return colspec_body<N, BC, SP_ENERGY>(a, tid, bid, nblk, lds);
+  }
   using C = ColCfg<N>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B;
   constexpr bool upd =
@@ -623,6 +686,127 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     } else {
       store_points(a.out);
     }
+  }
+}
+
+// The forward z pass with the spectral work behind it (SpecPass).  A block leaves its two FP64 sums
+// in the first two float2 of its own columns of `out` (= `in`), which nothing reads as a spectrum
+// any more; col_sums_at gives their place.  For the adjoint step this one pass replaces the forward
+// z passes of three buffers, a spectral kernel and the inverse z passes of two: 5 instead of 15
+// buffer passes (128^3: 33 -> 16 us), bound at that size by the latency of its chain, on larger
+// grids by memory.  The transforms and the per-bin arithmetic are those of the separate kernels.
+EVX_HD long long col_sums_at(long long block, int seqs, int n_lo, long long stride_lo,
+                             long long stride_hi) {
+  const long long o = block * (seqs / 8), h = o / n_lo;
+  return h * stride_hi + (o - h * n_lo) * stride_lo;
+}
+
+template <int N, int BC, int MODE>
+EVX_DEV void colspec_body(const ColArgs& a, int tid, int bid, int nblk, float2* lds) {
+  using C = ColCfg<N>;
+  constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
+  constexpr bool zf = BC == BC_ZERO_FLUX, adj = MODE == SP_ADJOINT;
+  static_assert(B * N * 8 >= T * 16, "the block's sums fit the exchange area");
+  const SpecPass& q = a.sp;
+  const int b = tid % B, t = tid / B;
+  const unsigned nb = a.lane_bytes;
+  ColTile<N, B> ct;
+  ct.locate(a, remap_block(bid, nblk, a.remap), b, t);
+  auto load = [&](const float2* p, float2 (&x)[E]) {
+    static_for<E>([&](auto e) {
+      constexpr int ev = decltype(e)::value;
+      if constexpr (zf)
+        x[e] = evx_buf_load2(ct.template res_m<ev>(p, a.row_stride, nb),
+                             ct.template off_m<ev>(a.row_stride));
+      else
+        x[e] = evx_buf_load2(ct.res(p, a.row_stride, ev, nb), ct.lo);
+    });
+  };
+  float2* const twl = lds + C::TW;
+  float* const k2l = reinterpret_cast<float*>(lds + C::K2);
+  TwStage<N, T> tws;
+  tws.load(a.tw, tid);
+  TableStage<N, T, float> k2s;
+  k2s.load(a.k2r, tid);
+  float2 c[E], f[adj ? E : 1], l[adj ? E : 1];
+  load(a.in, c);
+  if constexpr (adj) {
+    load(q.f, f);
+    load(q.l, l);
+  }
+  const int y = ct.live ? ct.olo : 0, xc = ct.live ? ct.x : 0;
+  const float ko = a.k2o[y];
+  const bool complex_bin = a.xcomplex;
+  const float kxa = a.k2c[complex_bin ? xc : 2 * xc];
+  const float kxb = complex_bin ? kxa : a.k2c[2 * xc + 1];
+  tws.store(twl, tid);
+  k2s.store(k2l, tid);
+  auto forward = [&](float2 (&x)[E]) {
+    fft_regs<N, -1, B>(x, lds, b, t, twl);
+    if constexpr (zf) makhoul_post<N, B>(x, lds, b, t, a.mk);
+  };
+  forward(c);
+  if constexpr (adj) {
+    forward(f);
+    forward(l);
+  }
+  evx_sync();  // K2 table visible (a single-stage periodic transform has no barrier of its own)
+  // sums per component without the weights; bin 0 of a cosine z weighs half of the others
+  const bool cosz = q.bcz != BC_PERIODIC;
+  double sa[2] = {0.0, 0.0}, sb[2] = {0.0, 0.0};
+  static_for<E>([&](auto e) {
+    const float kyz = ko + k2l[t + TPS * decltype(e)::value];
+    const float ka = kxa + kyz, kb = kxb + kyz;
+    double w = 1.0;
+    if constexpr (decltype(e)::value == 0) w = cosz && t == 0 ? 0.5 : 1.0;
+    if constexpr (adj) {
+      adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, q.dt, q.dt_kappa, ka, w, c[e].x, f[e].x, l[e].x,
+                  sa[0], sa[1]);
+      adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, q.dt, q.dt_kappa, kb, w, c[e].y, f[e].y, l[e].y,
+                  sb[0], sb[1]);
+      // one bin's FP64 terms at a time: left to the end of the pass they hold 100 registers more
+      evx_here(sa[0], sa[1], sb[0], sb[1]);
+    } else {
+      sa[0] += w * double(ka) * double(c[e].x) * double(c[e].x);
+      sb[0] += w * double(kb) * double(c[e].y) * double(c[e].y);
+    }
+  });
+  if constexpr (adj) {
+    auto back = [&](float2 (&x)[E], float2* p) {
+      if constexpr (zf) makhoul_pre<N, B>(x, lds, b, t, a.mk);
+      fft_regs<N, +1, B>(x, lds, b, t, twl);
+      static_for<E>([&](auto e) {
+        constexpr int ev = decltype(e)::value;
+        if constexpr (zf)
+          evx_buf_store2(ct.template res_m<ev>(p, a.row_stride, nb),
+                         ct.template off_m<ev>(a.row_stride), x[e]);
+        else
+          evx_buf_store2(ct.res(p, a.row_stride, ev, nb), ct.lo, x[e]);
+      });
+    };
+    back(l, q.l_out);
+    back(f, q.f_out);
+  }
+  // Parseval weights.  A complex bin weighs 1 on the x half spectrum's ends, else 2, and 1/4 or 1/2
+  // per cosine axis (the 1/V normalisation is applied to the sums).
+  double wa, wb;
+  if (complex_bin) {
+    wa = q.xcplx ? (xc == 0 ? 0.25 : 0.5) : ((xc == 0 || 2 * xc == q.nx) ? 1.0 : 2.0);
+    wa *= q.bcy == BC_PERIODIC ? 1.0 : (y == 0 ? 0.25 : 0.5);
+    wa *= cosz ? 0.5 : 1.0;
+    wb = wa;
+  } else {
+    const double wyz = dct_weight(y, q.ny) * dct_weight(1, q.nz);
+    wa = dct_weight(2 * xc, q.nx) * wyz;
+    wb = dct_weight(2 * xc + 1, q.nx) * wyz;
+  }
+  double s0 = wa * sa[0] + wb * sb[0], s1 = wa * sa[1] + wb * sb[1];
+  evx_sync();
+  block_sums<T>(s0, s1, tid, reinterpret_cast<double*>(lds));
+  if (tid == 0) {
+    double* const p = reinterpret_cast<double*>(a.out + ct.tb);
+    p[0] = s0;
+    p[1] = s1;
   }
 }
 

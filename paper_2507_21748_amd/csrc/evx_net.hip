@@ -226,6 +226,7 @@ struct ConvArgs {
   int nx, ny, nz;
   WinMap win;            // windows of in, z_out, a_out, zprev and out
   long long c_stride;    // floats between the windows of c
+  double* incr;          // EPI_RESID, inference: per block the sum of its out - c (null: none)
 };
 
 // ----------------------------------------------------------------------------- MFMA 32 -> 32
@@ -493,6 +494,10 @@ template <bool IN_F32, int EPI>
 __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int ntiles) {
   static_assert(EPI == EPI_GELU || EPI == EPI_GELU_Z || EPI == EPI_DGELU, "epilogue kind");
   typedef typename std::conditional<IN_F32, float, bf16_t>::type elem_t;
+  // inference reads the FP32 field and rounds it here (training stores the rounded input, which its
+  // weight gradient reads again): a cast pass of its own took 0.28 ms at 512^3
+  constexpr bool CAST = EPI == EPI_GELU;
+  typedef typename std::conditional<CAST, float, elem_t>::type src_t;
   constexpr int NT = IN_F32 ? 3 : 1;
   __shared__ elem_t s_h[HALO_VOX];
   __shared__ __attribute__((aligned(16))) bf16_t s_gt[GT_N];
@@ -503,7 +508,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
   const int ntx = (a.nx + TX - 1) / TX, nty = (a.ny + TY - 1) / TY;
   constexpr int IT = (HALO_VOX + SMALL_THREADS - 1) / SMALL_THREADS;
   const bool narrow = a.nx < HX || a.ny < HY || a.nz < HZ;  // uniform
-  const elem_t* gin = static_cast<const elem_t*>(a.in);
+  const src_t* gin = static_cast<const src_t*>(a.in);
   const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int zl = wave >> 1, yb = (wave & 1) * 4;
   // A[R][d] = W[d][o] for row R = li of MFMA h, channel o = out_channel(h, li), and this lane's
@@ -536,11 +541,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
   }
   // persistent: the table and the weights are staged once, then the block walks tiles; the next
   // tile's halo is loaded into registers while the current one is computed
-  elem_t pre[IT];
+  src_t pre[IT];
   constexpr bool MANY = EPI != EPI_GELU;
   const int per = ntx * nty * ((a.nz + TZ - 1) / TZ);
   auto fetch = [&](int tl) {
-    const elem_t* const src = at_win(gin, a.win.template off<MANY>(window_of<MANY>(tl, per)));
+    const src_t* const src = at_win(gin, a.win.template off<MANY>(window_of<MANY>(tl, per)));
     const int fx0 = (tl % ntx) * TX;
     const int fy0 = (tl / ntx % nty) * TY;
     const int fz0 = (tl / ntx / nty) * TZ;
@@ -559,7 +564,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
         gy = wrap(gy, a.ny);
         gz = wrap(gz, a.nz);
       }
-      pre[k] = src[((long long)gz * a.ny + gy) * a.nx + gx];
+      pre[k] = src[((long long)gz * a.ny + gy) * a.nx + gx];  // rounded when it is staged
     }
   };
   if (int(blockIdx.x) < ntiles) fetch(blockIdx.x);
@@ -573,7 +578,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void conv_in_mfma(ConvArgs a, int nt
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
       const int i = tid + k * SMALL_THREADS;
-      if (i < HALO_VOX) s_h[i] = pre[k];
+      if constexpr (CAST) {
+        if (i < HALO_VOX) s_h[i] = f2bf(pre[k]);
+      } else {
+        if (i < HALO_VOX) s_h[i] = pre[k];
+      }
     }
     __syncthreads();
     if (tile + int(gridDim.x) < ntiles) fetch(tile + gridDim.x);
@@ -684,7 +693,7 @@ constexpr int O_PER_WAVE = (O_GROUPS + O_WAVES - 1) / O_WAVES;   // 6
 constexpr int O_PP = 27;  // P row pitch: odd, so the gathers of a wave's 64 voxels spread over banks
 
 __global__ __launch_bounds__(O_THREADS) void conv_out_mfma(ConvArgs a, int ncols, int lz) {
-  __shared__ float s_p[O_HALO * O_PP];
+  __shared__ __attribute__((aligned(16))) float s_p[O_HALO * O_PP];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int ntx = (a.nx + OX - 1) / OX;
   const int col = int(blockIdx.x) % ncols, chunk = int(blockIdx.x) / ncols;
@@ -726,6 +735,7 @@ __global__ __launch_bounds__(O_THREADS) void conv_out_mfma(ConvArgs a, int ncols
   const int x = x0 + tx, y = y0 + ty;
   const bool own = x < a.nx && y < a.ny;
   float r_prev = 0.f, r_cur = 0.f, r_next = 0.f;  // sums of out[zi - 1], out[zi], out[zi + 1]
+  double incr = 0.0;
   fetch(z0 - 1);
   for (int zi = z0 - 1; zi <= z1; ++zi) {
 #pragma unroll
@@ -761,12 +771,23 @@ __global__ __launch_bounds__(O_THREADS) void conv_out_mfma(ConvArgs a, int ncols
     const int zo = zi - 1;
     if (zo >= z0 && own) {
       const long long v = ((long long)zo * a.ny + y) * a.nx + x;
-      out[v] = cin[v] + (r_prev + bias);
+      const float cv = cin[v], ov = cv + (r_prev + bias);
+      out[v] = ov;
+      incr += double(ov) - double(cv);
     }
     r_prev = r_cur;
     r_cur = r_next;
     r_next = 0.f;
   }
+  if (!a.incr) return;  // uniform; the mass projection's sum, in a fixed order
+  double* const red = reinterpret_cast<double*>(s_p);
+  red[tid] = incr;
+  __syncthreads();
+  for (int h = O_THREADS / 2; h > 0; h >>= 1) {
+    if (tid < h) red[tid] += red[tid + h];
+    __syncthreads();
+  }
+  if (tid == 0) a.incr[blockIdx.x] = red[0];
 }
 
 // ----------------------------------------------------------------------------- weight gradient
@@ -1229,24 +1250,8 @@ __global__ void adam_kernel(float* p, float* m, float* v, const float* g, long l
   p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// Mass projection of a prediction: partial[b] = sum over the block's voxels of (out - c).
+// Mass projection of a prediction (conv_out_mfma leaves the partial sums of its increments).
 constexpr int MP_BLOCKS = 1024;
-
-__global__ __launch_bounds__(256) void increment_sum(const float* out, const float* c, long long n,
-                                                     double* partial) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n;
-       i += (long long)gridDim.x * 256)
-    s += double(out[i]) - double(c[i]);
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
 
 // out -= (sum of partials) / n, the partial sums added in a fixed order by every block.
 __global__ __launch_bounds__(256) void remove_mean(float* out, long long n, const double* partial,
@@ -1306,6 +1311,14 @@ enum : int { K_MFMA = 0, K_IN1 = 1, K_OUT1 = 2, K_BWD_F32 = 3 };
 
 long long g_num_cus = 256;  // set from the device at evx_surrogate_create
 
+long long out_columns(int nx, int ny) {
+  return (long long)((nx + OX - 1) / OX) * ((ny + OY - 1) / OY);
+}
+long long out_planes(long long ncols, int nz, int windows) {
+  const long long lz = (nz * ncols * windows + 4 * g_num_cus - 1) / (4 * g_num_cus);
+  return lz < 2 ? (nz < 2 ? nz : 2) : (lz > nz ? nz : lz);
+}
+
 hipError_t launch_conv(int kind, int epi, const ConvArgs& a, hipStream_t s) {
   const long long nt = (long long)((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY) *
                        ((a.nz + TZ - 1) / TZ) * a.win.n;
@@ -1332,9 +1345,8 @@ hipError_t launch_conv(int kind, int epi, const ConvArgs& a, hipStream_t s) {
   } else if (kind == K_OUT1) {
     // columns of 16 x 16, each marching up lz planes: long runs (few halo planes re-read), but
     // at least about four blocks per CU
-    const long long ncols = (long long)((a.nx + OX - 1) / OX) * ((a.ny + OY - 1) / OY);
-    long long lz = (a.nz * ncols * a.win.n + 4 * g_num_cus - 1) / (4 * g_num_cus);
-    lz = lz < 2 ? 2 : (lz > a.nz ? a.nz : lz);
+    const long long ncols = out_columns(a.nx, a.ny);
+    const long long lz = out_planes(ncols, a.nz, a.win.n);
     const long long grid = ncols * ((a.nz + lz - 1) / lz);
     if (grid >= (1LL << 31)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(conv_out_mfma, dim3(unsigned(grid), unsigned(a.win.n)), dim3(O_THREADS), 0,
@@ -1400,9 +1412,16 @@ bool grid_ok(int nx, int ny, int nz) {
   return nx >= 1 && ny >= 1 && nz >= 1 && (long long)nx * ny * nz * CH < (1LL << 40);
 }
 
-// Inference workspace: X0 (bf16 [V]) | A (bf16 [V][32]) | B (bf16 [V][32]) | mass partials.
-size_t infer_bytes(long long V) {
-  return a256(V * 2) + 2 * a256(V * CH * 2) + a256(MP_BLOCKS * sizeof(double));
+// Inference workspace: A (bf16 [V][32]) | B (bf16 [V][32]) | increment sums, one per workgroup of the
+// last layer: at most one per column and two planes, and about four per compute unit (up to 512)
+// beyond one per column.
+size_t incr_bytes(int nx, int ny, int nz) {
+  const size_t ncols = size_t(out_columns(nx, ny));
+  const size_t fine = ncols * ((size_t(nz) + 1) / 2), few = ncols + 4 * 512;
+  return a256((fine < few ? fine : few) * sizeof(double));
+}
+size_t infer_bytes(int nx, int ny, int nz) {
+  return 2 * a256((long long)nx * ny * nz * CH * 2) + incr_bytes(nx, ny, nz);
 }
 
 // Training workspace of one n^3 window: X0 | Z1 A1 Z2 A2 Z3 A3 | dZ3 dZ2 dZ1 (bf16 [V][32]) | out dY
@@ -1533,7 +1552,7 @@ evx_status evx_surrogate_workspace_bytes(int nx, int ny, int nz, int train, size
   if (!grid_ok(nx, ny, nz)) return nfail(EVX_ERR_SIZE, "grid %d x %d x %d", nx, ny, nz);
   const long long V = (long long)nx * ny * nz;
   const int edge = nx > ny ? (nx > nz ? nx : nz) : (ny > nz ? ny : nz);
-  *bytes = train ? train_bytes(edge, train > 1 ? train : 1) : infer_bytes(V);
+  *bytes = train ? train_bytes(edge, train > 1 ? train : 1) : infer_bytes(nx, ny, nz);
   return EVX_OK;
 }
 
@@ -1543,17 +1562,19 @@ evx_status evx_surrogate_infer(evx_net* n, const float* c_in, float* c_out, int 
   if (!n->have_params) return nfail(EVX_ERR_STATE, "parameters not set");
   if (!grid_ok(nx, ny, nz)) return nfail(EVX_ERR_SIZE, "grid %d x %d x %d", nx, ny, nz);
   const long long V = (long long)nx * ny * nz;
-  if (ws_bytes < infer_bytes(V)) return nfail(EVX_ERR_NOMEM, "workspace too small");
+  if (ws_bytes < infer_bytes(nx, ny, nz)) return nfail(EVX_ERR_NOMEM, "workspace too small");
   if (reinterpret_cast<uintptr_t>(ws) % 256) return nfail(EVX_ERR_ARG, "workspace alignment");
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* p = static_cast<char*>(ws);
-  bf16_t* x0 = reinterpret_cast<bf16_t*>(p);
-  bf16_t* A = reinterpret_cast<bf16_t*>(p + a256(V * 2));
-  bf16_t* B = reinterpret_cast<bf16_t*>(p + a256(V * 2) + a256(V * CH * 2));
-  hipLaunchKernelGGL(cast_bf16, dim3(unsigned((V + 255) / 256)), dim3(256), 0, s, c_in, x0, V,
-                     WinMap{});
-  NET_TRY(hipGetLastError());
-  ConvArgs a = conv_args(n, 0, false, x0, nx, ny, nz);
+  bf16_t* A = reinterpret_cast<bf16_t*>(p);
+  bf16_t* B = reinterpret_cast<bf16_t*>(p + a256(V * CH * 2));
+  double* partial = reinterpret_cast<double*>(p + 2 * a256(V * CH * 2));
+  const bool conserve = (flags & EVX_SURROGATE_CONSERVE_MASS) != 0;
+  const long long ncols = out_columns(nx, ny), lz = out_planes(ncols, nz, 1);
+  const long long sums = ncols * ((nz + lz - 1) / lz);
+  if (conserve && size_t(sums) * sizeof(double) > incr_bytes(nx, ny, nz))
+    return nfail(EVX_ERR_UNSUPPORTED, "mass projection: more than 512 compute units");
+  ConvArgs a = conv_args(n, 0, false, c_in, nx, ny, nz);
   a.a_out = A;
   NET_TRY(launch_conv(K_IN1, EPI_GELU, a, s));
   a = conv_args(n, 1, false, A, nx, ny, nz);
@@ -1565,13 +1586,11 @@ evx_status evx_surrogate_infer(evx_net* n, const float* c_in, float* c_out, int 
   a = conv_args(n, 3, false, A, nx, ny, nz);
   a.c = c_in;
   a.out = c_out;
+  a.incr = conserve ? partial : nullptr;
   NET_TRY(launch_conv(K_OUT1, EPI_RESID, a, s));
-  if (flags & EVX_SURROGATE_CONSERVE_MASS) {
-    double* partial = reinterpret_cast<double*>(p + a256(V * 2) + 2 * a256(V * CH * 2));
-    hipLaunchKernelGGL(increment_sum, dim3(MP_BLOCKS), dim3(256), 0, s, c_out, c_in, V, partial);
-    NET_TRY(hipGetLastError());
+  if (conserve) {
     hipLaunchKernelGGL(remove_mean, dim3(MP_BLOCKS), dim3(256), 0, s, c_out, V, partial,
-                       MP_BLOCKS);
+                       int(sums));
     NET_TRY(hipGetLastError());
   }
   return EVX_OK;

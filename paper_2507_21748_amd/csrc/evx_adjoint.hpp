@@ -16,24 +16,6 @@
 
 namespace evx {
 
-// Full forward transform of a real field into a spectral buffer (optionally of f'(field)).
-template <class L>
-void sched_forward(L& l, const Geom& g, const TablePtrs& t, const float* c, float2* out,
-                   bool fprime_first, int remap) {
-  l.row(g.row_len, g.bc, fprime_first ? ROW_FWD_FP : ROW_FWD,
-        x_args(g, t, nullptr, c, out, nullptr));
-  l.col(g.fy, g.bcy, COL_FWD, y_args(g, t, out, out, remap));
-  l.col(g.fz, g.bcz, COL_FWD, z_args(g, t, out, out, nullptr, StepCoef{0, 0, 0}, remap));
-}
-
-// Full inverse transform of a spectral buffer (consumed) into a real field.
-template <class L>
-void sched_inverse(L& l, const Geom& g, const TablePtrs& t, float2* in, float* c, int remap) {
-  l.col(g.fz, g.bcz, COL_INV, z_args(g, t, in, in, nullptr, StepCoef{0, 0, 0}, remap));
-  l.col(g.fy, g.bcy, COL_INV, y_args(g, t, in, in, remap));
-  l.row(g.row_len, g.bc, ROW_INV, x_args(g, t, in, nullptr, nullptr, c));
-}
-
 struct AdjointBufs {
   float2 *A, *B, *Lm;  // spectral scratch
   float* v;            // real scratch
@@ -68,9 +50,9 @@ void sched_adjoint(L& l, const Geom& g, const TablePtrs& t, const float* c, floa
                    const AdjointBufs& b, const AdjointCoef& co, double* dk, double* dM,
                    int remap) {
   // forward transforms of c, f'(c) and lam (A, B, Lm), each pass batched over the buffers
-  const PassBatch rows_fwd{{c, lam, nullptr}, {b.A, b.Lm, nullptr}, 2};
+  PassBatch rows_fwd{{c, lam, c}, {b.A, b.Lm, b.B}, 3};
+  rows_fwd.fp[2] = 1;
   l.row_batch(g.row_len, g.bc, ROW_FWD, x_args(g, t, nullptr, c, b.A, nullptr), rows_fwd);
-  l.row(g.row_len, g.bc, ROW_FWD_FP, x_args(g, t, nullptr, c, b.B, nullptr));
   const PassBatch spec3{{b.A, b.B, b.Lm}, {b.A, b.B, b.Lm}, 3};
   l.col_batch(g.fy, g.bcy, COL_FWD, y_args(g, t, b.A, b.A, remap), spec3);
   const ColArgs za = spec_z_args(g, t, b, co, SP_ADJOINT, remap);
@@ -80,9 +62,18 @@ void sched_adjoint(L& l, const Geom& g, const TablePtrs& t, const float* c, floa
   // inverse transforms: Lm -> lam, B -> v
   const PassBatch spec2{{b.Lm, b.B, nullptr}, {b.Lm, b.B, nullptr}, 2};
   l.col_batch(g.fy, g.bcy, COL_INV, y_args(g, t, b.Lm, b.Lm, remap), spec2);
-  const PassBatch rows_inv{{b.Lm, b.B, nullptr}, {lam, b.v, nullptr}, 2};
-  l.row_batch(g.row_len, g.bc, ROW_INV, x_args(g, t, b.Lm, nullptr, nullptr, lam), rows_inv);
-  l.combine(CombineArgs{lam, c, b.v, g.V});
+  RowArgs xa = x_args(g, t, b.Lm, nullptr, nullptr, lam);
+  if (g.bc == BC_PERIODIC) {  // both inverse transforms and the f'' term in one pass
+    xa.comb = 1;
+    xa.in_c2 = b.B;
+    xa.in_r = c;
+    l.row(g.row_len, g.bc, ROW_INV, xa);
+  } else {
+    // a cosine row shares its transform with the next row of the same buffer
+    const PassBatch rows_inv{{b.Lm, b.B, nullptr}, {lam, b.v, nullptr}, 2};
+    l.row_batch(g.row_len, g.bc, ROW_INV, xa, rows_inv);
+    l.combine(CombineArgs{lam, c, b.v, g.V});
+  }
 }
 
 // out[0] = mass dx^3 sum c, out[1] = energy dx^3 [sum f(c) + (kappa/2) sum c (-L c)].

@@ -59,6 +59,15 @@ __global__ __launch_bounds__((row_threads<NH, BC>())) void row_gs_kernel(RowArgs
       lds);
 }
 
+// the adjoint step's inverse x pass (RowArgs::comb)
+template <int NH>
+__global__ __launch_bounds__((row_threads<NH, BC_PERIODIC>())) void row_comb_kernel(RowArgs a) {
+  __shared__ float2 lds[RowCfg<NH, BC_PERIODIC>::LDS];
+  rowpass_comb_body<NH>(
+      a, threadIdx.x,
+      (long long)remap_block(blockIdx.x, gridDim.x, a.remap) * RowCfg<NH, BC_PERIODIC>::ROWS, lds);
+}
+
 // One workgroup per z plane (small periodic grids; see planepass_body).
 template <int NY, int NH>
 constexpr int plane_threads() {
@@ -132,6 +141,14 @@ static hipError_t row_go(const RowArgs& a, hipStream_t s) {
       return hipGetLastError();
     }
   }
+  if constexpr (MODE == ROW_INV) {
+    if (a.comb) {
+      if (BC != BC_PERIODIC || a.vx) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((row_comb_kernel<NH>), dim3(unsigned(nblk)),
+                         dim3(RowCfg<NH, BC_PERIODIC>::THREADS), 0, s, a);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((row_kernel<NH, BC, MODE>), dim3(unsigned(nblk)), dim3(C::THREADS), 0, s, a);
   return hipGetLastError();
 }
@@ -191,7 +208,6 @@ static hipError_t row_mode(int mode, const RowArgs& a, hipStream_t s) {
     case ROW_FWD: return row_go<NH, BC, ROW_FWD>(a, s);
     case ROW_INV: return row_go<NH, BC, ROW_INV>(a, s);
     case ROW_INV_ADD: return row_go<NH, BC, ROW_INV_ADD>(a, s);
-    case ROW_FWD_FP: return row_go<NH, BC, ROW_FWD_FP>(a, s);
     case ROW_FUSED_REC: return row_go<NH, BC, ROW_FUSED_REC>(a, s);
     case ROW_FUSED_POLY: return row_go<NH, BC, ROW_FUSED_POLY>(a, s);
     default: return hipErrorInvalidValue;
@@ -213,7 +229,6 @@ static hipError_t row_mode_batch(int mode, const RowArgs& a, const PassBatch& p,
   switch (mode) {
     case ROW_FWD: return row_go_batch<NH, BC, ROW_FWD>(a, p, s);
     case ROW_INV: return row_go_batch<NH, BC, ROW_INV>(a, p, s);
-    case ROW_FWD_FP: return row_go_batch<NH, BC, ROW_FWD_FP>(a, p, s);
     default: return hipErrorInvalidValue;
   }
 }

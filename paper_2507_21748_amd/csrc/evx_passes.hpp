@@ -96,7 +96,7 @@ enum : int {
   ROW_FUSED = 0,  // complex row -> inverse x -> f' -> forward x -> complex row
   ROW_FWD = 1,    // real row -> forward x -> complex row
   ROW_INV = 2,    // complex row -> inverse x -> real row
-  ROW_FWD_FP = 3, // real row -> f'(c) -> forward x -> complex row (adjoint: T[f'(c)])
+  ROW_FWD_FP = 3, // ROW_FWD of f'(c) (the kernels take RowArgs::fp, the emulator offers the mode)
   ROW_FUSED_REC = 4, // ROW_FUSED that also stores the real row it passes through (out_r)
   ROW_INV_ADD = 5,   // ROW_INV that adds the real row to out_r instead of storing it
   ROW_FUSED_POLY = 6 // ROW_FUSED with the cubic poly(c) of RowArgs in place of f'(c)
@@ -174,6 +174,8 @@ struct RowArgs {
   float gs_dt, gs_F, gs_k;
   int mean;            // MEAN_IN: in_c and in_c2 lack their means (spec_mean)
   int rate;            // the results are the reaction terms alone (the species are in states)
+  int comb;            // ROW_INV of two buffers: out_r <- row of in_c - f''(in_r) (row of in_c2)
+  int fp;              // ROW_FWD: transform f'(c) instead of c (one of a batch)
 };
 
 // A spectral buffer may lack its mean: its bin 0 is then zero and the bin's value, an FP64 number,
@@ -202,6 +204,7 @@ struct PassBatch {
   int n;
   float a_dt[kMaxBatch];  // ColArgs::a_dt and state of each pair (the two-species z pass)
   float2* state[kMaxBatch];
+  int fp[kMaxBatch];      // RowArgs::fp of each pair
 };
 EVX_HD void bind_batch(ColArgs& a, const PassBatch& b, int k) {
   a.in = static_cast<const float2*>(b.in[k]);
@@ -217,6 +220,7 @@ EVX_HD void bind_batch(RowArgs& a, bool inverse, const PassBatch& b, int k) {
   } else {
     a.in_r = static_cast<const float*>(b.in[k]);
     a.out_c = static_cast<float2*>(b.out[k]);
+    a.fp = b.fp[k];
   }
 }
 
@@ -926,6 +930,13 @@ struct RealRows {
       if constexpr (V == 2) lds[at + 1] = make_float2(r[I].z, r[I].w);
     });
   }
+  // the staged rows into the lane's pieces
+  EVX_DEV void unstage(int tid, const float2* lds) {
+    pieces(tid, [&](auto I, unsigned, int at) {
+      const float2 u = lds[at], v = V == 2 ? lds[at + V - 1] : u;
+      r[I] = make_float4(u.x, u.y, v.x, v.y);
+    });
+  }
   // stores the staged rows, or adds them to the rows loaded before
   template <bool ADD>
   EVX_DEV void store(int tid, const float2* lds) {
@@ -1322,8 +1333,8 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
     });
     evx_sync();
     static_for<E>([&](auto e) { x[e] = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2]; });
-    if constexpr (MODE == ROW_FWD_FP)
-      static_for<E>([&](auto e) { x[e] = row_nonlin<MODE, false>(1.0f, nullptr, x[e]); });
+    if (MODE == ROW_FWD_FP || (!GS && a.fp))
+      static_for<E>([&](auto e) { x[e] = row_nonlin<ROW_FUSED, false>(1.0f, nullptr, x[e]); });
     evx_sync();
     if constexpr (GS) react(1.0f);
   } else {
@@ -1457,6 +1468,8 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
 // it is bound by its access pattern (65 pieces of 512 bytes a block) and stays at 2.1 ms.
 template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* lds);
+template <int NH>
+EVX_DEV void rowpass_comb_body(const RowArgs& a, int tid, long long r0, float2* lds);
 
 template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* lds) {
@@ -1473,6 +1486,12 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
         rowpass_gs_body<NH, BC, MODE>(a, tid, r, lds);
         evx_sync();
       }
+      return;
+    }
+  }
+  if constexpr (kEmulated && BC == BC_PERIODIC && MODE == ROW_INV) {
+    if (a.comb) {
+      rowpass_comb_body<NH>(a, tid, (long long)bid * C::ROWS, lds);
       return;
     }
   }
@@ -1498,8 +1517,8 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     if constexpr (real_in) {
       real_row_in<NH, B>(a, a.in_r, r0, tid, tables, lds, x);
       static_for<E>([&](auto e) {  // with the halves r2c_post leaves out
-        if constexpr (MODE == ROW_FWD_FP) {
-          x[e] = row_nonlin<MODE, true>(1.0f, nullptr, x[e]);
+        if (MODE == ROW_FWD_FP || a.fp) {
+          x[e] = row_nonlin<ROW_FUSED, true>(1.0f, nullptr, x[e]);
         } else {
           x[e] = cscale(x[e], 0.5f);
         }
@@ -1545,6 +1564,51 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
   } else {
     cos_rows<NH, MODE, false>(a, tid, r0, lds);
   }
+}
+
+// The adjoint step's inverse x pass on a periodic x: rows of in_c (the A operator's image) and in_c2
+// (the B operator's, v) become lam = A image - f''(c) v in one pass, c the field in in_r.  Storing
+// both and combining them in a kernel of its own moved six fields instead of four.
+template <int NH>
+EVX_DEV void rowpass_comb_body(const RowArgs& a, int tid, long long r0, float2* lds) {
+  using C = RowCfg<NH, BC_PERIODIC>;
+  constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
+  using RR = RealRows<B, NH, C::SROW, C::V, T>;
+  int b, t;
+  row_lane<B, TPS>(tid, b, t);
+  float2 x[E], y[E];
+  float2* const twl = lds + C::TW;
+  float2* const rowl = lds + b * C::SROW + t;
+  PostTw<NH, C::PL> w;
+  w.po = lds + C::PO;
+  w.t = t;
+  const SpecLane<TPS> ln(a.sg, r0, b, r0 + b < a.nrows, t);
+  const float2 ny = spec_row_in<NH>(a.in_c2, a.sg, ln, t, y);
+  const float2 nx = spec_row_in<NH>(a.in_c, a.sg, ln, t, x);
+  row_tables<NH, T>(a, tid, t, twl, w);
+  const float sg = a.scale * (a.flip ? dirichlet_sign(r0 + b, 0, a.ny, a.flip) : 1.0f);
+  auto back = [&](float2 (&z)[E], float2 nyq) {
+    row_c2r<NH, B>(z, nyq, w, lds, b, t);
+    fft_regs<NH, +1, B>(z, lds, b, t, twl);
+    static_for<E>([&](auto e) { rowl[TPS * decltype(e)::value] = cscale(z[e], sg); });
+    evx_sync();
+  };
+  RR c(a.in_r, r0, a.nrows), v(a.out_r, r0, a.nrows);
+  back(y, ny);
+  v.unstage(tid, lds);
+  evx_sync();
+  c.load(tid);  // in flight during the second transform
+  back(x, nx);
+  auto lam = [](float l, float cc, float vv) { return l - (3.0f * cc * cc - 1.0f) * vv; };
+  v.pieces(tid, [&](auto I, unsigned off, int at) {
+    const float2 p = lds[at], q = C::V == 2 ? lds[at + C::V - 1] : p;
+    const float4 cc = c.r[I], vv = v.r[I];
+    const float2 o = make_float2(lam(p.x, cc.x, vv.x), lam(p.y, cc.y, vv.y));
+    if constexpr (C::V == 2)
+      evx_buf_store4(v.buf, off, make_float4(o.x, o.y, lam(q.x, cc.z, vv.z), lam(q.y, cc.w, vv.w)));
+    else
+      evx_buf_store2(v.buf, off, o);
+  });
 }
 
 // The two-species fused x pass: u and v to real rows, one explicit reaction step, and back (MODE

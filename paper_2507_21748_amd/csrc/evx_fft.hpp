@@ -272,6 +272,18 @@ constexpr int seqs_per_block() {
   return b;
 }
 
+// Columns per tile of the stored spectral state: the sequences of a 256-thread workgroup (of one
+// lane a sequence at length 16).  It is a format (a caller may keep a state in a file and resume
+// from it), so it does not follow the workgroup; every workgroup covers part of one tile or all.
+template <int N>
+constexpr int state_cols() {
+  constexpr int tps = N == 16 ? 1 : FftPlan<N>::TPS;
+  int b = 8;
+  while (2 * b * tps <= 256 && b < 256) b *= 2;
+  while (b > 8 && b * N * 8 > 65536) b /= 2;
+  return b;
+}
+
 // LDS slot of point n of sequence b in the exchange area.
 template <int B>
 EVX_DEV int lidx(int n, int b) {

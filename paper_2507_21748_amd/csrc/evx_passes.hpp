@@ -372,6 +372,7 @@ constexpr int makhoul_group_min(int e) {
 template <int N, int B>
 struct ColTile {
   static constexpr int TPS = FftPlan<N>::TPS;
+  static constexpr int SB = state_cols<N>();
   long long tb = 0;  // float2 offset of the block's first sequence (uniform)
   unsigned lo = 0;   // lane byte offset of point 0 relative to tb, or kDeadLane
   unsigned lc = 0;   // lane byte offset of its column (row 0) relative to tb
@@ -398,14 +399,16 @@ struct ColTile {
                            ((long long)l - (long long)l0) * a.stride_lo + c;
     lc = unsigned(cofs * 8);
     lo = live ? unsigned((cofs + (long long)t * a.row_stride) * 8) : kDeadLane;
-    so = live ? unsigned((t * B + b) * 8) : kDeadLane;
+    so = live ? unsigned((t * SB + int(s0 % unsigned(SB)) + b) * 8) : kDeadLane;
   }
-  // The spectral state is stored tile-major: tile, then transform point k, then column b, at
-  // (tile N + k) B + b, so that a block's state is one contiguous N B run (read and written only
-  // by the z pass).  Point t + TPS e of lane (t, b): uniform base plus the lane offset `so`.
+  // The spectral state is stored tile-major: tile of SB sequences, then transform point k, then
+  // column, at (tile N + k) SB + column (read and written only by the z pass).  A block's state is
+  // one contiguous N B run where B = SB, else N runs of B.  Point t + TPS e of lane (t, b): uniform
+  // base plus the lane offset `so`.
   EVX_DEV evx_buf sres(const float2* state, int e) const {
-    return evx_make_buf(state + tile * ((long long)N * B) + (long long)(TPS * e) * B,
-                        unsigned(TPS * B * 8));
+    static_assert(SB % B == 0, "a block lies within one tile of the state");
+    return evx_make_buf(state + tile / (SB / B) * ((long long)N * SB) + (long long)(TPS * e) * SB,
+                        unsigned(TPS * SB * 8));
   }
   // vertex-centred axis: lane offset of data row `row` from the point-0 base
   EVX_DEV unsigned voff(long long row_stride, int row) const {

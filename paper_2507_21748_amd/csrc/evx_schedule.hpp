@@ -43,6 +43,19 @@ inline int col_block_seqs(int n) {
   }
 }
 
+// Columns per tile of the spectral state for a z transform length (0 if unsupported).
+inline int col_state_cols(int n) {
+  switch (n) {
+#define EVX_CASE(N) \
+  case N:           \
+    return state_cols<N>();
+    EVX_FOR_EACH_N(EVX_CASE)
+#undef EVX_CASE
+    default:
+      return 0;
+  }
+}
+
 struct Geom {
   int nx = 0, ny = 0, nz = 0;   // points per axis (the data)
   int vert = 0;          // vertex-centred zero-flux axes (bit 0 x, 1 y, 2 z): the transform is the
@@ -101,7 +114,7 @@ inline Geom make_geom3(int nx, int ny, int nz, int bcx, int bcy, int bcz, int sc
   g.ngx = (g.ncols + 7) / 8;
   g.ypitch = ny + kSpecYPad;
   g.spec = (long long)g.ngx * nz * g.ypitch * 8;
-  const long long bz = col_block_seqs(g.fz), nseq_z = (long long)g.ngx * ny * 8;
+  const long long bz = col_state_cols(g.fz), nseq_z = (long long)g.ngx * ny * 8;
   g.state = bz > 0 ? (nseq_z + bz - 1) / bz * bz * g.fz : g.spec;
   g.nrows = (long long)ny * nz;
   g.plane_ny = (bcx == BC_PERIODIC && bcy == BC_PERIODIC && bcz == BC_PERIODIC &&

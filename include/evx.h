@@ -246,8 +246,8 @@ evx_status evx_ch_diagnostics(evx_plan* plan, const float* c, const evx_ch_param
  * u, v: caller-owned real fields (C order, V floats each), advanced nsteps in place on the plan's
  * grid, boundaries and scheme.  Needs a workspace sized for EVX_OP_GRAY_SCOTT (EVX_ERR_NOMEM
  * otherwise); it uses the stepper's work buffer, so a later evx_ch_advance restores it from the
- * state first.  Per step: one reaction kernel, the four forward transforms batched per pass, one
- * spectral update, the two inverse transforms batched per pass. */
+ * state first.  The species stay spectral between the steps of a call: a step is the two y passes, an x
+ * pass with the reaction and a z pass with the multiplier, each over both species. */
 typedef struct evx_gs_params {
   double dt;
   double Du;

@@ -1,7 +1,6 @@
 // Pass schedules of the adjoint step and of the diagnostics (shared by the HIP launcher and the
 // host emulator).  A launcher L additionally provides col_batch / row_batch (one pass over a
-// PassBatch of buffer pairs), spec(SpecArgs), realsum(RealSumArgs), final(FinalArgs) and
-// combine(CombineArgs).
+// PassBatch of buffer pairs), realsum(RealSumArgs), final(FinalArgs) and combine(CombineArgs).
 //
 // Adjoint of one step c^{n+1} = A c^n - B f'(c^n), A = T^{-1} diag(G P) T,
 // B = T^{-1} diag(dt M K2 G) T (both symmetric):

@@ -607,6 +607,9 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
         const float gb = evx_rcp(1.0f + a.a_dt * Kb + a.dt_m_kappa * Kb * Kb);
         x[e] = make_float2((cs[e].x + a.dt_m * x[e].x) * ga, (cs[e].y + a.dt_m * x[e].y) * gb);
       });
+      // a vertex-centred axis reads each state row twice, once as its mirror, which another lane owns:
+      // every lane has its states before any lane stores new ones
+      if (!zf && a.vlen) evx_sync();
       store_points(a.state);
     } else if (a.mean && ct.tile == 0 && b == 0 && t == 0) {  // bin 0, whose multiplier is dt
       double* const m = spec_mean(a.out, a.n_lo);

@@ -52,11 +52,13 @@ def _lib():
 
 
 class _Workspace:
-    def __init__(self, nbytes: int, device):
+    def __init__(self, nbytes: int, device, windows: int = 0, replaced=None):
         self.buf = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
         self.off = (-self.buf.data_ptr()) % 256
         self.nbytes = nbytes
-        self.streams = set()  # streams whose work may still read it when a larger one replaces it
+        self.windows = windows    # training windows it holds
+        self.asked = windows      # the largest batch it was asked for
+        self.replaced = replaced  # the smaller one before it, kept alive
 
     @property
     def ptr(self):
@@ -111,31 +113,38 @@ class Net:
 
     def _workspace(self, shape, windows: int) -> _Workspace:
         """The workspace for inference (windows = 0) or for training on up to `windows` windows at
-        once; one per shape and kind, which grows when a larger batch comes."""
+        once, one per shape and kind.  A training step takes any workspace of one window or more, so
+        a full device means fewer windows at once, and a larger batch brings a larger workspace only
+        where that holds twice the windows.  The one it replaces stays until release_workspaces: a
+        captured graph, another stream or a view of train_buffers may still use it."""
         key = (tuple(shape), windows > 0)
-        have = self._ws.get(key)
-        if have is None or have[0] < windows:
-            nz, ny, nx = shape
+        ws = self._ws.get(key)
+        if ws is not None and ws.asked >= windows:
+            return ws
+        nz, ny, nx = shape
 
-            def size(count):
-                nb = ctypes.c_size_t()
-                evx._check(evx._LIB.evx_surrogate_workspace_bytes(nx, ny, nz, count,
-                                                                  ctypes.byref(nb)),
-                           "evx_surrogate_workspace_bytes")
-                return nb.value
+        def size(count):
+            nb = ctypes.c_size_t()
+            evx._check(evx._LIB.evx_surrogate_workspace_bytes(nx, ny, nz, count,
+                                                              ctypes.byref(nb)),
+                       "evx_surrogate_workspace_bytes")
+            return nb.value
 
-            fit = windows
-            if windows > 1:
-                each = size(2) - size(1)
-                fit = max(1, min(windows, self.TRAIN_WINDOWS, self.TRAIN_BYTES // each))
-            if have is None or size(fit) > have[1].nbytes:
-                for stream in have[1].streams if have else ():
-                    have[1].buf.record_stream(stream)
-                have = (windows, _Workspace(size(fit), self.device))
-            else:
-                have = (windows, have[1])
-            self._ws[key] = have
-        return have[1]
+        fit = windows
+        if windows > 1:
+            each = size(2) - size(1)
+            fit = max(1, min(windows, self.TRAIN_WINDOWS, self.TRAIN_BYTES // each))
+        while ws is None or fit >= 2 * ws.windows:
+            try:
+                ws = _Workspace(size(fit), self.device, fit, ws)
+                break
+            except torch.OutOfMemoryError:
+                if ws is None and fit <= 1:
+                    raise
+                fit //= 2
+        ws.asked = windows
+        self._ws[key] = ws
+        return ws
 
     def release_workspaces(self):
         self._ws.clear()
@@ -159,7 +168,6 @@ class Net:
         b, n = x.shape[0], x.shape[1]
         assert x.shape == (b, n, n, n) and y.shape == x.shape
         ws = self._workspace((n, n, n), b)
-        ws.streams.add(torch.cuda.current_stream(self.device))
         self.step += 1
         evx._check(evx._LIB.evx_surrogate_train_step(
             self._h, evx._dev_ptr(x), evx._dev_ptr(y), b, n, halo,

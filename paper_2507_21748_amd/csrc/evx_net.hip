@@ -1252,20 +1252,40 @@ __global__ void adam_kernel(float* p, float* m, float* v, const float* g, long l
 
 // Mass projection of a prediction (conv_out_mfma leaves the partial sums of its increments).
 constexpr int MP_BLOCKS = 1024;
+// Every block of remove_mean adds all the sums, so a plane of many columns (one sum each or more)
+// folds them first: 8192 x 8192 x 1 has 262144 and took 35.0 ms an inference without, 34.4 with;
+// up to this many sums (32 KB, 512^3 has 1024) the extra launch gains nothing.
+constexpr int MP_FOLD = 4 * MP_BLOCKS;
 
-// out -= (sum of partials) / n, the partial sums added in a fixed order by every block.
-__global__ __launch_bounds__(256) void remove_mean(float* out, long long n, const double* partial,
-                                                   int nparts) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int b = threadIdx.x; b < nparts; b += 256) s += partial[b];
+// The block's 256 values added in a fixed order.
+__device__ double block_total(double s, double* red) {
   red[threadIdx.x] = s;
   __syncthreads();
   for (int h = 128; h > 0; h >>= 1) {
     if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
     __syncthreads();
   }
-  const float shift = float(red[0] / double(n));
+  return red[0];
+}
+
+// partial[b per] <- the sum of partial[b per .. b per + per - 1] (block b).
+__global__ __launch_bounds__(256) void fold_sums(double* partial, int nparts, int per) {
+  __shared__ double red[256];
+  const int first = blockIdx.x * per, end = first + per < nparts ? first + per : nparts;
+  double s = 0.0;
+  for (int b = first + int(threadIdx.x); b < end; b += 256) s += partial[b];
+  s = block_total(s, red);  // (its barriers: the block's values are read)
+  if (threadIdx.x == 0) partial[first] = s;
+}
+
+// out -= (sum of the nparts values at partial[b stride]) / n, added in a fixed order by every block.
+__global__ __launch_bounds__(256) void remove_mean(float* out, long long n, const double* partial,
+                                                   int nparts, int stride) {
+  __shared__ double red[256];
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nparts; b += 256) s += partial[(long long)b * stride];
+  s = block_total(s, red);
+  const float shift = float(s / double(n));
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n;
        i += (long long)gridDim.x * 256)
     out[i] -= shift;
@@ -1589,8 +1609,13 @@ evx_status evx_surrogate_infer(evx_net* n, const float* c_in, float* c_out, int 
   a.incr = conserve ? partial : nullptr;
   NET_TRY(launch_conv(K_OUT1, EPI_RESID, a, s));
   if (conserve) {
-    hipLaunchKernelGGL(remove_mean, dim3(MP_BLOCKS), dim3(256), 0, s, c_out, V, partial,
-                       int(sums));
+    const int per = sums > MP_FOLD ? int((sums + MP_BLOCKS - 1) / MP_BLOCKS) : 1;
+    const int folded = int((sums + per - 1) / per);
+    if (per > 1) {
+      hipLaunchKernelGGL(fold_sums, dim3(unsigned(folded)), dim3(256), 0, s, partial, int(sums), per);
+      NET_TRY(hipGetLastError());
+    }
+    hipLaunchKernelGGL(remove_mean, dim3(MP_BLOCKS), dim3(256), 0, s, c_out, V, partial, folded, per);
     NET_TRY(hipGetLastError());
   }
   return EVX_OK;

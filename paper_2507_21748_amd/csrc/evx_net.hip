@@ -1453,17 +1453,19 @@ struct TrainBufs {
   double* lpart;
 };
 
-size_t partial_bytes(int edge) {
-  return a256(size_t(wgrad_sets(wgrad_tiles(edge, edge, edge), WG_MAXBLK)) * 28 * CH * CH * 4);
+size_t partial_bytes(int nx, int ny, int nz) {
+  return a256(size_t(wgrad_sets(wgrad_tiles(nx, ny, nz), WG_MAXBLK)) * 28 * CH * CH * 4);
 }
-size_t window_bytes(int edge) {
-  const long long V = (long long)edge * edge * edge;
+size_t window_bytes(int nx, int ny, int nz) {
+  const long long V = (long long)nx * ny * nz;
   return a256(V * 2) + 9 * a256(V * CH * 2) + 2 * a256(V * 4) +
-         a256(LOSS_BLOCKS * sizeof(double)) + partial_bytes(edge) + a256(28 * CH * CH * 4);
+         a256(LOSS_BLOCKS * sizeof(double)) + partial_bytes(nx, ny, nz) + a256(28 * CH * CH * 4);
 }
-size_t train_bytes(int edge, int windows = 1) {
-  return windows * window_bytes(edge) + a256(NPARAM * 4);
+size_t train_bytes(int nx, int ny, int nz, int windows = 1) {
+  return windows * window_bytes(nx, ny, nz) + a256(NPARAM * 4);
 }
+size_t window_bytes(int edge) { return window_bytes(edge, edge, edge); }
+size_t train_bytes(int edge) { return train_bytes(edge, edge, edge); }
 
 TrainBufs carve_train(void* ws, int edge) {
   const long long V = (long long)edge * edge * edge;
@@ -1479,7 +1481,7 @@ TrainBufs carve_train(void* ws, int edge) {
   b.out = reinterpret_cast<float*>(take(V * 4));
   b.dy = reinterpret_cast<float*>(take(V * 4));
   b.lpart = reinterpret_cast<double*>(take(LOSS_BLOCKS * sizeof(double)));
-  b.partial = reinterpret_cast<float*>(take(partial_bytes(edge)));
+  b.partial = reinterpret_cast<float*>(take(partial_bytes(edge, edge, edge)));
   b.sum = reinterpret_cast<float*>(take(28 * CH * CH * 4));
   b.grads = reinterpret_cast<float*>(take(NPARAM * 4));
   return b;
@@ -1570,9 +1572,7 @@ evx_status evx_surrogate_set_params(evx_net* n, const float* params, void* strea
 evx_status evx_surrogate_workspace_bytes(int nx, int ny, int nz, int train, size_t* bytes) {
   if (!bytes) return nfail(EVX_ERR_ARG, "bytes is NULL");
   if (!grid_ok(nx, ny, nz)) return nfail(EVX_ERR_SIZE, "grid %d x %d x %d", nx, ny, nz);
-  const long long V = (long long)nx * ny * nz;
-  const int edge = nx > ny ? (nx > nz ? nx : nz) : (ny > nz ? ny : nz);
-  *bytes = train ? train_bytes(edge, train > 1 ? train : 1) : infer_bytes(nx, ny, nz);
+  *bytes = train ? train_bytes(nx, ny, nz, train > 1 ? train : 1) : infer_bytes(nx, ny, nz);
   return EVX_OK;
 }
 

@@ -21,6 +21,7 @@
 //                 partial sums with a fixed-order reduction (bit-reproducible).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -196,6 +197,10 @@ struct WinMap {
     return w == n - 1 ? 0 : first + w * stride;
   }
 };
+// Windows run together at most: a launch's grid.y is the window (65535 at most), a tile looks for its
+// window one by one, and this many fill every persistent grid (four blocks a compute unit) even at one
+// tile each.
+constexpr int MAX_WINDOWS = 1024;
 template <class T>
 __device__ __forceinline__ T* at_win(T* p, long long bytes) {
   return (T*)((char*)p + bytes);
@@ -1649,7 +1654,7 @@ evx_status evx_surrogate_train_step(evx_net* n, const float* x, const float* y, 
   // 12.7 of 13 rounds and share the launches (batch 4 of 72^3: 1.92 ms one after another).  Every
   // sum keeps its order, so the results are those of the windows one after another to the bit.
   const long long room = 1 + (long long)((ws_bytes - train_bytes(edge)) / window_bytes(edge));
-  const int most = int(room < batch ? room : batch);
+  const int most = int(std::min({room, (long long)batch, (long long)MAX_WINDOWS}));
   for (int w0 = 0; w0 < batch; w0 += most) {
     WinMap win;
     win.first = (long long)train_bytes(edge);

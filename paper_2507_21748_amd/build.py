@@ -76,6 +76,22 @@ def build(jobs: int | None = None, verbose: bool = False, lib: str = LIB,
     return lib
 
 
+def build_tests(verbose: bool = False) -> list[str]:
+    """The device code that tests run on its own: tests/hip/<name>.hip -> tests/hip/lib<name>.so."""
+    out = []
+    folder = os.path.join(ROOT, "tests", "hip")
+    for src in sorted(os.listdir(folder)) if os.path.isdir(folder) else []:
+        if src.endswith(".hip"):
+            lib = os.path.join(folder, f"lib{src[:-4]}.so")
+            _run([hipcc(), *HIPFLAGS, "-shared", os.path.join(folder, src), "-o", lib + ".tmp"])
+            os.replace(lib + ".tmp", lib)
+            out.append(lib)
+    if verbose:
+        print("built", *out)
+    return out
+
+
 if __name__ == "__main__":
     build(verbose=True)
+    build_tests(verbose=True)
     sys.exit(0)

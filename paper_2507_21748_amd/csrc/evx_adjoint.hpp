@@ -112,6 +112,11 @@ void sched_distance(L& l, const Geom& g, const float* a, const float* b, const A
 struct GsCoef {
   float dt, dt_du, dt_dv, F, k;
 };
+// The diffusion multipliers' common scale (coef_scale).
+inline float gs_scale(const Geom& g, const GsCoef& co) {
+  const double d = co.dt_du > co.dt_dv ? co.dt_du : co.dt_dv;
+  return coef_scale(1.0 + d * k2_bound(g));
+}
 
 template <class L>
 void sched_gray_scott(L& l, const Geom& g, const TablePtrs& t, float* u, float* v,
@@ -120,9 +125,10 @@ void sched_gray_scott(L& l, const Geom& g, const TablePtrs& t, float* u, float* 
   const bool states = g.flip != 0;
   const PassBatch two{{b.A, b.B}, {b.A, b.B}, 2};
   const ColArgs ya = y_args(g, t, b.A, b.A, remap);
-  const StepCoef zc{0.0f, 0.0f, states ? co.dt : 1.0f};  // a_dt comes with the batch
+  const float sc = gs_scale(g, co);
+  const StepCoef zc{0.0f, 0.0f, sc * (states ? co.dt : 1.0f), sc};  // a_dt comes with the batch
   ColArgs za = z_args(g, t, b.A, b.A, nullptr, zc, remap);
-  PassBatch upd{{b.A, b.B}, {b.A, b.B}, 2, {co.dt_du, co.dt_dv}};
+  PassBatch upd{{b.A, b.B}, {b.A, b.B}, 2, {sc * co.dt_du, sc * co.dt_dv}};
   RowArgs xa = x_args(g, t, b.A, u, b.A, nullptr);
   xa.gs = 1;
   xa.in_c2 = b.B;
@@ -172,7 +178,8 @@ void sched_varmob(L& l, const Geom& g, const TablePtrs& t, float* phi, const Adj
                   const VmCoef& co, int nsteps, int remap) {
   const int per = (g.bc == BC_PERIODIC ? 1 : 0) | (g.bcy == BC_PERIODIC ? 2 : 0) |
                   (g.bcz == BC_PERIODIC ? 4 : 0);
-  const StepCoef zc{0.0f, co.c4, co.dt};  // the z pass reads dt from dt_m, c4 from dt_m_kappa
+  // the z pass reads dt from dt_m, c4 from dt_m_kappa
+  const StepCoef zc = implicit_coef(g, 0.0, co.c4, co.dt, false);
   // mu and the fluxes in one z-marching pass (mu stays in LDS)
   const VmStencilArgs fused{phi, b.v2, g.nx, g.ny, g.nz, per, co.c_g, co.c_lap, co.c_flux};
   for (int n = 0; n < nsteps; ++n) {

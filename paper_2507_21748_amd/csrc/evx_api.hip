@@ -142,8 +142,16 @@ int zmode_of(const evx_ch_params* q) {
   return etd ? COL_Z_ETD : COL_Z_UPDATE;
 }
 
-StepCoef coef_of(const evx_ch_params* q) {
-  return StepCoef{float(q->A * q->dt), float(q->dt * q->M * q->kappa), float(q->dt * q->M)};
+StepCoef coef_of(const evx_plan* p, const evx_ch_params* q) {
+  const double a_dt = q->A * q->dt, dt_m_kappa = q->dt * q->M * q->kappa, dt_m = q->dt * q->M;
+  if (q->integrator == EVX_INTEGRATOR_ETD1)
+    return StepCoef{float(a_dt), float(dt_m_kappa), float(dt_m)};
+  return implicit_coef(p->g, a_dt, dt_m_kappa, dt_m, q->model == EVX_MODEL_ALLEN_CAHN);
+}
+
+AdjointCoef adjoint_coef(const evx_plan* p, const evx_ch_params* q) {
+  const StepCoef c = coef_of(p, q);
+  return AdjointCoef{c, float(q->dt * c.one), float(q->dt * q->kappa * c.one)};
 }
 
 // Launcher that optionally brackets each launch with an event pair.
@@ -527,7 +535,7 @@ evx_status evx_ch_advance(evx_plan* p, int nsteps, const evx_ch_params* q, void*
   if (!p->w_valid) {
     if ((st = evx_ch_restore(p, s)) != EVX_OK) return st;
   }
-  st = run_steps(p, nsteps, coef_of(q), zmode_of(q), s, "advance");
+  st = run_steps(p, nsteps, coef_of(p, q), zmode_of(q), s, "advance");
   if (st == EVX_OK && q->check_finite) st = check_state_finite(p, p->W, s);
   return st;
 }
@@ -544,7 +552,7 @@ evx_status evx_ch_advance_record(evx_plan* p, int nsteps, const evx_ch_params* q
     if ((st = evx_ch_restore(p, s)) != EVX_OK) return st;
   }
   TimedLauncher l = launcher(p, s);
-  sched_advance_record(l, p->g, p->t, p->S, p->W, coef_of(q), nsteps, p->remap, zmode_of(q),
+  sched_advance_record(l, p->g, p->t, p->S, p->W, coef_of(p, q), nsteps, p->remap, zmode_of(q),
                        traj);
   st = finish(l, "advance_record");
   if (st == EVX_OK && q->check_finite) st = check_state_finite(p, p->W, s);
@@ -595,7 +603,7 @@ evx_status evx_ch_step_noalloc(evx_plan* p, float* c, int nsteps, const evx_ch_p
   HipLauncher l;  // no pass timing: its events would be created on demand
   l.stream = static_cast<hipStream_t>(s);
   sched_begin(l, p->g, p->t, c, S, W, p->remap);
-  sched_advance(l, p->g, p->t, S, W, coef_of(q), nsteps, p->remap, zmode_of(q));
+  sched_advance(l, p->g, p->t, S, W, coef_of(p, q), nsteps, p->remap, zmode_of(q));
   if (l.bad_len) return fail(EVX_ERR_SIZE, "step_noalloc: transform length has no kernel");
   if (l.err != hipSuccess) return hip_fail(l.err, "step_noalloc");
   if (q->check_finite && (st = check_state_finite(p, W, s)) != EVX_OK) return st;
@@ -616,7 +624,7 @@ evx_status evx_ch_adjoint_step(evx_plan* p, const float* c_n, float* lam,
     return fail(EVX_ERR_UNSUPPORTED, "adjoint step: no vertex-centred axes");
   if (!p->has_adj)
     return fail(EVX_ERR_NOMEM, "workspace too small for the adjoint (EVX_OP_ADJOINT)");
-  AdjointCoef co{coef_of(q), float(q->dt), float(q->dt * q->kappa)};
+  const AdjointCoef co = adjoint_coef(p, q);
   TimedLauncher l = launcher(p, s);
   sched_adjoint(l, p->g, p->t, c_n, lam, p->aux, co, dkappa, dM, p->remap);
   return finish(l, "adjoint step");
@@ -635,7 +643,7 @@ evx_status evx_ch_adjoint_sweep(evx_plan* p, const float* states, int nsteps, fl
     return fail(EVX_ERR_UNSUPPORTED, "adjoint sweep: no vertex-centred axes");
   if (!p->has_adj)
     return fail(EVX_ERR_NOMEM, "workspace too small for the adjoint (EVX_OP_ADJOINT)");
-  const AdjointCoef co{coef_of(q), float(q->dt), float(q->dt * q->kappa)};
+  const AdjointCoef co = adjoint_coef(p, q);
   TimedLauncher l = launcher(p, s);
   for (int n = nsteps - 1; n >= 0; --n)
     sched_adjoint(l, p->g, p->t, states + size_t(n) * size_t(p->g.V), lam, p->aux, co, dkappa,
@@ -673,7 +681,7 @@ evx_status evx_rd_step(evx_plan* p, float* c, int nsteps, const evx_rd_params* q
                 "reaction-diffusion on Dirichlet axes needs an odd reaction (a0 = a2 = 0)");
   if (!p->S) return fail(EVX_ERR_NOMEM, "no workspace set");
   // the z pass's Allen-Cahn update with M = 1, kappa = D; the x pass evaluates -f
-  const StepCoef co{float(q->A * q->dt), float(q->dt * q->D), float(q->dt)};
+  const StepCoef co = implicit_coef(p->g, q->A * q->dt, q->dt * q->D, q->dt, true);
   const float poly[4] = {float(-q->a0), float(-q->a1), float(-q->a2), float(-q->a3)};
   TimedLauncher l = launcher(p, s);
   sched_begin(l, p->g, p->t, c, p->S, p->W, p->remap);

@@ -93,9 +93,9 @@ EVX_DEV void spec_body(const SpecArgs& a, int tid, int bid, int nblk, double* re
       }
       continue;
     }
-    adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[0], w[0], Cv.x, Fv.x, Lv.x, s0,
+    adjoint_bin(1.0f, a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[0], w[0], Cv.x, Fv.x, Lv.x, s0,
                 s1);
-    adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[1], w[1], Cv.y, Fv.y, Lv.y, s0,
+    adjoint_bin(1.0f, a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[1], w[1], Cv.y, Fv.y, Lv.y, s0,
                 s1);
     a.L[i] = Lv;
     a.F[i] = Fv;

@@ -142,6 +142,7 @@ struct ColArgs {
   float a_dt;              // A dt
   float dt_m_kappa;        // dt M kappa
   float dt_m;              // dt M
+  float one;               // 1, or the power of two that a_dt, dt_m_kappa and dt_m carry (coef_scale)
   int remap;               // XCD-aware block order
   int xcomplex;            // z pass: a column is one complex x bin (else two real x bins)
   int mean;                // COL_Z_VM: MEAN_* (the buffer's mean travels beside it, see spec_mean)
@@ -440,11 +441,12 @@ EVX_DEV double dct_weight(int k, int n) { return (k == 0 ? 0.25 : 0.5) / double(
 //   - dt K2 G F)),  l <- G P Lam,  f <- dt M K2 G Lam.
 // (Re(conj(L) X) = L.x X.x + L.y X.y, both components with the same weight; under a cosine x they
 // are two independent real coefficients.)
-EVX_DEV void adjoint_bin(float a_dt, float dt_m_kappa, float dt_m, float dt, float dt_kappa, float k2,
-                         double w, float c, float& f, float& l, double& s0, double& s1) {
+EVX_DEV void adjoint_bin(float one, float a_dt, float dt_m_kappa, float dt_m, float dt,
+                         float dt_kappa, float k2, double w, float c, float& f, float& l, double& s0,
+                         double& s1) {
   const float k4 = k2 * k2;
-  const float P = 1.0f + a_dt * k2;
-  const float G = evx_rcp(1.0f + dt_m_kappa * k4 + a_dt * k2);
+  const float P = one + a_dt * k2;
+  const float G = evx_rcp(one + dt_m_kappa * k4 + a_dt * k2);
   const float c1 = G * (P * c - dt_m * k2 * f);
   s0 += w * double(-dt_m * k4 * G) * double(l) * double(c1);
   s1 += w * (double(-dt_kappa * k4 * G) * double(l) * double(c1) +
@@ -588,7 +590,7 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     // about ten VALU instructions, and two of them a point were a fifth of this pass's.
     evx_sync();  // K2 table visible
     auto mult = [&](float K2) {
-      return a.dt_m * evx_rcp(1.0f + a.a_dt * K2 + a.dt_m_kappa * K2 * K2);
+      return a.dt_m * evx_rcp(a.one + a.a_dt * K2 + a.dt_m_kappa * K2 * K2);
     };
     if constexpr (MODE == COL_Z_GS) {
       float2 cs[E];
@@ -603,9 +605,10 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
       static_for<E>([&](auto e) {
         const float kr = k2l[t + TPS * decltype(e)::value];
         const float Ka = kca + kr, Kb = kcb + kr;
-        const float ga = evx_rcp(1.0f + a.a_dt * Ka + a.dt_m_kappa * Ka * Ka);
-        const float gb = evx_rcp(1.0f + a.a_dt * Kb + a.dt_m_kappa * Kb * Kb);
-        x[e] = make_float2((cs[e].x + a.dt_m * x[e].x) * ga, (cs[e].y + a.dt_m * x[e].y) * gb);
+        const float ga = evx_rcp(a.one + a.a_dt * Ka + a.dt_m_kappa * Ka * Ka);
+        const float gb = evx_rcp(a.one + a.a_dt * Kb + a.dt_m_kappa * Kb * Kb);
+        x[e] = make_float2((a.one * cs[e].x + a.dt_m * x[e].x) * ga,
+                           (a.one * cs[e].y + a.dt_m * x[e].y) * gb);
       });
       // a vertex-centred axis reads each state row twice, once as its mirror, which another lane owns:
       // every lane has its states before any lane stores new ones
@@ -657,14 +660,14 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
                     a.dt_m_kappa * K2 * K2};
       } else if constexpr (MODE == COL_Z_AC) {
         // Allen-Cahn: C' = G (P C - dt M F), P = 1 + A dt, G = 1 / (1 + A dt + dt M kappa K2)
-        const float P = 1.0f + a.a_dt;
+        const float P = a.one + a.a_dt;
         return Coef{evx_rcp(P + a.dt_m_kappa * K2), P, a.dt_m};
       } else if constexpr (MODE == COL_Z_AC_ETD) {
         // Allen-Cahn ETD1: C' = C + phi1(dt S) dt R, dt S = -(dt M kappa K2 + A dt),
         // dt R = -(dt M F + dt M kappa K2 C)
         return Coef{evx_phi1(-(a.dt_m_kappa * K2 + a.a_dt)), a.dt_m, a.dt_m_kappa * K2};
       } else {
-        return Coef{evx_rcp(1.0f + a.dt_m_kappa * K2 * K2 + a.a_dt * K2), 1.0f + a.a_dt * K2,
+        return Coef{evx_rcp(a.one + a.dt_m_kappa * K2 * K2 + a.a_dt * K2), a.one + a.a_dt * K2,
                     a.dt_m * K2};
       }
     };
@@ -770,10 +773,10 @@ EVX_DEV void colspec_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     double w = 1.0;
     if constexpr (decltype(e)::value == 0) w = cosz && t == 0 ? 0.5 : 1.0;
     if constexpr (adj) {
-      adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, q.dt, q.dt_kappa, ka, w, c[e].x, f[e].x, l[e].x,
-                  sa[0], sa[1]);
-      adjoint_bin(a.a_dt, a.dt_m_kappa, a.dt_m, q.dt, q.dt_kappa, kb, w, c[e].y, f[e].y, l[e].y,
-                  sb[0], sb[1]);
+      adjoint_bin(a.one, a.a_dt, a.dt_m_kappa, a.dt_m, q.dt, q.dt_kappa, ka, w, c[e].x, f[e].x,
+                  l[e].x, sa[0], sa[1]);
+      adjoint_bin(a.one, a.a_dt, a.dt_m_kappa, a.dt_m, q.dt, q.dt_kappa, kb, w, c[e].y, f[e].y,
+                  l[e].y, sb[0], sb[1]);
       // one bin's FP64 terms at a time: left to the end of the pass they hold 100 registers more
       evx_here(sa[0], sa[1], sb[0], sb[1]);
     } else {

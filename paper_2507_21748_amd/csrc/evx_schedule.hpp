@@ -207,9 +207,33 @@ struct TablePtrs {
   const float *k2_x, *k2_y, *k2_z;
 };
 
+// Coefficients of the z pass's update.  `one` stands for the 1 of its denominator 1 + dt M kappa K2^2 +
+// A dt K2 (Cahn-Hilliard; the other forms likewise): all four may carry a common power of two, which
+// cancels in numerator and denominator (coef_scale).
 struct StepCoef {
   float a_dt, dt_m_kappa, dt_m;
+  float one = 1.0f;
 };
+
+// An upper bound on any bin's K2.
+inline double k2_bound(const Geom& g) { return 3.0 * (M_PI / g.dx) * (M_PI / g.dx); }
+
+// The power of two that brings a denominator of at most `bound` into the range of evx_rcp: 1 up to
+// 2^120, so that only steps far beyond any use of the model scale at all.
+inline float coef_scale(double bound) {
+  if (!(bound > 0x1p120)) return 1.0f;
+  int e = 0;
+  (void)std::frexp(bound < 0x1p220 ? bound : 0x1p220, &e);  // bound <= 2^e
+  return float(std::ldexp(1.0, e > 220 ? -100 : 120 - e));
+}
+
+// The semi-implicit update's coefficients (ac: the Allen-Cahn form, whose stabilisation multiplies dt
+// alone), scaled where they have to be.
+inline StepCoef implicit_coef(const Geom& g, double a_dt, double dt_m_kappa, double dt_m, bool ac) {
+  const double K = k2_bound(g);
+  const float s = coef_scale(ac ? 1.0 + a_dt + dt_m_kappa * K : 1.0 + dt_m_kappa * K * K + a_dt * K);
+  return StepCoef{float(a_dt * s), float(dt_m_kappa * s), float(dt_m * s), s};
+}
 
 inline SpecGeom spec_geom(const Geom& g) {
   return SpecGeom{(long long)g.nz * g.ypitch * 8, (long long)g.ypitch * 8, g.ny};
@@ -259,6 +283,7 @@ inline ColArgs z_args(const Geom& g, const TablePtrs& t, const float2* in, float
   a.a_dt = c.a_dt;
   a.dt_m_kappa = c.dt_m_kappa;
   a.dt_m = c.dt_m;
+  a.one = c.one;
   a.remap = remap;
   a.xcomplex = (g.bc == BC_PERIODIC || g.xcplx) ? 1 : 0;
   return a;

@@ -19,7 +19,7 @@ struct AdjointBufs {
   float2 *A, *B, *Lm;  // spectral scratch
   float* v;            // real scratch
   double* partial;     // 2 * AUX_BLOCKS
-  float* v2;           // second real scratch (two-species model)
+  float* v2;           // second real scratch (variable mobility's right-hand side)
 };
 
 struct AdjointCoef {
@@ -166,9 +166,9 @@ void sched_gray_scott(L& l, const Geom& g, const TablePtrs& t, float* u, float* 
 
 // Variable-mobility Cahn-Hilliard in the paper's increment form (appendix "Semi-implicit
 // timestepping"): phi <- phi + T^{-1}[dt / (1 + c4 K2^2) T[div(M grad mu)]], the right-hand side
-// from the two stencil passes; the multiplier sits between the forward and inverse z transforms
-// of one column pass, and the inverse x pass adds the increment to phi.  Scratch: v (mu), v2 (the
-// right-hand side), A.
+// from the stencil pass; the multiplier sits between the forward and inverse z transforms
+// of one column pass, and the inverse x pass adds the increment to phi.  Scratch: v2 (the right-hand
+// side), A.
 struct VmCoef {
   float dt, c4, c_g, c_lap, c_flux;
 };

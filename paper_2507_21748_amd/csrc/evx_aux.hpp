@@ -21,20 +21,6 @@ constexpr int AUX_THREADS = 256;
 #endif
 constexpr int AUX_BLOCKS = EVX_AUX_BLOCKS;
 
-struct SpecArgs {
-  const float2* C;  // T[c^n]
-  float2* F;        // in: T[f'(c^n)];  out: dt M K2 G Lam   (the B operator's multiplier)
-  float2* L;        // in: T[lam^{n+1}]; out: G P Lam        (the A operator's multiplier)
-  long long n;      // float2 elements of a spectral buffer
-  int nx, ny, nz, ypitch, ncols, bc;  // grouped spectral layout; ncols x columns hold data
-  int xcplx;                          // cosine x with one complex column per bin
-  int bcy, bcz;                      // y and z transform families (x periodic may mix them)
-  const float *k2x, *k2y, *k2z;
-  float a_dt, dt_m_kappa, dt_m, dt, dt_kappa;
-  double* partial;  // 2 per block: sum for dL/dkappa, sum for dL/dM (before the 1/V factor)
-  int mode;         // 0 adjoint, 1 energy (sum w K2 |C|^2 into partial[2b])
-};
-
 template <int T>
 EVX_DEV void block_sum2(double& s0, double& s1, int tid, double* red) {
   red[2 * tid] = s0;
@@ -49,62 +35,6 @@ EVX_DEV void block_sum2(double& s0, double& s1, int tid, double* red) {
   }
   s0 = red[0];
   s1 = red[1];
-}
-
-// The spectral work of colspec_body on whole spectra (adjoint, mode 0, or energy, mode 1); the host
-// emulator's launcher still offers it.
-EVX_DEV void spec_body(const SpecArgs& a, int tid, int bid, int nblk, double* red) {
-  double s0 = 0.0, s1 = 0.0;
-  const long long stride = (long long)nblk * AUX_THREADS;
-  for (long long i = (long long)bid * AUX_THREADS + tid; i < a.n; i += stride) {
-    const SpecPos sp = spec_pos(i, a.ny, a.ypitch, a.nz, a.ncols);
-    if (!sp.live) continue;  // pad row or dead column
-    const int xc = sp.x, y = sp.y, z = sp.z;
-    const float kyz = a.k2y[y] + a.k2z[z];
-    const float2 Cv = a.C[i];
-    float2 Fv = make_float2(0.f, 0.f), Lv = make_float2(0.f, 0.f);
-    if (a.mode == 0) {
-      Fv = a.F[i];
-      Lv = a.L[i];
-    }
-    float K2[2];
-    double w[2];
-    if (a.bc == BC_PERIODIC || a.xcplx) {
-      K2[0] = K2[1] = a.k2x[xc] + kyz;
-      // half spectrum along x (or a cosine x bin as a complex column); a cosine axis weighs its
-      // bins n w_k relative to a periodic one (the 1/V normalisation is applied to the sums)
-      const double wx = a.xcplx ? (xc == 0 ? 0.25 : 0.5)
-                                : ((xc == 0 || 2 * xc == a.nx) ? 1.0 : 2.0);
-      const double fy = a.bcy == BC_PERIODIC ? 1.0 : (y == 0 ? 0.25 : 0.5);
-      const double fz = a.bcz == BC_PERIODIC ? 1.0 : (z == 0 ? 0.25 : 0.5);
-      w[0] = w[1] = wx * fy * fz;
-    } else {
-      K2[0] = a.k2x[2 * xc] + kyz;
-      K2[1] = a.k2x[2 * xc + 1] + kyz;
-      const double wyz = dct_weight(y, a.ny) * dct_weight(z, a.nz);
-      w[0] = dct_weight(2 * xc, a.nx) * wyz;
-      w[1] = dct_weight(2 * xc + 1, a.nx) * wyz;
-    }
-    if (a.mode == 1) {
-      if (a.bc == BC_PERIODIC || a.xcplx) {
-        s0 += w[0] * double(K2[0]) * (double(Cv.x) * Cv.x + double(Cv.y) * Cv.y);
-      } else {
-        s0 += w[0] * double(K2[0]) * double(Cv.x) * Cv.x + w[1] * double(K2[1]) * double(Cv.y) * Cv.y;
-      }
-      continue;
-    }
-    adjoint_bin(1.0f, a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[0], w[0], Cv.x, Fv.x, Lv.x, s0,
-                s1);
-    adjoint_bin(1.0f, a.a_dt, a.dt_m_kappa, a.dt_m, a.dt, a.dt_kappa, K2[1], w[1], Cv.y, Fv.y, Lv.y, s0,
-                s1);
-    a.L[i] = Lv;
-    a.F[i] = Fv;
-  }
-  block_sum2<AUX_THREADS>(s0, s1, tid, red);
-  if (tid == 0) {
-    a.partial[2 * bid] = s0;
-    a.partial[2 * bid + 1] = s1;
-  }
 }
 
 // Real-space sums.  Diagnostics (b == null): partial[2b] = sum f(c), partial[2b+1] = sum c.
@@ -209,66 +139,6 @@ EVX_DEV void finite_body(const FiniteArgs& a, int tid, int bid, int nblk, int* r
     evx_sync();
   }
   if (tid == 0) a.flag[bid] = red[0];
-}
-
-// The two bodies below are the Gray-Scott step's pieces taken one at a time (its kernels fuse them
-// into the x and z passes); the host emulator's launcher still offers them.
-// Gray-Scott reaction terms in real space (feed F, kill k): ru = -u v^2 + F (1 - u),
-// rv = u v^2 - k v.
-struct GsReactArgs {
-  const float* u;
-  const float* v;
-  float* ru;
-  float* rv;
-  long long n;
-  float F, k;
-};
-
-EVX_DEV void gs_react_body(const GsReactArgs& a, int tid, int bid, int nblk) {
-  const long long stride = (long long)nblk * AUX_THREADS;
-  for (long long i = (long long)bid * AUX_THREADS + tid; i < a.n; i += stride) {
-    const float u = a.u[i], v = a.v[i];
-    const float uv2 = u * v * v;
-    a.ru[i] = -uv2 + a.F * (1.0f - u);
-    a.rv[i] = uv2 - a.k * v;
-  }
-}
-
-// Gray-Scott spectral update of both species (diffusion implicit, reaction explicit):
-// U <- (U + dt RU) / (1 + dt Du K2), V <- (V + dt RV) / (1 + dt Dv K2), in the layout of the
-// spectral buffers (periodic x: complex half-spectrum rows; cosine x: two real bins per float2).
-struct GsUpdateArgs {
-  float2* U;
-  float2* V;
-  const float2* RU;
-  const float2* RV;
-  long long n;
-  int ny, ypitch, nz, ncols, bc;
-  int xcplx;  // cosine x with one complex column per bin
-  const float *k2x, *k2y, *k2z;
-  float dt, dt_du, dt_dv;
-};
-
-EVX_DEV void gs_update_body(const GsUpdateArgs& a, int tid, int bid, int nblk) {
-  const long long stride = (long long)nblk * AUX_THREADS;
-  for (long long i = (long long)bid * AUX_THREADS + tid; i < a.n; i += stride) {
-    const SpecPos sp = spec_pos(i, a.ny, a.ypitch, a.nz, a.ncols);
-    if (!sp.live) continue;  // pad row or dead column
-    const int xc = sp.x;
-    const float kyz = a.k2y[sp.y] + a.k2z[sp.z];
-    float ka, kb;
-    if (a.bc == BC_PERIODIC || a.xcplx) {
-      ka = kb = a.k2x[xc] + kyz;
-    } else {
-      ka = a.k2x[2 * xc] + kyz;
-      kb = a.k2x[2 * xc + 1] + kyz;
-    }
-    const float2 U = a.U[i], V = a.V[i], RU = a.RU[i], RV = a.RV[i];
-    a.U[i] = make_float2((U.x + a.dt * RU.x) / (1.0f + a.dt_du * ka),
-                         (U.y + a.dt * RU.y) / (1.0f + a.dt_du * kb));
-    a.V[i] = make_float2((V.x + a.dt * RV.x) / (1.0f + a.dt_dv * ka),
-                         (V.y + a.dt * RV.y) / (1.0f + a.dt_dv * kb));
-  }
 }
 
 // Variable-mobility Cahn-Hilliard (paper, appendix "Phase transformations of first and second

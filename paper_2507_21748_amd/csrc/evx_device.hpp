@@ -27,8 +27,6 @@ namespace evx_emu {
 extern thread_local std::barrier<>* block_barrier;
 }
 inline void evx_sync() { evx_emu::block_barrier->arrive_and_wait(); }
-// A value the caller knows to be the same in every lane of a wave (kept in scalar registers).
-inline int evx_wave_uniform(int v) { return v; }
 inline float evx_rcp(float x) { return 1.0f / x; }
 constexpr bool kEmulated = true;
 inline void evx_here(double&, double&, double&, double&) {}
@@ -81,8 +79,6 @@ inline void evx_buf_store1(evx_buf r, unsigned off, float v) {
 #define EVX_RESTRICT __restrict__
 
 __device__ __forceinline__ void evx_sync() { __syncthreads(); }
-// A value the caller knows to be the same in every lane of a wave (kept in scalar registers).
-__device__ __forceinline__ int evx_wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 // 1 / x for 2^-100 <= x <= 2^120: the hardware estimate and one Newton step with fused multiply-adds,
 // five instructions instead of an IEEE division's ten.  An estimate within 1 ulp would not promise the
 // division's bits for every x; those of gfx950 give them, which tests/test_gpu_reciprocal.py holds for

@@ -61,15 +61,10 @@ EVX_HD SpecPos spec_pos(long long i, int ny, int ypitch, int nz, int ncols) {
   return p;
 }
 
-// Float2 offset of row r = z ny + y (x group 0, column 0).
-EVX_HD long long spec_row_offset(const SpecGeom& s, long long r) {
-  const long long z = r / s.ny;
-  return z * s.zstride + (r - z * s.ny) * 8;
-}
-
-// The same for row (z0, y0) + j (0 <= y0 < ny, j >= 0, y0 + j < 2^31), without a branch: an
-// unsigned division.  (A carry loop would be a divergent region, into which the compiler sinks the
-// loads that use the offset, each then waited for before the region ends.)
+// Float2 offset (x group 0, column 0) of the row j rows past (z0, y0) (0 <= y0 < ny, j >= 0,
+// y0 + j < 2^31), without a branch: an unsigned division.  (A carry loop would be a divergent region,
+// into which the compiler sinks the loads that use the offset, each then waited for before the region
+// ends.)
 EVX_HD long long spec_row_offset_from(const SpecGeom& s, long long z0, int y0, int j) {
   const unsigned y = unsigned(y0 + j), ny = unsigned(s.ny);
   const unsigned dz = y / ny;
@@ -96,10 +91,9 @@ enum : int {
   ROW_FUSED = 0,  // complex row -> inverse x -> f' -> forward x -> complex row
   ROW_FWD = 1,    // real row -> forward x -> complex row
   ROW_INV = 2,    // complex row -> inverse x -> real row
-  ROW_FWD_FP = 3, // ROW_FWD of f'(c) (the kernels take RowArgs::fp, the emulator offers the mode)
-  ROW_FUSED_REC = 4, // ROW_FUSED that also stores the real row it passes through (out_r)
-  ROW_INV_ADD = 5,   // ROW_INV that adds the real row to out_r instead of storing it
-  ROW_FUSED_POLY = 6 // ROW_FUSED with the cubic poly(c) of RowArgs in place of f'(c)
+  ROW_FUSED_REC = 3, // ROW_FUSED that also stores the real row it passes through (out_r)
+  ROW_INV_ADD = 4,   // ROW_INV that adds the real row to out_r instead of storing it
+  ROW_FUSED_POLY = 5 // ROW_FUSED with the cubic poly(c) of RowArgs in place of f'(c)
 };
 
 // What a forward z pass does with the finished spectrum of its columns instead of storing it
@@ -265,9 +259,6 @@ EVX_DEV float2 load_or_zero(const float2* EVX_RESTRICT src, long long i, bool ok
   const float2 v = src[ok ? i : 0];
   const unsigned m = ok ? ~0u : 0u;
   return make_float2(evx_keep(v.x, m), evx_keep(v.y, m));
-}
-EVX_DEV float load_or_zero(const float* EVX_RESTRICT src, long long i, bool ok) {
-  return evx_keep(src[ok ? i : 0], ok ? ~0u : 0u);
 }
 
 // A block's copy of a small constant table (COUNT entries) staged in LDS: every lane issues its
@@ -1245,7 +1236,7 @@ template <int NH, int MODE, bool GS>
 EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   using C = RowCfg<NH, BC_ZERO_FLUX>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
-  constexpr bool real_in = MODE == ROW_FWD || MODE == ROW_FWD_FP;
+  constexpr bool real_in = MODE == ROW_FWD;
   constexpr bool real_out =
       MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC;
   constexpr bool add = MODE == ROW_INV_ADD;
@@ -1342,7 +1333,7 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
     });
     evx_sync();
     static_for<E>([&](auto e) { x[e] = prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2]; });
-    if (MODE == ROW_FWD_FP || (!GS && a.fp))
+    if (!GS && a.fp)
       static_for<E>([&](auto e) { x[e] = row_nonlin<ROW_FUSED, false>(1.0f, nullptr, x[e]); });
     evx_sync();
     if constexpr (GS) react(1.0f);
@@ -1484,7 +1475,7 @@ template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* lds) {
   using C = RowCfg<NH, BC>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
-  constexpr bool real_in = MODE == ROW_FWD || MODE == ROW_FWD_FP;
+  constexpr bool real_in = MODE == ROW_FWD;
   constexpr bool real_out =
       MODE == ROW_INV || MODE == ROW_INV_ADD || MODE == ROW_FUSED_REC;
   constexpr bool add = MODE == ROW_INV_ADD;
@@ -1526,7 +1517,7 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     if constexpr (real_in) {
       real_row_in<NH, B>(a, a.in_r, r0, tid, tables, lds, x);
       static_for<E>([&](auto e) {  // with the halves r2c_post leaves out
-        if (MODE == ROW_FWD_FP || a.fp) {
+        if (a.fp) {
           x[e] = row_nonlin<ROW_FUSED, true>(1.0f, nullptr, x[e]);
         } else {
           x[e] = cscale(x[e], 0.5f);

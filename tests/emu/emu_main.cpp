@@ -102,7 +102,6 @@ struct EmuLauncher {
     switch (mode) {
       case ROW_FUSED: row_t<NH, BC, ROW_FUSED>(a); break;
       case ROW_FWD: row_t<NH, BC, ROW_FWD>(a); break;
-      case ROW_FWD_FP: row_t<NH, BC, ROW_FWD_FP>(a); break;
       case ROW_INV_ADD: row_t<NH, BC, ROW_INV_ADD>(a); break;
       case ROW_FUSED_REC: row_t<NH, BC, ROW_FUSED_REC>(a); break;
       case ROW_FUSED_POLY: row_t<NH, BC, ROW_FUSED_POLY>(a); break;
@@ -136,11 +135,6 @@ struct EmuLauncher {
       row(n, bc, mode, b);
     }
   }
-  void spec(const SpecArgs& a) {
-    run_grid(AUX_BLOCKS, AUX_THREADS, 2 * AUX_THREADS, [&](int tid, int bid, int nb, float2* lds) {
-      spec_body(a, tid, bid, nb, reinterpret_cast<double*>(lds));
-    });
-  }
   void realsum(const RealSumArgs& a) {
     run_grid(AUX_BLOCKS, AUX_THREADS, 2 * AUX_THREADS, [&](int tid, int bid, int nb, float2* lds) {
       realsum_body(a, tid, bid, nb, reinterpret_cast<double*>(lds));
@@ -154,16 +148,6 @@ struct EmuLauncher {
   void combine(const CombineArgs& a) {
     run_grid(AUX_BLOCKS, AUX_THREADS, 1, [&](int tid, int bid, int nb, float2*) {
       combine_body(a, tid, bid, nb);
-    });
-  }
-  void gs_react(const GsReactArgs& a) {
-    run_grid(AUX_BLOCKS, AUX_THREADS, 1, [&](int tid, int bid, int nb, float2*) {
-      gs_react_body(a, tid, bid, nb);
-    });
-  }
-  void gs_update(const GsUpdateArgs& a) {
-    run_grid(AUX_BLOCKS, AUX_THREADS, 1, [&](int tid, int bid, int nb, float2*) {
-      gs_update_body(a, tid, bid, nb);
     });
   }
   void vm_fused(const VmStencilArgs& a) {

@@ -10,12 +10,13 @@
 
 namespace evx {
 
-// Workgroups of 512 lanes (length 1024) fit a compute unit twice only below 129 VGPRs, four waves a
-// SIMD; the compiler is held to that (at most five registers spill, in the rarer forms), since one
-// workgroup alone waits for its own loads.
+// Workgroups of 8192 points (length 1024: 512 lanes of 16) fit a compute unit twice only below 129
+// VGPRs, four waves a SIMD; the compiler is held to that (at most five registers spill, in the rarer
+// forms), since one workgroup alone waits for its own loads.  Length 512 (512 lanes of 8 points) is
+// left alone: held to it, a 512 x 256 x 256 zero-flux step took 230.2 us, without 228.2.
 template <int N>
 constexpr int col_min_waves() {
-  return ColCfg<N>::THREADS >= 512 ? 4 : 1;
+  return ColCfg<N>::B * N >= 8192 ? 4 : 1;
 }
 
 template <int N, int BC, int MODE>

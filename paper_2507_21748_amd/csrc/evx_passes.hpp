@@ -637,9 +637,10 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
       cs[e] = evx_buf_load2(ct.sres(a.state, e), ct.so);
     });
     // one bin: C' from C, F and its K2.  The coefficients of a complex bin's two components are the
-    // same and evaluated once: in the periodic family, where pair columns are the exception, and
-    // below length 1024, whose 512 lanes have no registers left for it (and wait for memory).
-    constexpr bool share = !zf && C::THREADS < 512;
+    // same and evaluated once: in the periodic family, where pair columns are the exception, and in
+    // workgroups below 8192 points (512^3 step 1099.5 -> 1096.6 us).  Length 1024 has that many, 16 a
+    // lane on 512 lanes, and no registers left for it (and waits for memory).
+    constexpr bool share = !zf && B * N < 8192;
     struct Coef {
       float p, q, r;
     };

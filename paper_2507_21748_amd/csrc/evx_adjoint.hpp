@@ -142,14 +142,16 @@ void sched_gray_scott(L& l, const Geom& g, const TablePtrs& t, float* u, float* 
     upd.state[1] = W;
     xa.rate = 1;
     const PassBatch rows{{u, v}, {b.Lm, W}, 2}, st{{b.Lm, W}, {b.Lm, W}, 2};
-    const PassBatch out{{b.Lm, W}, {b.A, b.B}, 2};
+    const PassBatch all{{b.A, b.B, b.Lm, W}, {b.A, b.B, b.Lm, W}, 4};
+    // the first step takes its reactions from the real fields, beside the states' own transforms
     l.row_batch(g.row_len, g.bc, ROW_FWD, x_args(g, t, nullptr, u, b.Lm, nullptr), rows);
-    l.col_batch(g.fy, g.bcy, COL_FWD, ya, st);
+    l.row(g.row_len, g.bc, ROW_FWD, xa);
+    l.col_batch(g.fy, g.bcy, COL_FWD, ya, all);
     l.col_batch(g.fz, g.bcz, COL_FWD, za, st);
-    l.col_batch(g.fz, g.bcz, COL_INV, za, out);
+    l.col_batch(g.fz, g.bcz, COL_Z_VM, za, upd);
   }
-  for (int n = 0; n < nsteps; ++n) {
-    const bool spectral = states || n > 0;  // the species' form on entry
+  for (int n = states ? 1 : 0; n < nsteps; ++n) {
+    const bool spectral = n > 0;  // the species' form on entry
     if (spectral) l.col_batch(g.fy, g.bcy, COL_INV, ya, two);
     if (!states) {
       xa.mean = n > 0 ? MEAN_IN : 0;

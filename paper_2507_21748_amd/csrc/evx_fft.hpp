@@ -272,6 +272,15 @@ constexpr int seqs_per_block() {
   return b;
 }
 
+// The same for grids so large that filling the chip is no concern (col_wide), where the lengths below
+// lose by their small workgroups: 64 and 128, whose 8 sequences move half lines, take 16, and 50 and
+// 100, whose 16 sequences of five lanes leave three eighths of two waves idle, 32 (160 of 192 lanes).
+template <int N>
+constexpr int wide_seqs() {
+  constexpr int tps = FftPlan<N>::TPS, b = seqs_per_block<N>();
+  return N <= 128 && (b == 8 || (tps & (tps - 1)) != 0) ? 2 * b : b;
+}
+
 // Columns per tile of the stored spectral state: the sequences of a 256-thread workgroup (of one
 // lane a sequence at length 16).  It is a format (a caller may keep a state in a file and resume
 // from it), so it does not follow the workgroup; every workgroup covers part of one tile or all.

@@ -19,10 +19,10 @@ constexpr int col_min_waves() {
   return ColCfg<N>::B * N >= 8192 ? 4 : 1;
 }
 
-template <int N, int BC, int MODE>
-__global__ __launch_bounds__(ColCfg<N>::THREADS, col_min_waves<N>()) void col_kernel(ColArgs a) {
-  __shared__ float2 lds[ColCfg<N>::LDS];
-  colpass_body<N, BC, MODE>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
+template <int N, int BC, int MODE, int SEQS = ColCfg<N>::B>
+__global__ __launch_bounds__((ColCfg<N, SEQS>::THREADS), col_min_waves<N>()) void col_kernel(ColArgs a) {
+  __shared__ float2 lds[ColCfg<N, SEQS>::LDS];
+  colpass_body<N, BC, MODE, SEQS>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
 }
 
 // the same passes over a batch of buffer pairs (grid.y = pair)
@@ -105,6 +105,19 @@ static hipError_t col_go(const ColArgs& a, hipStream_t s) {
   }
   const long long nblk = (a.nseq + C::B - 1) / C::B;
   if (nblk <= 0) return hipSuccess;
+  constexpr int WIDE = wide_seqs<N>();
+  if constexpr (WIDE != C::B) {
+    if (col_wide<N>(a) && a.sp.mode == SP_NONE) {
+      const long long lane_bytes = col_lane_bytes<N, WIDE>(a), nwide = (a.nseq + WIDE - 1) / WIDE;
+      if (nwide > 0x7fffffffLL || a.nseq > 0x7fffffffLL || lane_bytes >= (long long)kDeadLane)
+        return hipErrorInvalidConfiguration;
+      ColArgs b = a;
+      b.lane_bytes = unsigned(lane_bytes);
+      hipLaunchKernelGGL((col_kernel<N, BC, MODE, WIDE>), dim3(unsigned(nwide)),
+                         dim3(ColCfg<N, WIDE>::THREADS), 0, s, b);
+      return hipGetLastError();
+    }
+  }
   // 32-bit sequence numbers and lane byte offsets (ColTile)
   const long long lane_bytes = col_lane_bytes<N>(a);
   if (nblk > 0x7fffffffLL || a.nseq > 0x7fffffffLL || lane_bytes >= (long long)kDeadLane)

@@ -236,11 +236,11 @@ constexpr int makhoul_src(int n) {
 }
 
 // ------------------------------------------------------------------ column pass
-template <int N>
+template <int N, int SEQS = seqs_per_block<N>()>
 struct ColCfg {
   static constexpr int E = FftPlan<N>::E;
   static constexpr int TPS = FftPlan<N>::TPS;
-  static constexpr int B = seqs_per_block<N>();
+  static constexpr int B = SEQS;
   static constexpr int THREADS = B * TPS;
   static constexpr int TW = B * N;             // twiddle table offset (after the exchange area)
   static constexpr int K2 = TW + N;             // z update: K2 along the transform axis (floats)
@@ -338,9 +338,9 @@ constexpr unsigned kDeadLane = 0xfffffff0u;
 
 // Bound on the bytes any lane addresses from a point base; the launchers check that it is below
 // kDeadLane and that sequence numbers fit in 31 bits.
-template <int N>
+template <int N, int B = ColCfg<N>::B>
 inline long long col_lane_bytes(const ColArgs& a) {
-  constexpr int B = ColCfg<N>::B, TPS = ColCfg<N>::TPS;
+  constexpr int TPS = ColCfg<N>::TPS;
   static_assert(B % 8 == 0, "a block covers whole outer indices");
   // outer indices o0 .. o0 + qmax of one block: at most qmax / n_lo + 1 group steps and qmax
   // steps of o_lo (offsets increase with o, see ColArgs)
@@ -349,6 +349,21 @@ inline long long col_lane_bytes(const ColArgs& a) {
   // a point base plus t rows, a Makhoul row shift (< 2 TPS rows), or a vertex axis's data row
   // (< N / 2 + 1 rows) from the point-0 base: N rows cover all of them (N >= 2 TPS)
   return (cmax + (long long)N * a.row_stride + 2) * 8;
+}
+
+// Whether a column pass runs on wide_seqs workgroups.  A z pass of length 64 or 128 from 64 MiB a buffer
+// on (below, the caches merge the half lines): 128 x 512 x 512 periodic 117 -> 86 us, 128 x 1024 x 1024
+// 479 -> 422, 64 x 1024 x 1024 229 -> 187, but 64 x 384 x 384, 38 MiB, 74 -> 76 us a step.  Lengths 50
+// and 100 from 8 MiB on: 100 x 256 x 256 zero flux 32.5 -> 24.9, 100 x 128 x 128 mixed 20.0 -> 18.6, but
+// 100 x 64 x 64 10.7 -> 11.1 and the y pass of 48 x 100 x 96 8.0 -> 8.4.
+constexpr long long kWideHalfLines = kEmulated ? 1 << 16 : 64 << 20;
+constexpr long long kWideIdleLanes = kEmulated ? 1 << 16 : 8 << 20;
+template <int N>
+inline bool col_wide(const ColArgs& a) {
+  if constexpr (wide_seqs<N>() == ColCfg<N>::B) return false;
+  const long long bytes = a.nseq * N * 8;
+  if constexpr (ColCfg<N>::B == 8) return a.row_stride > 8 && bytes >= kWideHalfLines;
+  return bytes >= kWideIdleLanes;
 }
 
 template <int N>
@@ -468,18 +483,18 @@ EVX_DEV void block_sums(double& s0, double& s1, int tid, double* red) {
 template <int N, int BC, int MODE>
 EVX_DEV void colspec_body(const ColArgs& a, int tid, int bid, int nblk, float2* lds);
 
-template <int N, int BC, int MODE>
+template <int N, int BC, int MODE, int SEQS = ColCfg<N>::B>
 EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* lds) {
   if constexpr (kEmulated && MODE == COL_FWD) {  // on the GPU kernels of their own
     if (a.sp.mode == SP_ADJOINT) return colspec_body<N, BC, SP_ADJOINT>(a, tid, bid, nblk, lds);
     if (a.sp.mode == SP_ENERGY) return colspec_body<N, BC, SP_ENERGY>(a, tid, bid, nblk, lds);
   }
-  using C = ColCfg<N>;
+  using C = ColCfg<N, SEQS>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B;
   constexpr bool upd =
       MODE == COL_Z_UPDATE || MODE == COL_Z_ETD || MODE == COL_Z_AC || MODE == COL_Z_AC_ETD;
   if constexpr (kEmulated && MODE == COL_Z_VM) {
-    if (a.state) return colpass_body<N, BC, COL_Z_GS>(a, tid, bid, nblk, lds);  // on the GPU a kernel
+    if (a.state) return colpass_body<N, BC, COL_Z_GS, SEQS>(a, tid, bid, nblk, lds);  // GPU: a kernel
   }
   constexpr bool vm = MODE == COL_Z_VM || MODE == COL_Z_GS;
   constexpr bool kt = upd || vm;  // needs the K2 tables

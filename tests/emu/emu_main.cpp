@@ -62,9 +62,16 @@ static void run_grid(int nblk, int threads, int lds_slots, Body body) {
 struct EmuLauncher {
   template <int N, int BC, int MODE>
   void col_t(const ColArgs& a) {
-    using C = ColCfg<N>;
-    const int nblk = int((a.nseq + C::B - 1) / C::B);
-    const long long lane_bytes = col_lane_bytes<N>(a);
+    if (wide_seqs<N>() != ColCfg<N>::B && col_wide<N>(a) && a.sp.mode == SP_NONE)
+      col_s<N, BC, MODE, wide_seqs<N>()>(a);
+    else
+      col_s<N, BC, MODE, ColCfg<N>::B>(a);
+  }
+  template <int N, int BC, int MODE, int SEQS>
+  void col_s(const ColArgs& a) {
+    using C = ColCfg<N, SEQS>;
+    const int nblk = int((a.nseq + SEQS - 1) / SEQS);
+    const long long lane_bytes = col_lane_bytes<N, SEQS>(a);
     if (lane_bytes >= (long long)kDeadLane) {
       std::fprintf(stderr, "column pass offsets exceed 32 bits\n");
       std::exit(3);
@@ -72,7 +79,7 @@ struct EmuLauncher {
     ColArgs b = a;
     b.lane_bytes = unsigned(lane_bytes);
     run_grid(nblk, C::THREADS, C::LDS, [&](int tid, int bid, int nb, float2* lds) {
-      colpass_body<N, BC, MODE>(b, tid, bid, nb, lds);
+      colpass_body<N, BC, MODE, SEQS>(b, tid, bid, nb, lds);
     });
   }
   template <int NH, int BC, int MODE>

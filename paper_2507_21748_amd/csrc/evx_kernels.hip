@@ -14,9 +14,14 @@ namespace evx {
 // VGPRs, four waves a SIMD; the compiler is held to that (at most five registers spill, in the rarer
 // forms), since one workgroup alone waits for its own loads.  Length 512 (512 lanes of 8 points) is
 // left alone: held to it, a 512 x 256 x 256 zero-flux step took 230.2 us, without 228.2.
+// Lanes of 20 points are held to three waves a SIMD, 168 VGPRs: with the update's coefficients shared
+// (one or two registers more) they fell to two, and the z pass of 100 x 256 x 256 periodic took 29.1 us
+// instead of 23.3, of 320 x 256 x 256 64.1 instead of 57.9.  (Lanes of 12 points held to five waves
+// instead of four spill, 192 x 256 x 256 36 -> 41 us; length 200 held to three 46.8 -> 48.4 at
+// 200 x 256 x 256 Dirichlet: both are left alone.)
 template <int N>
 constexpr int col_min_waves() {
-  return ColCfg<N>::B * N >= 8192 ? 4 : 1;
+  return ColCfg<N>::B * N >= 8192 ? 4 : (ColCfg<N>::E == 20 && N != 200 ? 3 : 1);
 }
 
 template <int N, int BC, int MODE, int SEQS = ColCfg<N>::B>
@@ -91,8 +96,9 @@ static hipError_t plane_go(const PlaneArgs& a, hipStream_t s) {
 }
 
 // the forward z pass that goes on with the spectral work (ColArgs::sp)
+// (two waves a SIMD at least: length 100 zero flux took one register too many for that)
 template <int N, int BC, int MODE>
-__global__ __launch_bounds__(ColCfg<N>::THREADS) void colspec_kernel(ColArgs a) {
+__global__ __launch_bounds__(ColCfg<N>::THREADS, 2) void colspec_kernel(ColArgs a) {
   __shared__ float2 lds[ColCfg<N>::LDS];
   colspec_body<N, BC, MODE>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
 }

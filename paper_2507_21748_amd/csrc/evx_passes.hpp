@@ -654,8 +654,10 @@ EVX_DEV void colpass_body(const ColArgs& a, int tid, int bid, int nblk, float2* 
     // one bin: C' from C, F and its K2.  The coefficients of a complex bin's two components are the
     // same and evaluated once: in the periodic family, where pair columns are the exception, and in
     // workgroups below 8192 points (512^3 step 1099.5 -> 1096.6 us).  Length 1024 has that many, 16 a
-    // lane on 512 lanes, and no registers left for it (and waits for memory).
-    constexpr bool share = !zf && B * N < 8192;
+    // lane on 512 lanes, and no registers left for it (and waits for memory).  Length 384, 12 points
+    // a lane and 8 sequences, falls from six waves a SIMD to four by it and only loses (384 x 128 x 128
+    // z pass 22.2 -> 23.8 us, 384 x 256 x 256 70.9 -> 72.2).
+    constexpr bool share = !zf && B * N < 8192 && !(E == 12 && B == 8);
     struct Coef {
       float p, q, r;
     };

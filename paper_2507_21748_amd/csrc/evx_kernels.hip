@@ -43,10 +43,10 @@ constexpr int row_threads() {
   return RowCfg<NH, BC>::THREADS;
 }
 
-template <int NH, int BC, int MODE>
+template <int NH, int BC, int MODE, bool STAGED = false>
 __global__ __launch_bounds__((row_threads<NH, BC>())) void row_kernel(RowArgs a) {
   __shared__ float2 lds[RowCfg<NH, BC>::LDS];
-  rowpass_body<NH, BC, MODE>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
+  rowpass_body<NH, BC, MODE, STAGED>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
 }
 
 template <int NH, int BC, int MODE>
@@ -166,6 +166,13 @@ static hipError_t row_go(const RowArgs& a, hipStream_t s) {
       if (BC != BC_PERIODIC || a.vx) return hipErrorInvalidValue;
       hipLaunchKernelGGL((row_comb_kernel<NH>), dim3(unsigned(nblk)),
                          dim3(RowCfg<NH, BC_PERIODIC>::THREADS), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (C::SHORT) {
+    if (row_staged<NH, BC>(a)) {
+      hipLaunchKernelGGL((row_kernel<NH, BC, MODE, true>), dim3(unsigned(nblk)), dim3(C::THREADS), 0,
+                         s, a);
       return hipGetLastError();
     }
   }

@@ -900,6 +900,63 @@ EVX_DEV void spec_tail_out(float2* p, const SpecGeom& sg, const SpecLane<TPS>& l
   });
 }
 
+// Spectral rows of a periodic block through LDS, for rows of one, two or four lanes (TPS) on many rows
+// (row_staged): there the lanes' own points are pieces of 8 TPS bytes, which the caches have to put
+// together to lines.  Eight consecutive lanes move the eight columns of a row's group instead, and a
+// wave whole lines; lds holds column k of row b at b S + k.  The transform's mirrored points come from
+// there too, so the way in costs no barrier more than row_c2r's.
+template <int B, int NH, int S, int TPS>
+struct SpecRows {
+  static constexpr int NG = NH / 8 + 1;   // groups of the NH + 1 columns
+  static constexpr int RPL = 8 / TPS;     // rows a lane moves of each group
+  static constexpr int STEP = B / RPL;    // between them
+  static_assert(8 % TPS == 0 && B % RPL == 0 && S > NH, "a lane's rows and columns");
+  const SpecGeom& sg;
+  long long base;      // float2 offset of the z plane of the block's first row (uniform)
+  int row, c;          // the lane's first row and its column within a group
+  unsigned off[RPL];   // lane byte offsets of its rows' column c, or kDeadRow
+  float2 r[NG * RPL];
+  EVX_DEV SpecRows(const SpecGeom& g, long long r0, long long nrows, int tid)
+      : sg(g), row(tid >> 3), c(tid & 7) {
+    const long long z0 = r0 / sg.ny;
+    const int y0 = int(r0 - z0 * sg.ny);
+    base = z0 * sg.zstride;
+    static_for<RPL>([&](auto K) {
+      const int j = row + STEP * decltype(K)::value;
+      off[K] = r0 + j < nrows ? unsigned((spec_row_offset_from(sg, 0, y0, j) + c) * 8) : kDeadRow;
+    });
+  }
+  // f(index, group, byte offset, lds slot, whether the column holds data)
+  template <class F>
+  EVX_DEV void each(F&& f) const {
+    static_for<NG * RPL>([&](auto I) {
+      constexpr int g = decltype(I)::value / RPL, k = decltype(I)::value % RPL;
+      const int col = 8 * g + c;
+      f(I, std::integral_constant<int, g>{}, off[k], (row + STEP * k) * S + col,
+        8 * g + 7 <= NH || col <= NH);
+    });
+  }
+  EVX_DEV void load(const float2* p) {
+    each([&](auto I, auto G, unsigned o, int, bool live) {
+      r[I] = evx_buf_load2(evx_make_buf(p + base + decltype(G)::value * sg.xstride, kRowRange),
+                           live ? o : kDeadRow);
+    });
+  }
+  EVX_DEV void stage(float2* lds) const {
+    each([&](auto I, auto, unsigned, int at, bool live) {
+      if (live) lds[at] = r[I];
+    });
+  }
+  // the staged columns, and zeros in the dead ones of the last group
+  EVX_DEV void store(float2* p, const float2* lds) const {
+    each([&](auto, auto G, unsigned o, int at, bool live) {
+      const float2 v = lds[live ? at : 0];
+      evx_buf_store2(evx_make_buf(p + base + decltype(G)::value * sg.xstride, kRowRange), o,
+                     live ? v : make_float2(0.f, 0.f));
+    });
+  }
+};
+
 // LDS row stride for B rows read by lanes (t, b) at row b, column t + const: the smallest
 // S >= need with S = q (mod 2q), q = 32 / min(B, 32), so that the 32 lanes of a half wave touch
 // distinct 64-bit bank pairs.
@@ -1055,6 +1112,7 @@ struct RowCfg {
   // table; 128^3 and 256^3 1% a step).
   static constexpr bool PL = BC == BC_PERIODIC && TPS >= 8;
   static constexpr int PO = TW + (FftPlan<NH>::S > 1 ? NH : 0);
+  static constexpr bool SHORT = BC == BC_PERIODIC && TPS <= 4;  // rows that SpecRows can move
   static constexpr int NPO = PL ? NH / 2 + 1 : 0;  // exp(-2 pi i (NH - k) / nx) = -conj(entry k)
   static constexpr int LDS = PO + NPO;
 };
@@ -1065,6 +1123,17 @@ template <int NH, int BC>
 inline bool row_fits32(const RowArgs& a) {
   const long long planes = RowCfg<NH, BC>::ROWS / a.sg.ny + 2;
   return (8 * a.sg.xstride + planes * a.sg.zstride + 8) * 8 < (long long)kDeadRow;
+}
+
+// Whether a periodic row pass stages its spectral rows (SpecRows): short rows on grids of many.  Fused
+// pass direct -> staged: 1024 x 1024 x 16 87.6 -> 40.9 us, 512 x 512 x 16 29.5 -> 14.4, 512 x 512 x 40 42.7
+// -> 23.6, 1024 x 1024 x 64 170 -> 135; but 128 x 128 x 16 7.2 -> 7.7, 64 x 64 x 20 6.8 -> 7.7 and, four lanes
+// a row, 256 x 256 x 96 16.8 -> 17.5 (512 x 512 x 96 42.2 either way).
+constexpr long long kStagedRows = kEmulated ? 64 : 32768;
+template <int NH, int BC>
+inline bool row_staged(const RowArgs& a) {
+  using C = RowCfg<NH, BC>;
+  return C::SHORT && !a.gs && !a.comb && a.nrows >= (C::TPS == 4 ? 4 : 1) * kStagedRows;
 }
 
 // Post-processing twiddles exp(-2 pi i k / nx) of a lane's points k = t + TPS e (RowCfg::PL).
@@ -1489,7 +1558,7 @@ EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* ld
 template <int NH>
 EVX_DEV void rowpass_comb_body(const RowArgs& a, int tid, long long r0, float2* lds);
 
-template <int NH, int BC, int MODE>
+template <int NH, int BC, int MODE, bool STAGED = false>
 EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* lds) {
   using C = RowCfg<NH, BC>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
@@ -1528,6 +1597,8 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     const long long row = r0 + b;
     const bool live = row < a.nrows;
     const SpecLane<TPS> ln(a.sg, r0, b, live, t);
+    static_assert(!STAGED || C::SHORT, "rows that are staged are short");
+    using SR = SpecRows<B, NH, C::SROW, C::SHORT ? TPS : 8>;
     using RR = RealRows<B, NH, C::SROW, C::V, T>;
     float2* const rowl = lds + b * C::SROW + t;  // the lane's points of its staged real row
     // vertex-centred x: rows of NH + 1 points, 4 (b (NH + 1) + j) bytes from the block's first
@@ -1542,9 +1613,23 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
         }
       });
     } else {
-      const float2 nyq = spec_row_in<NH>(a.in_c, a.sg, ln, t, x);
-      tables();
-      row_c2r<NH, B>(x, nyq, w, lds, b, t);
+      if constexpr (STAGED) {
+        SR sr(a.sg, r0, a.nrows, tid);
+        sr.load(a.in_c);
+        tables();
+        sr.stage(lds);
+        evx_sync();
+        static_for<E>([&](auto e) {
+          const int k = t + TPS * decltype(e)::value;
+          x[e] = c2r_pre(rowl[TPS * decltype(e)::value], cconj(lds[b * C::SROW + NH - k]),
+                         w.template at<decltype(e)::value>());
+        });
+        evx_sync();
+      } else {
+        const float2 nyq = spec_row_in<NH>(a.in_c, a.sg, ln, t, x);
+        tables();
+        row_c2r<NH, B>(x, nyq, w, lds, b, t);
+      }
       // real rows to add to: in flight during the transform
       RR rr(a.out_r, r0, a.nrows);
       if constexpr (add) {
@@ -1578,7 +1663,15 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     // ---------------------------------------------------------------- forward x (R2C)
     fft_regs<NH, -1, B>(x, lds, b, t, twl);
     const float2 nyq = row_r2c<NH, B>(x, w, lds, b, t);
-    spec_row_out<NH>(a.out_c, a.sg, ln, t, x, nyq);
+    if constexpr (STAGED) {
+      evx_sync();  // the mirrored points are read
+      static_for<E>([&](auto e) { rowl[TPS * decltype(e)::value] = x[e]; });
+      if (t == 0) rowl[NH] = nyq;
+      evx_sync();
+      SR(a.sg, r0, a.nrows, tid).store(a.out_c, lds);
+    } else {
+      spec_row_out<NH>(a.out_c, a.sg, ln, t, x, nyq);
+    }
   } else {
     cos_rows<NH, MODE, false>(a, tid, r0, lds);
   }

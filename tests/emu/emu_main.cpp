@@ -87,6 +87,9 @@ struct EmuLauncher {
     using C = RowCfg<NH, BC>;
     const int nblk = int((a.nrows + C::ROWS - 1) / C::ROWS);
     run_grid(nblk, C::THREADS, C::LDS, [&](int tid, int bid, int nb, float2* lds) {
+      if constexpr (C::SHORT) {
+        if (row_staged<NH, BC>(a)) return rowpass_body<NH, BC, MODE, true>(a, tid, bid, nb, lds);
+      }
       rowpass_body<NH, BC, MODE>(a, tid, bid, nb, lds);
     });
   }

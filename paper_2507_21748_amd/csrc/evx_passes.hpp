@@ -1112,7 +1112,7 @@ struct RowCfg {
   // table; 128^3 and 256^3 1% a step).
   static constexpr bool PL = BC == BC_PERIODIC && TPS >= 8;
   static constexpr int PO = TW + (FftPlan<NH>::S > 1 ? NH : 0);
-  static constexpr bool SHORT = BC == BC_PERIODIC && TPS <= 4;  // rows that SpecRows can move
+  static constexpr bool SHORT = TPS <= 4;  // rows that SpecRows (periodic) or CosRows can move
   static constexpr int NPO = PL ? NH / 2 + 1 : 0;  // exp(-2 pi i (NH - k) / nx) = -conj(entry k)
   static constexpr int LDS = PO + NPO;
 };
@@ -1125,15 +1125,20 @@ inline bool row_fits32(const RowArgs& a) {
   return (8 * a.sg.xstride + planes * a.sg.zstride + 8) * 8 < (long long)kDeadRow;
 }
 
-// Whether a periodic row pass stages its spectral rows (SpecRows): short rows on grids of many.  Fused
+// Whether a row pass stages its spectral rows (SpecRows, CosRows): short rows on grids of many.  Fused
 // pass direct -> staged: 1024 x 1024 x 16 87.6 -> 40.9 us, 512 x 512 x 16 29.5 -> 14.4, 512 x 512 x 40 42.7
 // -> 23.6, 1024 x 1024 x 64 170 -> 135; but 128 x 128 x 16 7.2 -> 7.7, 64 x 64 x 20 6.8 -> 7.7 and, four lanes
 // a row, 256 x 256 x 96 16.8 -> 17.5 (512 x 512 x 96 42.2 either way).
+// Cosine rows keep their bins in LDS anyway and lose by the direct way only with complex columns, of
+// whose 8 bytes it takes 4 (512 x 512 x 20 mixed 44.3 -> 21.9, 1024 x 1024 x 40 177 -> 117), and with pair
+// columns on rows of one lane (1024 x 1024 x 12 zero flux 49.4 -> 29.4); 256 x 256 rows lose by neither.
 constexpr long long kStagedRows = kEmulated ? 64 : 32768;
 template <int NH, int BC>
 inline bool row_staged(const RowArgs& a) {
   using C = RowCfg<NH, BC>;
-  return C::SHORT && !a.gs && !a.comb && a.nrows >= (C::TPS == 4 ? 4 : 1) * kStagedRows;
+  if (!C::SHORT || a.gs || a.comb) return false;
+  if (BC != BC_PERIODIC) return (a.xcplx || C::TPS == 1) && a.nrows >= 4 * kStagedRows;
+  return a.nrows >= (C::TPS == 4 ? 4 : 1) * kStagedRows;
 }
 
 // Post-processing twiddles exp(-2 pi i k / nx) of a lane's points k = t + TPS e (RowCfg::PL).
@@ -1315,11 +1320,66 @@ EVX_DEV void real_row_in(const RowArgs& a, const float* in, long long r0, int ti
   }
 }
 
+// The same for the 2 B cosine rows of a block and COLS columns, pairs of bins or (CPLX) one complex
+// column a bin whose real part counts: bin n of row j is float X::at(n) + j of lds.
+template <int B, int COLS, bool CPLX, int TPS, class X>
+struct CosRows {
+  static constexpr int NG = (COLS + 7) / 8, RPL = 16 / TPS, STEP = 2 * B / RPL;
+  static_assert(16 % TPS == 0 && 2 * B % RPL == 0, "a lane's rows");
+  const SpecGeom& sg;
+  long long base;
+  int row, c, ate, ato;  // ate, ato: float offsets of column c's bins
+  unsigned off[RPL];
+  float2 r[NG * RPL];
+  EVX_DEV CosRows(const SpecGeom& g, long long r0, long long nrows, int tid)
+      : sg(g), row(tid >> 3), c(tid & 7), ate(X::at(CPLX ? c : 2 * c)), ato(X::at(2 * c + 1)) {
+    const long long z0 = r0 / sg.ny;
+    const int y0 = int(r0 - z0 * sg.ny);
+    base = z0 * sg.zstride;
+    static_for<RPL>([&](auto K) {
+      const int j = row + STEP * decltype(K)::value;
+      off[K] = r0 + j < nrows ? unsigned((spec_row_offset_from(sg, 0, y0, j) + c) * 8) : kDeadRow;
+    });
+  }
+  template <class F>
+  EVX_DEV void each(F&& f) const {
+    static_for<NG * RPL>([&](auto I) {
+      constexpr int g = decltype(I)::value / RPL, k = decltype(I)::value % RPL, n0 = (CPLX ? 8 : 16) * g;
+      const int j = row + STEP * k;
+      f(I, std::integral_constant<int, g>{}, off[k], X::template at<n0>(CPLX ? c : 2 * c, ate) + j,
+        X::template at<n0>(2 * c + 1, ato) + j, 8 * g + 7 < COLS || 8 * g + c < COLS);
+    });
+  }
+  EVX_DEV void load(const float2* p) {
+    each([&](auto I, auto G, unsigned o, int, int, bool live) {
+      const evx_buf b = evx_make_buf(p + base + decltype(G)::value * sg.xstride, kRowRange);
+      if constexpr (CPLX)
+        r[I].x = evx_buf_load1(b, live ? o : kDeadRow);
+      else
+        r[I] = evx_buf_load2(b, live ? o : kDeadRow);
+    });
+  }
+  EVX_DEV void stage(float* lds) const {
+    each([&](auto I, auto, unsigned, int e, int o, bool live) {
+      if (!live) return;
+      lds[e] = r[I].x;
+      if constexpr (!CPLX) lds[o] = r[I].y;
+    });
+  }
+  EVX_DEV void store(float2* p, const float* lds) const {
+    each([&](auto, auto G, unsigned off_, int e, int o, bool live) {
+      float2 v = make_float2(0.f, 0.f);
+      if (live) v = make_float2(lds[e], CPLX ? 0.f : lds[o]);
+      evx_buf_store2(evx_make_buf(p + base + decltype(G)::value * sg.xstride, kRowRange), off_, v);
+    });
+  }
+};
+
 // Cosine rows.  GS = false: sequence b packs rows r0 + 2b and r0 + 2b + 1 as a + i b, and lane (t, b)
 // moves bins of rows r0 + b and r0 + B + b (RowXch).  GS = true: sequence b packs row r0 + b of the
 // two species as u + i v.  A spectral column is a pair of real bins (2c, 2c + 1), or with xcplx one
 // complex column per bin.
-template <int NH, int MODE, bool GS>
+template <int NH, int MODE, bool GS, bool STAGED = false>
 EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
   using C = RowCfg<NH, BC_ZERO_FLUX>;
   constexpr int E = C::E, TPS = C::TPS, B = C::B, T = C::THREADS;
@@ -1400,6 +1460,16 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
                x[e].y);
     });
   };
+  static_assert(!STAGED || (C::SHORT && !GS), "rows that are staged are short, of one species");
+  // f(rows) with the block's rows as CosRows
+  auto staged = [&](auto&& f) {
+    if constexpr (STAGED) {
+      if (a.xcplx)
+        f(CosRows<B, NX, true, TPS, X>(a.sg, r0, a.nrows, tid));
+      else
+        f(CosRows<B, NX / 2, false, TPS, X>(a.sg, r0, a.nrows, tid));
+    }
+  };
   float2 pa[H], pb[H];
   if constexpr (real_in) {
     const evx_buf src = evx_make_buf(a.in_r + r0 * NX, kRowRange);
@@ -1425,7 +1495,13 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
     evx_sync();
     if constexpr (GS) react(1.0f);
   } else {
-    if (a.xcplx) {  // complex columns, one per bin (a periodic y or z follows): real parts
+    if constexpr (STAGED) {
+      staged([&](auto rows) {
+        rows.load(a.in_c);
+        tws.store(twl, tid);
+        rows.stage(st);
+      });
+    } else if (a.xcplx) {  // complex columns, one per bin (a periodic y or z follows): real parts
       float qa[E], qb[E];
       spec_points<E>(a.in_c, la, [&](auto e, evx_buf r, unsigned off) {
         qa[e] = evx_buf_load1(r, off);
@@ -1518,6 +1594,10 @@ EVX_DEV void cos_rows(const RowArgs& a, int tid, long long r0, float2* lds) {
     prs[X::template at<TPS * decltype(e)::value>(t, atp) / 2] = x[e];
   });
   evx_sync();
+  if constexpr (STAGED) {
+    staged([&](auto rows) { rows.store(a.out_c, st); });
+    return;
+  }
   if (a.xcplx) {
     spec_points<E>(a.out_c, la, [&](auto e, evx_buf r, unsigned off) {
       evx_buf_store2(r, off, make_float2(rwa[X::template at<TPS * decltype(e)::value>(to, atx)], 0.f));
@@ -1598,7 +1678,7 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
     const bool live = row < a.nrows;
     const SpecLane<TPS> ln(a.sg, r0, b, live, t);
     static_assert(!STAGED || C::SHORT, "rows that are staged are short");
-    using SR = SpecRows<B, NH, C::SROW, C::SHORT ? TPS : 8>;
+    using SR = SpecRows<B, NH, C::SROW, STAGED ? TPS : 8>;
     using RR = RealRows<B, NH, C::SROW, C::V, T>;
     float2* const rowl = lds + b * C::SROW + t;  // the lane's points of its staged real row
     // vertex-centred x: rows of NH + 1 points, 4 (b (NH + 1) + j) bytes from the block's first
@@ -1673,7 +1753,7 @@ EVX_DEV void rowpass_body(const RowArgs& a, int tid, int bid, int nblk, float2* 
       spec_row_out<NH>(a.out_c, a.sg, ln, t, x, nyq);
     }
   } else {
-    cos_rows<NH, MODE, false>(a, tid, r0, lds);
+    cos_rows<NH, MODE, false, STAGED>(a, tid, r0, lds);
   }
 }
 

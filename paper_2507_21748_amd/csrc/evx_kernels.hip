@@ -14,18 +14,19 @@ namespace evx {
 // VGPRs, four waves a SIMD; the compiler is held to that (at most five registers spill, in the rarer
 // forms), since one workgroup alone waits for its own loads.  Length 512 (512 lanes of 8 points) is
 // left alone: held to it, a 512 x 256 x 256 zero-flux step took 230.2 us, without 228.2.
-// Lanes of 20 points are held to three waves a SIMD, 168 VGPRs: with the update's coefficients shared
-// (one or two registers more) they fell to two, and the z pass of 100 x 256 x 256 periodic took 29.1 us
-// instead of 23.3, of 320 x 256 x 256 64.1 instead of 57.9.  (Lanes of 12 points held to five waves
-// instead of four spill, 192 x 256 x 256 36 -> 41 us; length 200 held to three 46.8 -> 48.4 at
-// 200 x 256 x 256 Dirichlet: both are left alone.)
-template <int N>
+// Lanes of 20 points in the periodic family are held to three waves a SIMD, 168 VGPRs: with the update's
+// coefficients shared (one or two registers more) they fell to two, and the z pass of 100 x 256 x 256
+// took 29.1 us instead of 23.3, of 320 x 256 x 256 64.1 instead of 57.9.  (The cosine family, which does
+// not share, spills when it is held: Allen-Cahn steps of 400 x 100 x 400 5% slower.  So do lanes of 12
+// points held to five waves instead of four: 192 x 256 x 256 36 -> 41 us.)
+template <int N, int BC>
 constexpr int col_min_waves() {
-  return ColCfg<N>::B * N >= 8192 ? 4 : (ColCfg<N>::E == 20 && N != 200 ? 3 : 1);
+  if (ColCfg<N>::B * N >= 8192) return 4;
+  return ColCfg<N>::E == 20 && BC == BC_PERIODIC ? 3 : 1;
 }
 
 template <int N, int BC, int MODE, int SEQS = ColCfg<N>::B>
-__global__ __launch_bounds__((ColCfg<N, SEQS>::THREADS), col_min_waves<N>()) void col_kernel(ColArgs a) {
+__global__ __launch_bounds__((ColCfg<N, SEQS>::THREADS), (col_min_waves<N, BC>())) void col_kernel(ColArgs a) {
   __shared__ float2 lds[ColCfg<N, SEQS>::LDS];
   colpass_body<N, BC, MODE, SEQS>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
 }

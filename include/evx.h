@@ -365,7 +365,8 @@ evx_status evx_surrogate_set_params(evx_net* net, const float* params, void* hip
 /* Device bytes of the caller-owned workspace for inference on an nx x ny x nz grid (train = 0,
  * about 130 bytes per voxel) or for training on edge^3 windows (nx = ny = nz = edge), `train` of
  * them at once (per window about 600 bytes per voxel plus up to 59 MB).  A training step accepts any
- * workspace of one window or more and runs as many windows of its batch together as it holds. */
+ * workspace of one window or more and runs as many windows of its batch together as it holds (at
+ * most 1024). */
 evx_status evx_surrogate_workspace_bytes(int nx, int ny, int nz, int train, size_t* bytes);
 /* c_out <- c_in + net(c_in) on a periodic grid.  With EVX_SURROGATE_CONSERVE_MASS in flags the
  * predicted increment's spatial mean is removed (FP64 fixed-order sum), so the prediction

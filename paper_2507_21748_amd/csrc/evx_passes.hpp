@@ -1806,8 +1806,8 @@ EVX_DEV void rowpass_comb_body(const RowArgs& a, int tid, long long r0, float2* 
 // The two-species fused x pass: u and v to real rows, one explicit reaction step, and back (MODE
 // ROW_FUSED_POLY; ROW_FWD starts from real rows) for the B rows from r0.  Periodic rows: a lane
 // holds its points of both species.  Cosine rows: one sequence holds a row of both.
-// Bound by memory traffic and occupancy (96 to 190 VGPRs for both species' points): 61 us at 256^3
-// periodic, 4.4 TB/s.  With a reaction kernel, four fields' forward transforms and an update kernel
+// Bound by memory traffic and occupancy (71 to 235 VGPRs for both species' points, 84 at 256^3, five
+// waves a SIMD): 65 us at 256^3 periodic, 4.2 TB/s.  With a reaction kernel, four fields' forward transforms and an update kernel
 // of its own a step took 0.61 ms at 256^3; with this pass and the multiplier in the z pass 0.19 ms.
 template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* lds) {

@@ -309,8 +309,8 @@ def test_emulated_reaction_diffusion_matches_oracle(asan, shape, bc, scheme):
                                              ((12, 20, 16), ("dirichlet", "zero_flux",
                                                              "periodic"), "spectral")])
 def test_emulated_gray_scott_matches_oracle(asan, shape, bc, scheme):
-    """The Gray-Scott schedule (reaction kernel, batched transforms of four fields, spectral
-    update, batched inverse of two) against the oracle's two-species steps."""
+    """The Gray-Scott schedule (the two-species x pass with the reaction, batched y and z passes of
+    both species, with and without spectral states) against the oracle's two-species steps."""
     from oracle import gray_scott as gs
     p = gs.GSParams(dt=0.8)
     u0 = quench_field(shape, 0.7, 0.3, seed=31)

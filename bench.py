@@ -105,10 +105,10 @@ def summarize_trace(d: str, name: str):
 
 
 def _pass_of_kernel(name: str):
-    """Pass of a stepper kernel from its template arguments (col_kernel<N, BC, MODE>: MODE 0 forward
-    y, 1 inverse y, 3 fused z update; row_kernel<NH, BC, MODE>: MODE 0 fused x with f')."""
+    """Pass of a stepper kernel from its template arguments (col_kernel<N, BC, MODE, ...>: MODE 0
+    forward y, 1 inverse y, 3 fused z update; row_kernel<NH, BC, MODE, ...>: MODE 0 fused x with f')."""
     import re
-    m = re.search(r"evx::(col|row)_kernel<(\d+), (\d+), (\d+)>", name)
+    m = re.search(r"evx::(col|row)_kernel<(\d+), (\d+), (\d+)[,>]", name)
     if not m:
         return None
     kind, mode = m.group(1), int(m.group(4))

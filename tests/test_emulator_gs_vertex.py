@@ -50,3 +50,11 @@ def test_states_on_a_vertex_z(kind, shape, bc):
     got, ref = gs_emulated(_build(kind), shape, bc, "stencil7", 2)
     for a, b in zip(got, ref):
         assert _rel(a, b) <= 1e-6
+
+
+@pytest.mark.parametrize("kind", ["asan", "tsan"])
+def test_one_step(kind):
+    """A call of one step takes its reactions from the real fields."""
+    got, ref = gs_emulated(_build(kind), (25, 8, 8), (VX, "periodic", "dirichlet"), "stencil7", 1)
+    for a, b in zip(got, ref):
+        assert _rel(a, b) <= 1e-6

@@ -26,7 +26,8 @@ constexpr int col_min_waves() {
 }
 
 template <int N, int BC, int MODE, int SEQS = ColCfg<N>::B>
-__global__ __launch_bounds__((ColCfg<N, SEQS>::THREADS), (col_min_waves<N, BC>())) void col_kernel(ColArgs a) {
+__global__ __launch_bounds__((ColCfg<N, SEQS>::THREADS), (col_min_waves<N, BC>())) void col_kernel(
+    ColArgs a) {
   __shared__ float2 lds[ColCfg<N, SEQS>::LDS];
   colpass_body<N, BC, MODE, SEQS>(a, threadIdx.x, blockIdx.x, gridDim.x, lds);
 }

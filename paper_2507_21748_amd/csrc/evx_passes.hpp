@@ -1126,9 +1126,9 @@ inline bool row_fits32(const RowArgs& a) {
 }
 
 // Whether a row pass stages its spectral rows (SpecRows, CosRows): short rows on grids of many.  Fused
-// pass direct -> staged: 1024 x 1024 x 16 87.6 -> 40.9 us, 512 x 512 x 16 29.5 -> 14.4, 512 x 512 x 40 42.7
-// -> 23.6, 1024 x 1024 x 64 170 -> 135; but 128 x 128 x 16 7.2 -> 7.7, 64 x 64 x 20 6.8 -> 7.7 and, four lanes
-// a row, 256 x 256 x 96 16.8 -> 17.5 (512 x 512 x 96 42.2 either way).
+// pass direct -> staged: 1024 x 1024 x 16 87.6 -> 40.9 us, 512 x 512 x 16 29.5 -> 14.4, 512 x 512 x 40
+// 42.7 -> 23.6, 1024 x 1024 x 64 170 -> 135; but 128 x 128 x 16 7.2 -> 7.7, 64 x 64 x 20 6.8 -> 7.7 and,
+// four lanes a row, 256 x 256 x 96 16.8 -> 17.5 (512 x 512 x 96 42.2 either way).
 // Cosine rows keep their bins in LDS anyway and lose by the direct way only with complex columns, of
 // whose 8 bytes it takes 4 (512 x 512 x 20 mixed 44.3 -> 21.9, 1024 x 1024 x 40 177 -> 117), and with pair
 // columns on rows of one lane (1024 x 1024 x 12 zero flux 49.4 -> 29.4); 256 x 256 rows lose by neither.
@@ -1807,8 +1807,9 @@ EVX_DEV void rowpass_comb_body(const RowArgs& a, int tid, long long r0, float2* 
 // ROW_FUSED_POLY; ROW_FWD starts from real rows) for the B rows from r0.  Periodic rows: a lane
 // holds its points of both species.  Cosine rows: one sequence holds a row of both.
 // Bound by memory traffic and occupancy (71 to 235 VGPRs for both species' points, 84 at 256^3, five
-// waves a SIMD): 65 us at 256^3 periodic, 4.2 TB/s.  With a reaction kernel, four fields' forward transforms and an update kernel
-// of its own a step took 0.61 ms at 256^3; with this pass and the multiplier in the z pass 0.19 ms.
+// waves a SIMD): 65 us at 256^3 periodic, 4.2 TB/s.  With a reaction kernel, four fields' forward
+// transforms and an update kernel of its own a step took 0.61 ms at 256^3; with this pass and the
+// multiplier in the z pass 0.19 ms.
 template <int NH, int BC, int MODE>
 EVX_DEV void rowpass_gs_body(const RowArgs& a, int tid, long long r0, float2* lds) {
   using C = RowCfg<NH, BC>;

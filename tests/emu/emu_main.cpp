@@ -62,10 +62,11 @@ static void run_grid(int nblk, int threads, int lds_slots, Body body) {
 struct EmuLauncher {
   template <int N, int BC, int MODE>
   void col_t(const ColArgs& a) {
-    if (wide_seqs<N>() != ColCfg<N>::B && col_wide<N>(a) && a.sp.mode == SP_NONE)
-      col_s<N, BC, MODE, wide_seqs<N>()>(a);
-    else
-      col_s<N, BC, MODE, ColCfg<N>::B>(a);
+    if constexpr (MODE == COL_FWD || MODE == COL_Z_INIT || MODE == COL_Z_UPDATE) {
+      if (wide_seqs<N>() != ColCfg<N>::B && col_wide<N>(a) && a.sp.mode == SP_NONE)
+        return col_s<N, BC, MODE, wide_seqs<N>()>(a);
+    }
+    col_s<N, BC, MODE, ColCfg<N>::B>(a);
   }
   template <int N, int BC, int MODE, int SEQS>
   void col_s(const ColArgs& a) {
@@ -87,7 +88,8 @@ struct EmuLauncher {
     using C = RowCfg<NH, BC>;
     const int nblk = int((a.nrows + C::ROWS - 1) / C::ROWS);
     run_grid(nblk, C::THREADS, C::LDS, [&](int tid, int bid, int nb, float2* lds) {
-      if constexpr (C::SHORT) {
+      // (the modes that stage the rows' way in, out and both; each form compiles for a minute or so)
+      if constexpr (C::SHORT && (MODE == ROW_FUSED || MODE == ROW_FWD || MODE == ROW_INV)) {
         if (row_staged<NH, BC>(a)) return rowpass_body<NH, BC, MODE, true>(a, tid, bid, nb, lds);
       }
       rowpass_body<NH, BC, MODE>(a, tid, bid, nb, lds);
